@@ -179,7 +179,7 @@ awsrc_status encode_module(const awsrc_params* p, const void* W, int32_t w_dtype
   a.seed_out = seed_out; a.code_out = code_out; a.scale_out = scale_out; a.gain_out = gain_out;
   a.alpha_out = alpha_or_null;
   HIPCHK(launch_scored_init(a, s, add_scored));
-  HIPCHK(launch_gen_basis(p->basis_key, p->C, p->P, p->S, p->gen_version, a.basis, s));
+  HIPCHK(launch_gen_basis(p->basis_key, p->C, p->P, p->S, p->gen_version, a.basis, false, s));
   if (d_mode == AWSRC_D_PER_COL) HIPCHK(launch_col_factors(a, s));
   HIPCHK(launch_encode_screen(a, s));
   if (!a.fused_rescore) HIPCHK(launch_encode_finalize(a, s));
@@ -209,6 +209,41 @@ PeLayout pe_layout(const awsrc_params* p, int n_modules, int64_t items) {
   return l;
 }
 
+// Workspace of the C = 16 encoder: count | row tables | sign patterns |
+// module table (several modules) or the screen's lists (one module).
+struct C16Layout {
+  size_t frag, masks, mods, list, total;
+};
+C16Layout c16_layout(const awsrc_params* p, int n_modules, int64_t T_total) {
+  C16Layout l;
+  l.frag = align_up(c16_frag_bytes(p->S), 256);
+  l.masks = align_up(c16_mask_bytes(p->S), 256);
+  l.mods = n_modules > 1 ? align_up((size_t)n_modules * sizeof(ModEntry), 256) : 0;
+  l.list = n_modules > 1 ? 0 : align_up((size_t)T_total * kTop * 4, 256);
+  l.total = 256 + l.frag + l.masks + l.mods + 2 * l.list + 256;
+  return l;
+}
+
+// Module table of a batched encode, with work items of `unit` rows x one
+// column block (unit > 0) or of 64 tiles in tile order (unit == 0); returns
+// the number of items.
+int64_t module_entries(const awsrc_params* p, int n_modules, const void* const* W, const float* const* W0,
+                       const float* const* d, const int64_t* rows, const int64_t* cols, int unit,
+                       std::vector<ModEntry>& tab) {
+  tab.resize(n_modules);
+  int64_t t0 = 0, items = 0;
+  for (int m = 0; m < n_modules; ++m) {
+    const int64_t nb = cols[m] / p->C;
+    ModEntry& e = tab[m];
+    e.W = W[m]; e.W0 = W0[m]; e.d = d[m];
+    e.rows = rows[m]; e.cols = cols[m];
+    e.tile_off = t0; e.item_off = items; e.pad_ = 0;
+    t0 += rows[m] * nb;
+    items += unit ? (rows[m] + unit - 1) / unit * nb : c16_items(rows[m] * nb);
+  }
+  return items;
+}
+
 // The encoder over n modules with outputs concatenated in module order.
 awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void* const* W, int32_t w_dtype,
                             const float* const* W0, const float* const* d, int32_t d_mode, const int64_t* rows,
@@ -230,9 +265,12 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
     T_total += T;
   }
   if (T_total > (int64_t)UINT32_MAX) return fail(AWSRC_EINVAL, "more than 2^32 tiles");
+  const bool c16 = c16_supported(p->C, p->P);
   const bool batched = pe_batched_supported(p->C, p->P, d_mode, p->gen_version);
   size_t need = 0;
-  if (batched) {
+  if (c16) {
+    need = c16_layout(p, n_modules, T_total).total;
+  } else if (batched) {
     need = pe_layout(p, n_modules, pe_items(p, n_modules, rows, cols)).total;
   } else {
     for (int m = 0; m < n_modules; ++m) {
@@ -253,6 +291,31 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
   }
   char* ws = reinterpret_cast<char*>(align_up(reinterpret_cast<uintptr_t>(workspace), 256));
   hipStream_t s = (hipStream_t)stream;
+  if (c16) {
+    const C16Layout l = c16_layout(p, n_modules, T_total);
+    EncodeArgs a{};
+    a.w_dtype = w_dtype; a.d_mode = d_mode;
+    a.C = p->C; a.P = p->P; a.b = p->b; a.S = p->S;
+    a.lambda = p->ridge_lambda;
+    a.scale_fmt = p->scale_fmt;
+    a.gen_version = p->gen_version;
+    a.scored = reinterpret_cast<unsigned long long*>(ws);
+    char* frag = ws + 256;
+    char* masks = frag + l.frag;
+    ModEntry* mods = reinterpret_cast<ModEntry*>(masks + l.masks);
+    if (l.list) {
+      a.top_gain = reinterpret_cast<float*>(masks + l.masks);
+      a.top_seed = reinterpret_cast<uint32_t*>(masks + l.masks + l.list);
+    }
+    a.seed_out = seed_out; a.code_out = code_out; a.scale_out = scale_out; a.gain_out = gain_out;
+    a.alpha_out = alpha_or_null;
+    std::vector<ModEntry> tab;
+    const int64_t items = module_entries(p, n_modules, W, W0, d, rows, cols, 0, tab);
+    if (n_modules > 1) HIPCHK(launch_mod_table(tab.data(), n_modules, mods, s));
+    HIPCHK(launch_encode_c16(a, p->basis_key, tab[0], mods, n_modules, items,
+                             (unsigned long long)T_total * (unsigned long long)p->S, frag, masks, s));
+    return AWSRC_OK;
+  }
   if (!batched) {
     int64_t t0 = 0;
     bool first = true;
@@ -291,21 +354,12 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
   a.nsplit = 1;
   a.seed_out = seed_out; a.code_out = code_out; a.scale_out = scale_out; a.gain_out = gain_out;
   a.alpha_out = alpha_or_null;
-  std::vector<ModEntry> tab(n_modules);
-  int64_t t0 = 0, items = 0;
-  for (int m = 0; m < n_modules; ++m) {
-    const int64_t nb = cols[m] / p->C;
-    ModEntry& e = tab[m];
-    e.W = W[m]; e.W0 = W0[m]; e.d = d[m];
-    e.rows = rows[m]; e.cols = cols[m];
-    e.tile_off = t0; e.item_off = items; e.pad_ = 0;
-    t0 += rows[m] * nb;
-    items += (rows[m] + kPeRows - 1) / kPeRows * nb;
-  }
+  std::vector<ModEntry> tab;
+  const int64_t items = module_entries(p, n_modules, W, W0, d, rows, cols, kPeRows, tab);
   if (items > (int64_t)INT32_MAX) return fail(AWSRC_EINVAL, "too many work items");
   HIPCHK(launch_mod_table(tab.data(), n_modules, mods, s));
   HIPCHK(launch_scored_zero(a.scored, s));  // the pruned screen adds its count
-  HIPCHK(launch_gen_basis(p->basis_key, p->C, p->P, p->S, p->gen_version, a.basis, s));
+  HIPCHK(launch_gen_basis(p->basis_key, p->C, p->P, p->S, p->gen_version, a.basis, false, s));
   HIPCHK(launch_pe_screen(a, mods, n_modules, items, a.frag, colsh, s));
   HIPCHK(launch_finalize_pe_modules(a, mods, n_modules, items, s));
   return AWSRC_OK;
@@ -356,6 +410,17 @@ extern "C" awsrc_status awsrc_encode_screen_lists(const awsrc_params* p, int32_t
     return AWSRC_OK;
   }
   if (n_modules != 1) return fail(AWSRC_EINVAL, "lists of several modules on the per-module path are not kept");
+  if (c16_supported(p->C, p->P)) {
+    const C16Layout l = c16_layout(p, 1, T_total);
+    *nsplit = 1;
+    if (!gain_out && !seed_out) return AWSRC_OK;
+    if (!gain_out || !seed_out) return fail(AWSRC_EINVAL, "NULL output");
+    const char* tg = ws + 256 + l.frag + l.masks;
+    const size_t n = (size_t)T_total * kTop;
+    HIPCHK(hipMemcpyAsync(gain_out, tg, n * 4, hipMemcpyDeviceToDevice, s));
+    HIPCHK(hipMemcpyAsync(seed_out, tg + l.list, n * 4, hipMemcpyDeviceToDevice, s));
+    return AWSRC_OK;
+  }
   const int ns = screen_nsplit(p->C, p->P, p->S, rows[0], cols[0], d_mode, p->gen_version);
   if (screen_fuses_rescore(p->C, p->P, d_mode, p->gen_version, ns))
     return fail(AWSRC_EINVAL, "this screen runs the re-score itself and keeps no lists");
@@ -715,7 +780,7 @@ extern "C" awsrc_status awsrc_decode_prepare(const uint8_t* stream_bytes, uint64
   const DecodeArgs a = decode_args(&pl);
   memcpy(tabs.data() + 2 * (size_t)nmod + 1, W0_ptrs, nmod * sizeof(void*));
   HIPCHK(hipMemcpyAsync(const_cast<uint64_t*>(a.mod_tile_off), tabs.data(), tabs.size() * 8, hipMemcpyHostToDevice, s));
-  HIPCHK(launch_gen_basis(key, C, P, (int)S, gen, a.basis, s));
+  HIPCHK(launch_gen_basis(key, C, P, (int)S, gen, a.basis, true, s));
   HIPCHK(launch_decode_validate(a, s));
   unsigned long long nerr = 0;
   HIPCHK(hipMemcpyAsync(&nerr, a.errors, 8, hipMemcpyDeviceToHost, s));

@@ -232,7 +232,9 @@ __device__ __forceinline__ float screen_score_ldl(const float (&b)[PB], const FP
 // Each returns hipSuccess or the first HIP error.
 // Basis tables of GenBasis version gen_version (1: signs and columns; 2: also
 // the seeded coordinate permutation, B_s[j, p] = sigma_j H[pi(j), c_p]/sqrt(C)).
-hipError_t launch_gen_basis(uint64_t key, int C, int P, int S, int gen_version, BasisTables t, hipStream_t st);
+// tsign (the decoder's transposed table) is built only on request.
+hipError_t launch_gen_basis(uint64_t key, int C, int P, int S, int gen_version, BasisTables t, bool tsign,
+                            hipStream_t st);
 
 // Scale double quantization of the backbone's group scales (blocks of 256).
 int64_t sdq_blocks(int64_t n_groups);
@@ -334,6 +336,17 @@ hipError_t launch_finalize_pe_modules(const EncodeArgs& a, const ModEntry* mods,
 // order ([T][kTop]), for awsrc_encode_screen_lists.
 hipError_t launch_pe_lists_tile_order(const float* tg, const uint32_t* ts, const ModEntry* mods, int n_mods,
                                       int64_t items, float* gain_out, uint32_t* seed_out, hipStream_t st);
+
+// C = 16, P <= 4: screen and re-score of every module in one launch, on row
+// tables of its own (no BasisTables).  Modules are linear runs of tiles, 64
+// per work item; `one` is the module itself when n_mods == 1 (no table).
+// a.top_gain / a.top_seed: where to keep the screen's lists, or null.
+bool c16_supported(int C, int P);
+int64_t c16_items(int64_t tiles);
+size_t c16_frag_bytes(int S);
+size_t c16_mask_bytes(int S);
+hipError_t launch_encode_c16(const EncodeArgs& a, uint64_t key, const ModEntry& one, const ModEntry* mods, int n_mods,
+                             int64_t items, unsigned long long candidates, void* frag, void* masks, hipStream_t st);
 
 bool encode_supported(int C, int P);
 // the matrix-core screens: C = 64 (P <= 8), C = 128 (P <= 8, per-column

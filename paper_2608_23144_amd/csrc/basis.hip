@@ -12,35 +12,9 @@
 // (pi(j) = rank of (key_j, j)), and builds the negative-entry patterns
 // sigma_j xor parity(pi(j) & c_p) by wavefront ballots.
 #include "awsrc_internal.h"
+#include "basis_gen.h"
 
 namespace awsrc {
-
-// Position of the m-th zero bit (0-based) among the low `width` bits of w.
-__device__ __forceinline__ int nth_zero(uint64_t w, int m, int width) {
-  uint64_t z = ~w;
-  if (width < 64) z &= (1ull << width) - 1ull;
-  int pos = 0;
-#pragma unroll
-  for (int half = 32; half >= 1; half >>= 1) {
-    const uint64_t lowmask = (1ull << half) - 1ull;
-    const int cnt = __popcll(z & lowmask);
-    if (m >= cnt) { m -= cnt; z >>= half; pos += half; }
-  }
-  return pos;
-}
-
-// Bit j of the result is parity(j & c) for j = 64*w .. 64*w + 63: the XOR of
-// the patterns "bit b of j" over the set bits b of c.
-__device__ __forceinline__ uint64_t hadamard_neg_word(int c, int w) {
-  const uint64_t pat[6] = {0xAAAAAAAAAAAAAAAAull, 0xCCCCCCCCCCCCCCCCull, 0xF0F0F0F0F0F0F0F0ull,
-                           0xFF00FF00FF00FF00ull, 0xFFFF0000FFFF0000ull, 0xFFFFFFFF00000000ull};
-  uint64_t x = 0ull;
-#pragma unroll
-  for (int b = 0; b < 6; ++b)
-    if ((c >> b) & 1) x ^= pat[b];
-  if (((c >> 6) & 1) && w == 1) x = ~x;
-  return x;
-}
 
 __global__ void k_gen_basis(uint64_t key, int C, int P, int S, int gen_version, uint64_t* __restrict__ sign,
                             uint64_t* __restrict__ mask, uint8_t* __restrict__ col) {
@@ -56,15 +30,7 @@ __global__ void k_gen_basis(uint64_t key, int C, int P, int S, int gen_version, 
   const uint64_t valid0 = C < 64 ? (1ull << C) - 1ull : ~0ull;
   uint64_t used[2] = {0ull, 0ull};
   for (int p = 0; p < P; ++p) {
-    const uint64_t v = splitmix64(key, base + (uint64_t)(nw + p));
-    int m = (int)(((v >> 32) * (uint64_t)(C - p)) >> 32);  // Lemire multiply-shift into [0, C-p)
-    // the m-th smallest column not drawn yet
-    const int w0 = C < 64 ? C : 64;
-    const int z0 = w0 - __popcll(used[0] & valid0);
-    int c;
-    if (m < z0) c = nth_zero(used[0], m, w0);
-    else c = 64 + nth_zero(used[1], m - z0, 64);
-    used[c >> 6] |= 1ull << (c & 63);
+    const int c = draw_column(key, base, nw, C, p, used);
     col[(size_t)s * kMaxP + p] = (uint8_t)c;
     if (gen_version != 1) continue;  // version 2: k_basis_perm builds the patterns
     for (int w = 0; w < 2; ++w) {
@@ -122,12 +88,14 @@ __global__ __launch_bounds__(64) void k_basis_perm(uint64_t key, int C, int P, B
     for (int p = 0; p < P; ++p) t.mask[((size_t)s * P + p) * 2 + 1] = 0ull;
 }
 
-hipError_t launch_gen_basis(uint64_t key, int C, int P, int S, int gen_version, BasisTables t, hipStream_t st) {
+hipError_t launch_gen_basis(uint64_t key, int C, int P, int S, int gen_version, BasisTables t, bool tsign,
+                            hipStream_t st) {
   const int threads = 64;
   const int blocks = (S + threads - 1) / threads;
   hipLaunchKernelGGL(k_gen_basis, dim3(blocks), dim3(threads), 0, st, key, C, P, S, gen_version, t.sign,
                      t.mask, t.col);
   if (gen_version == 2) hipLaunchKernelGGL(k_basis_perm, dim3((unsigned)S), dim3(64), 0, st, key, C, P, t);
+  if (!tsign) return hipGetLastError();
   const int64_t n = (int64_t)S * C;
   hipLaunchKernelGGL(k_basis_tsign, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, C, P, S,
                      t.mask, t.tsign);

@@ -828,8 +828,7 @@ static hipError_t run_finalize(const EncodeArgs& a, hipStream_t st) {
   do {                                                                  \
     const int pb_ = PBSEL((a).C, (a).P);                                \
     switch ((a).C) {                                                    \
-      case 16:                                                          \
-        if (pb_ == 4) return FN<16, 4>(a, st);                          \
+      case 16: /* P <= 4: encode_c16.hip */                             \
         if (pb_ == 8) return FN<16, 8>(a, st);                          \
         return FN<16, 16>(a, st);                                       \
       case 32:                                                          \

@@ -188,6 +188,47 @@ def test_encode_generator_v2(C, P, b, S, rows, cols, d_mode):
     assert nd <= max(1, T // 50)
 
 
+@pytest.mark.parametrize("P,b,S,d_mode,gen,fmt,name", [
+    (4, 4, 16, "elem", 1, 1, "block3b"), (4, 4, 16, "elem", 2, 1, "block3b"), (4, 4, 16, "col", 1, 0, "linear256"),
+    (4, 3, 33, "col", 2, 0, "block3b"), (3, 5, 2, "elem", 1, 0, "linear256"), (1, 4, 7, "col", 1, 1, "block3b"),
+    (2, 2, 64, "elem", 2, 0, "block3b")])
+def test_encode_c16(P, b, S, d_mode, gen, fmt, name):
+    """The C = 16, P <= 4 encoder (four seeds per row table, 64 tiles per
+    wavefront): padded columns, seed counts off a multiple of four, modules
+    whose tiles end inside a wavefront or number less than one group of 16,
+    an empty module, both weight types, scale formats and generators, into a
+    workspace of 0xFF bytes; one call over all modules equals one per module."""
+    wl = workload(name, C=16, P=P, b=b, S=S, d_mode=d_mode)
+    mods = [Module("a", 9, 128, 0, 1, 1), Module("none", 0, 128, 0, 2, 2), Module("b", 1, 128, 0, 3, 3),
+            Module("c", 33, 384, 0, 4, 4)]
+    p = _params(wl, fmt, gen)
+    inps = [gen_module_inputs(wl, m, DEV) for m in mods]
+    W0s = [awsrc.awsrc_backbone_rtn(i["W"])[3] if m.rows else torch.empty(0, m.cols, device=DEV)
+           for m, i in zip(mods, inps)]
+    shapes = [(m.rows, m.cols) for m in mods]
+    dm = awsrc.AWSRC_D_PER_COL if d_mode == "col" else awsrc.AWSRC_D_PER_ELEM
+    dt = awsrc.AWSRC_DTYPE_F32 if wl.w_dtype == "f32" else awsrc.AWSRC_DTYPE_BF16
+    ws = torch.full((awsrc.encode_modules_workspace_bytes(p, shapes, dt, dm),), 0xFF, dtype=torch.uint8, device=DEV)
+    got = awsrc.awsrc_encode_modules(p, [i["W"] for i in inps], W0s, [i["d"] for i in inps], want_alpha=True,
+                                     workspace=ws)
+    assert awsrc.awsrc_encode_scored(got) == got["seed"].numel() * S
+    off = 0
+    for m, inp, W0 in zip(mods, inps, W0s):
+        T = m.rows * m.cols // 16
+        if not T:
+            continue
+        ref = awsrc.awsrc_encode_tiles(p, inp["W"], W0, inp["d"], want_alpha=True)
+        for k in ("seed", "codes", "scale", "gain", "alpha"):
+            assert torch.equal(got[k][off:off + T], ref[k]), (m.name, k)
+        g32, w32 = awsrc.awsrc_encode_screen_lists(p, [(m.rows, m.cols)], dm, ref["workspace"])
+        assert g32.shape == (T, 1, 2) and bool(((w32 & 0xFFFF) < S).all())
+        # the stored record is one of the two kept, and the screen's score of it is near its gain
+        kept = (w32[:, 0] & 0xFFFF) == (ref["seed"].to(torch.int32) & 0xFFFF)[:, None]
+        assert bool(kept.any(1).all())
+        assert _check_encode_sample(wl, m, inp, W0, ref, np.arange(T), fmt, gen) <= max(1, T // 50)
+        off += T
+
+
 def test_pipeline_generator_v2_matches_oracle():
     """Version-2 encode, rank and decode against the oracle's stream: the
     records the GPU ranks are the oracle's where seeds agree, the stream's
