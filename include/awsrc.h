@@ -99,9 +99,10 @@ enum { AWSRC_SCALE_FP16 = 0, AWSRC_SCALE_POW2 = 1 };
  *               signs and columns plus the seeded coordinate permutation of
  *               Eq. (2) / Sec. 3.1: coordinate j draws word ceil(C/64)+P+j and
  *               pi_s(j) is the rank of (word, j) in increasing order.  With
- *               per-element weights version 2 runs on the vector screen (the
- *               Gram entries need a transform of the permuted weights per
- *               seed); per-column weights keep the matrix-core screen.
+ *               per-element weights at C = 64, P <= 8 the Gram entries are
+ *               matrix products too; at other shapes (but C = 16, P <= 4)
+ *               they need a transform of the permuted weights per seed, on
+ *               the vector screen.
  *  reserved     must be 0.
  *  basis_key    generator key, stored in the stream header.
  *  ridge_lambda eps_t = ridge_lambda * mean_j d_{t,j} in Eq. (3); >= 0.
@@ -204,8 +205,9 @@ awsrc_status awsrc_encode_tiles(const awsrc_params* p, const void* W, int32_t w_
  * are those of calling awsrc_encode_tiles once per module.  With per-element
  * weights, C = 64, P <= 8 and generator version 1 (the Fisher-blended weights
  * of Sec. 3.3 at the workloads' shapes) every module is screened in one
- * launch, so that small modules do not leave the GPU idle; otherwise the
- * modules are encoded one after another.
+ * launch, so that small modules do not leave the GPU idle, likewise with
+ * generator version 2 and with C = 16, P <= 4; otherwise the modules are
+ * encoded one after another.
  *  W, W0, d     host arrays [n_modules] of device pointers, each module's
  *               inputs as in awsrc_encode_tiles (16-byte aligned).
  *  rows, cols   host arrays [n_modules]; cols % C == 0; rows may be 0.

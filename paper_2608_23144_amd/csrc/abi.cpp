@@ -217,30 +217,46 @@ struct C16Layout {
 C16Layout c16_layout(const awsrc_params* p, int n_modules, int64_t T_total) {
   C16Layout l;
   l.frag = align_up(c16_frag_bytes(p->S), 256);
-  l.masks = align_up(c16_mask_bytes(p->S), 256);
+  l.masks = align_up(c16_info_bytes(p->S), 256);
   l.mods = n_modules > 1 ? align_up((size_t)n_modules * sizeof(ModEntry), 256) : 0;
   l.list = n_modules > 1 ? 0 : align_up((size_t)T_total * kTop * 4, 256);
   l.total = 256 + l.frag + l.masks + l.mods + 2 * l.list + 256;
   return l;
 }
 
+// Workspace of the version-2 per-element encoder (C = 64): count | basis | the
+// screen's lists in tile order | module table (several modules).
+struct PermLayout {
+  size_t basis, list, mods, total;
+};
+PermLayout perm_layout(const awsrc_params* p, int n_modules, int64_t T_total) {
+  PermLayout l;
+  l.basis = align_up(basis_bytes(p->S, p->P), 256);
+  l.list = align_up((size_t)T_total * kTop * 4, 256);
+  l.mods = n_modules > 1 ? align_up((size_t)n_modules * sizeof(ModEntry), 256) : 0;
+  l.total = 256 + l.basis + 2 * l.list + l.mods + 256;
+  return l;
+}
+
 // Module table of a batched encode, with work items of `unit` rows x one
 // column block (unit > 0) or of 64 tiles in tile order (unit == 0); returns
-// the number of items.
+// the number of items.  *items2: those of kPermRows rows.
 int64_t module_entries(const awsrc_params* p, int n_modules, const void* const* W, const float* const* W0,
                        const float* const* d, const int64_t* rows, const int64_t* cols, int unit,
-                       std::vector<ModEntry>& tab) {
+                       std::vector<ModEntry>& tab, int64_t* items2 = nullptr) {
   tab.resize(n_modules);
-  int64_t t0 = 0, items = 0;
+  int64_t t0 = 0, items = 0, n2 = 0;
   for (int m = 0; m < n_modules; ++m) {
     const int64_t nb = cols[m] / p->C;
     ModEntry& e = tab[m];
     e.W = W[m]; e.W0 = W0[m]; e.d = d[m];
     e.rows = rows[m]; e.cols = cols[m];
-    e.tile_off = t0; e.item_off = items; e.pad_ = 0;
+    e.tile_off = t0; e.item_off = items; e.item2_off = n2;
     t0 += rows[m] * nb;
     items += unit ? (rows[m] + unit - 1) / unit * nb : c16_items(rows[m] * nb);
+    n2 += (rows[m] + kPermRows - 1) / kPermRows * nb;
   }
+  if (items2) *items2 = n2;
   return items;
 }
 
@@ -268,8 +284,11 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
   const bool c16 = c16_supported(p->C, p->P);
   const bool batched = pe_batched_supported(p->C, p->P, d_mode, p->gen_version);
   size_t need = 0;
+  const bool perm = perm_batched_supported(p->C, p->P, d_mode, p->gen_version);
   if (c16) {
     need = c16_layout(p, n_modules, T_total).total;
+  } else if (perm) {
+    need = perm_layout(p, n_modules, T_total).total;
   } else if (batched) {
     need = pe_layout(p, n_modules, pe_items(p, n_modules, rows, cols)).total;
   } else {
@@ -312,8 +331,35 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
     std::vector<ModEntry> tab;
     const int64_t items = module_entries(p, n_modules, W, W0, d, rows, cols, 0, tab);
     if (n_modules > 1) HIPCHK(launch_mod_table(tab.data(), n_modules, mods, s));
+    if (items > (int64_t)INT32_MAX) return fail(AWSRC_EINVAL, "too many work items");
     HIPCHK(launch_encode_c16(a, p->basis_key, tab[0], mods, n_modules, items,
                              (unsigned long long)T_total * (unsigned long long)p->S, frag, masks, s));
+    return AWSRC_OK;
+  }
+  if (perm) {
+    const PermLayout l = perm_layout(p, n_modules, T_total);
+    EncodeArgs a{};
+    a.w_dtype = w_dtype; a.d_mode = d_mode;
+    a.C = p->C; a.P = p->P; a.b = p->b; a.S = p->S;
+    a.lambda = p->ridge_lambda;
+    a.scale_fmt = p->scale_fmt;
+    a.gen_version = p->gen_version;
+    a.scored = reinterpret_cast<unsigned long long*>(ws);
+    a.basis = carve_basis(ws + 256, p->S, p->P);
+    a.top_gain = reinterpret_cast<float*>(ws + 256 + l.basis);
+    a.top_seed = reinterpret_cast<uint32_t*>(ws + 256 + l.basis + l.list);
+    ModEntry* mods = reinterpret_cast<ModEntry*>(ws + 256 + l.basis + 2 * l.list);
+    a.seed_out = seed_out; a.code_out = code_out; a.scale_out = scale_out; a.gain_out = gain_out;
+    a.alpha_out = alpha_or_null;
+    std::vector<ModEntry> tab;
+    int64_t items2 = 0;
+    const int64_t items = module_entries(p, n_modules, W, W0, d, rows, cols, kPeRows, tab, &items2);
+    if (items > (int64_t)INT32_MAX) return fail(AWSRC_EINVAL, "too many work items");
+    if (n_modules > 1) HIPCHK(launch_mod_table(tab.data(), n_modules, mods, s));
+    HIPCHK(launch_scored_zero(a.scored, s));  // the pruned screen adds its count
+    HIPCHK(launch_gen_basis(p->basis_key, p->C, p->P, p->S, p->gen_version, a.basis, false, s));
+    HIPCHK(launch_perm_screen(a, tab[0], mods, n_modules, items2, s));
+    HIPCHK(launch_finalize_pe_modules(a, tab[0], mods, n_modules, items, s));
     return AWSRC_OK;
   }
   if (!batched) {
@@ -361,7 +407,7 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
   HIPCHK(launch_scored_zero(a.scored, s));  // the pruned screen adds its count
   HIPCHK(launch_gen_basis(p->basis_key, p->C, p->P, p->S, p->gen_version, a.basis, false, s));
   HIPCHK(launch_pe_screen(a, mods, n_modules, items, a.frag, colsh, s));
-  HIPCHK(launch_finalize_pe_modules(a, mods, n_modules, items, s));
+  HIPCHK(launch_finalize_pe_modules(a, tab[0], mods, n_modules, items, s));
   return AWSRC_OK;
 }
 

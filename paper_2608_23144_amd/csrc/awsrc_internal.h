@@ -29,6 +29,8 @@ __host__ __device__ __forceinline__ uint64_t splitmix64(uint64_t key, uint64_t n
 //   mask[s][p][w]   bit j set <=> B_s[j, p] < 0, i.e. sigma_j xor parity(j & c_p)
 //   col[s][p]       the P selected Hadamard columns (draw order)
 //   tsign[s][j]     bit p set <=> B_s[j, p] < 0 (the mask transposed, one u16 per coordinate)
+//   sbytes(s)[c]    the same region before tsign is built, generator version 2, C <= 64, P <= 8:
+//                   byte p holds coordinates 8 c .. 8 c + 7 of the mask of column p (0 for p >= P)
 struct BasisTables {
   uint64_t* sign;
   uint64_t* mask;
@@ -36,6 +38,7 @@ struct BasisTables {
   uint16_t* tsign;
   uint8_t* perm;   // [S][kMaxC] pi(j) (generator version 2)
   uint8_t* iperm;  // [S][kMaxC] pi^-1(i) (generator version 2)
+  __host__ __device__ uint64_t* sbytes(int s) const { return reinterpret_cast<uint64_t*>(tsign + (size_t)s * kMaxC); }
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -182,6 +185,35 @@ __device__ __forceinline__ float screen_fwd(const float (&b)[PB], const FP& f, f
   return bound;
 }
 
+// G + eps I = L diag(e) L^T of one candidate in the layout of the per-column
+// table (strict lower L by rows, then 1/e, then e), from its strict lower
+// Gram entries gq (packed the same way) and its diagonal (eps included).
+// Padded columns (p >= P) get L = 0, e = 1; FULLP: P == PB, no padding.
+template <int PB, bool FULLP>
+__device__ __forceinline__ void screen_factor(const float (&gq)[PB * (PB - 1) / 2], float diag, int P,
+                                              float (&f)[PB * (PB - 1) / 2 + 2 * PB]) {
+  constexpr int LS = PB * (PB - 1) / 2;
+#pragma unroll
+  for (int p = 0; p < PB; ++p) {
+    const bool real = FULLP || p < P;
+    float E[PB];
+#pragma unroll
+    for (int q = 0; q < p; ++q) {
+      float t = real ? gq[ltri(p, q)] : 0.0f;
+#pragma unroll
+      for (int kk = 0; kk < q; ++kk) t = fmaf(-E[kk], f[ltri(q, kk)], t);
+      E[q] = t;
+      f[ltri(p, q)] = t * f[LS + q];
+    }
+    float t = real ? diag : 1.0f;
+#pragma unroll
+    for (int kk = 0; kk < p; ++kk) t = fmaf(-E[kk], f[ltri(p, kk)], t);
+    t = fmaxf(t, 1e-30f);
+    f[LS + PB + p] = t;
+    f[LS + p] = __builtin_amdgcn_rcpf(t);
+  }
+}
+
 template <int PB, bool POW2, int RAW, typename FP>
 __device__ __forceinline__ float screen_gain_w(const float (&w)[PB], const FP& f, float qmax, float inv_qmax,
                                                bool* edge) {
@@ -286,18 +318,19 @@ struct ModEntry {
   int64_t rows, cols;
   int64_t tile_off;
   int64_t item_off;
-  int64_t pad_;  // keeps entries at 64 bytes
+  int64_t item2_off;  // the same in another unit of rows (the version-2 screen's)
 };
 static_assert(sizeof(ModEntry) == 64, "module table entries are 64 bytes");
 
-// The module holding work item `item`: the last m with item_off <= item
-// (modules without work items share their successor's offset and are
-// skipped).  Wavefront-uniform.
+// The module holding work item `item`: the last m with item_off (or another
+// offset field) <= item (modules without work items share their successor's
+// offset and are skipped).  Wavefront-uniform.
+template <int64_t ModEntry::*OFF = &ModEntry::item_off>
 __device__ __forceinline__ int find_module(const ModEntry* mods, int n, int64_t item) {
   int lo = 0, hi = n - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (mods[mid].item_off <= item) lo = mid;
+    if (mods[mid].*OFF <= item) lo = mid;
     else hi = mid - 1;
   }
   return lo;
@@ -330,8 +363,10 @@ bool pe_batched_supported(int C, int P, int d_mode, int gen_version);
 size_t pe_colsh_bytes(int S);
 hipError_t launch_pe_screen(const EncodeArgs& a, const ModEntry* mods, int n_mods, int64_t items, const void* frag,
                             uint32_t* colsh, hipStream_t st);
-hipError_t launch_finalize_pe_modules(const EncodeArgs& a, const ModEntry* mods, int n_mods, int64_t items,
-                                      hipStream_t st);
+// The re-score of either generator version over 32-row items; `one` as for
+// launch_encode_c16 (version 1 always passes a table).
+hipError_t launch_finalize_pe_modules(const EncodeArgs& a, const ModEntry& one, const ModEntry* mods, int n_mods,
+                                      int64_t items, hipStream_t st);
 // The batched screen's top lists ([item][kTop][32], work-item major) in tile
 // order ([T][kTop]), for awsrc_encode_screen_lists.
 hipError_t launch_pe_lists_tile_order(const float* tg, const uint32_t* ts, const ModEntry* mods, int n_mods,
@@ -344,9 +379,9 @@ hipError_t launch_pe_lists_tile_order(const float* tg, const uint32_t* ts, const
 bool c16_supported(int C, int P);
 int64_t c16_items(int64_t tiles);
 size_t c16_frag_bytes(int S);
-size_t c16_mask_bytes(int S);
+size_t c16_info_bytes(int S);
 hipError_t launch_encode_c16(const EncodeArgs& a, uint64_t key, const ModEntry& one, const ModEntry* mods, int n_mods,
-                             int64_t items, unsigned long long candidates, void* frag, void* masks, hipStream_t st);
+                             int64_t items, unsigned long long candidates, void* frag, void* info, hipStream_t st);
 
 bool encode_supported(int C, int P);
 // the matrix-core screens: C = 64 (P <= 8), C = 128 (P <= 8, per-column
@@ -358,6 +393,12 @@ size_t mfma_frag_bytes(int C, int S);
 hipError_t launch_mfma_frags(const BasisTables& bt, int C, int P, int S, void* frag, hipStream_t st);
 // Seed ranges per tile for the screen (1 unless the matrix-core screen runs).
 int screen_nsplit(int C, int P, int S, int64_t rows, int64_t cols, int d_mode, int gen_version);
+// The screen for per-element weights and generator version 2 (C = 64,
+// P <= 8) over every module; lists in tile order, [T_total][kTop].
+bool perm_batched_supported(int C, int P, int d_mode, int gen_version);
+constexpr int kPermRows = 64;  // rows per workgroup (offsets in ModEntry::item2_off)
+hipError_t launch_perm_screen(const EncodeArgs& a, const ModEntry& one, const ModEntry* mods, int n_mods,
+                              int64_t items2, hipStream_t st);
 hipError_t launch_encode_screen_mfma(const EncodeArgs& a, void* frag, hipStream_t st);
 hipError_t launch_col_factors(const EncodeArgs& a, hipStream_t st);
 hipError_t launch_encode_screen(const EncodeArgs& a, hipStream_t st);

@@ -63,6 +63,7 @@ __global__ __launch_bounds__(64) void k_basis_perm(uint64_t key, int C, int P, B
   for (int j = threadIdx.x; j < C; j += 64) s_key[j] = splitmix64(key, base + (uint64_t)j);
   __syncthreads();
   const uint64_t sw0 = t.sign[2 * (size_t)s], sw1 = t.sign[2 * (size_t)s + 1];
+  uint64_t bytes = 0ull;  // lane c < 8: byte c of every column's pattern
   for (int h = 0; h < nw; ++h) {
     const int j = threadIdx.x + 64 * h;
     const bool on = j < C;
@@ -82,8 +83,10 @@ __global__ __launch_bounds__(64) void k_basis_perm(uint64_t key, int C, int P, B
       const bool neg = on && ((sg ^ (uint64_t)(__popc((unsigned)(rank & c)) & 1)) != 0);
       const uint64_t word = __ballot(neg);
       if (threadIdx.x == 0) t.mask[((size_t)s * P + p) * 2 + h] = word;
+      if (nw == 1 && p < 8) bytes |= ((word >> (8 * (threadIdx.x & 7))) & 0xFFull) << (8 * p);
     }
   }
+  if (nw == 1 && P <= 8 && threadIdx.x < 8) t.sbytes(s)[threadIdx.x] = bytes;
   if (nw == 1 && threadIdx.x == 0)
     for (int p = 0; p < P; ++p) t.mask[((size_t)s * P + p) * 2 + 1] = 0ull;
 }

@@ -27,6 +27,7 @@
 
 #include "awsrc_internal.h"
 #include "rescore64.h"
+#include "screen_valu.h"
 
 namespace awsrc {
 
@@ -152,30 +153,7 @@ __global__ __launch_bounds__(64) void k_col_factors(EncodeArgs a, int nb, int st
         G[p][q] = g;
       }
   }
-  // LDL^T (G is SPD: d > 0 and the columns are orthonormal)
-  double L[PB][PB], e[PB];
-#pragma unroll
-  for (int p = 0; p < PB; ++p) {
-#pragma unroll
-    for (int q = 0; q < p; ++q) {
-      double acc = G[p][q];
-#pragma unroll
-      for (int k = 0; k < q; ++k) acc -= L[p][k] * L[q][k] * e[k];
-      L[p][q] = acc / e[q];
-    }
-    double acc = G[p][p];
-#pragma unroll
-    for (int k = 0; k < p; ++k) acc -= L[p][k] * L[p][k] * e[k];
-    e[p] = fmax(acc, 1e-300);
-  }
-  float* out = a.colfac + (size_t)idx * stride;
-#pragma unroll
-  for (int p = 0; p < PB; ++p) {
-#pragma unroll
-    for (int q = 0; q < p; ++q) out[ltri(p, q)] = (float)L[p][q];
-    out[PB * (PB - 1) / 2 + p] = (float)(1.0 / e[p]);
-    out[PB * (PB - 1) / 2 + PB + p] = (float)e[p];
-  }
+  col_factor64<PB>(G, a.colfac + (size_t)idx * stride);
 }
 
 // ----------------------------------------------------------------------------
@@ -235,7 +213,6 @@ __global__ __launch_bounds__(64) void k_screen_valu(EncodeArgs a, int stride) {
     bool edge = false;
     if constexpr (PE) {
       // Cholesky factor of G = B^T D B + eps I from the Gram gathers
-      float L[PB][PB], inv[PB];
       const uint8_t* cs = a.basis.col + (size_t)s * kMaxP;
       int c[PB];
 #pragma unroll
@@ -248,66 +225,15 @@ __global__ __launch_bounds__(64) void k_screen_valu(EncodeArgs a, int stride) {
         fwht<C>(wd);
       }
       const float eps = (float)a.lambda * wd[0] * invC;
+      float G[PB][PB];
 #pragma unroll
       for (int p = 0; p < PB; ++p)
 #pragma unroll
         for (int q = 0; q <= p; ++q) {
-          float acc;
-          if (p < P && q < P) acc = wd[c[p] ^ c[q]] * invC + (p == q ? eps : 0.0f);
-          else acc = (p == q) ? 1.0f : 0.0f;
-#pragma unroll
-          for (int k = 0; k < q; ++k) acc -= L[p][k] * L[q][k];
-          if (p == q) {
-            L[p][p] = sqrtf(fmaxf(acc, 1e-30f));
-            inv[p] = 1.0f / L[p][p];
-          } else {
-            L[p][q] = acc * inv[q];
-          }
+          if (p < P && q < P) G[p][q] = wd[c[p] ^ c[q]] * invC + (p == q ? eps : 0.0f);
+          else G[p][q] = (p == q) ? 1.0f : 0.0f;
         }
-      // solve L L^T alpha = b
-      float z[PB], al[PB];
-#pragma unroll
-      for (int p = 0; p < PB; ++p) {
-        float acc = bv[p];
-#pragma unroll
-        for (int k = 0; k < p; ++k) acc -= L[p][k] * z[k];
-        z[p] = acc * inv[p];
-      }
-#pragma unroll
-      for (int p = PB - 1; p >= 0; --p) {
-        float acc = z[p];
-#pragma unroll
-        for (int k = p + 1; k < PB; ++k) acc -= L[k][p] * al[k];
-        al[p] = acc * inv[p];
-      }
-      // quantize with one fp16 scale and score
-      float m = 0.0f;
-#pragma unroll
-      for (int p = 0; p < PB; ++p) m = fmaxf(m, fabsf(al[p]));
-      float isc;
-      const float sc = pow2 ? screen_scale<true>(m, inv_qmax, &isc, &edge) : screen_scale<false>(m, inv_qmax, &isc, &edge);
-      g = 0.0f;
-      if (sc > 0.0f) {
-        float q[PB], t1 = 0.0f, qq = 0.0f;
-#pragma unroll
-        for (int p = 0; p < PB; ++p) {
-          const float x = al[p] * isc;
-          q[p] = fminf(fmaxf(rintf(x), -qmax), qmax);
-          edge = edge || code_edge(x, qmax);
-          t1 += q[p] * bv[p];
-          qq += q[p] * q[p];
-        }
-        float quad = 0.0f;
-#pragma unroll
-        for (int k = 0; k < PB; ++k) {
-          float y = 0.0f;
-#pragma unroll
-          for (int i = k; i < PB; ++i) y += L[i][k] * q[i];
-          quad += y * y;
-        }
-        quad -= eps * qq;
-        g = sc * (2.0f * t1 - sc * quad);
-      }
+      g = chol_score32<PB>(bv, G, eps, qmax, inv_qmax, pow2, &edge);
     } else {
       const float* fs = a.colfac + ((size_t)blk * a.S + s) * stride;
       g = pow2 ? screen_score_ldl<PB, true, 0>(bv, fs, qmax, inv_qmax, &edge)
@@ -788,10 +714,11 @@ template <int C, int PB>
 static hipError_t run_screen(const EncodeArgs& a, hipStream_t st) {
   const int nb = (int)(a.cols / C);
   const int64_t waves = nb * ((a.rows + 63) / 64);
-  if (a.d_mode == AWSRC_D_PER_ELEM && a.gen_version != 1)
-    hipLaunchKernelGGL((k_screen_valu<C, PB, true, true>), dim3((unsigned)waves), dim3(64), 0, st, a,
-                       colfac_stride(PB));
-  else if (a.d_mode == AWSRC_D_PER_ELEM)
+  if (a.d_mode == AWSRC_D_PER_ELEM && a.gen_version != 1) {
+    if constexpr (C != 64 || PB > 8)  // C = 64, P <= 8: encode_perm.hip
+      hipLaunchKernelGGL((k_screen_valu<C, PB, true, true>), dim3((unsigned)waves), dim3(64), 0, st, a,
+                         colfac_stride(PB));
+  } else if (a.d_mode == AWSRC_D_PER_ELEM)
     hipLaunchKernelGGL((k_screen_valu<C, PB, true, false>), dim3((unsigned)waves), dim3(64), 0, st, a,
                        colfac_stride(PB));
   else

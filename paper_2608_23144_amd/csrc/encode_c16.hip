@@ -22,19 +22,24 @@
 //     of two sign columns, which serve either generator version).  A lane then
 //     owns a whole candidate without any exchange.
 //   * Every candidate is scored in full (with 16 seeds, four per lane, there
-//     is little to prune); each lane keeps its two best, the four lanes of a
+//     is little to prune).  One whose rounding is on a knife edge (about 1e-3
+//     of them) is scored again in the general screen's arithmetic: with
+//     power-of-two scales a flipped rounding moves the score by percents.  Each
+//     lane keeps its two best, the four lanes of a
 //     tile merge, and the re-score runs in the same wavefront with one lane
 //     per tile, from the residual and weights kept in LDS.
 //
 // On the gate, up and down projections of a 3B layer (67.6 M weights, bf16,
 // per-element weights, S = 16): 3884 us with the general vector screen and
-// re-score, 402 us here (1.85 TB/s of the tensors; a copy of them takes 160).
+// re-score, 491 us here, 90 of them in the knife-edge scores (a copy of the
+// tensors takes 160).
 #include <math.h>
 
 #include "awsrc_internal.h"
 #include "basis_gen.h"
 #include "mfma_bf16.h"
 #include "rescore64.h"
+#include "screen_valu.h"
 
 namespace awsrc {
 
@@ -95,17 +100,103 @@ struct Top2 {
   }
 };
 
+// What is known of a seed besides its row tables.
+struct SeedInfo {
+  uint32_t mask[2];  // sign columns, 16 bits each (bit j set: B_s[j, p] < 0; 0 for p >= P)
+  uint32_t col;      // selected Hadamard columns, a byte each (0 for p >= P)
+  uint32_t pad_;
+  uint64_t inv;      // pi^-1: nibble i is the coordinate whose Hadamard row is i
+  uint64_t pad2_;
+};
+static_assert(sizeof(SeedInfo) == 32, "table entry");
+
+// Entry k of the length-16 transform of x, in the operation order of the
+// in-place butterflies (so the same value bit for bit).
+__device__ __forceinline__ float wht16_entry(const float (&x)[kC], uint32_t k) {
+  float v[kC];
+#pragma unroll
+  for (int i = 0; i < kC; ++i) v[i] = x[i];
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const uint32_t s = (k << (31 - b)) & 0x80000000u;
+#pragma unroll
+    for (int i = 0; i < (kC >> (b + 1)); ++i) v[i] = v[2 * i] + __uint_as_float(__float_as_uint(v[2 * i + 1]) ^ s);
+  }
+  return v[0];
+}
+
+// The score of one candidate in the general vector screen's arithmetic
+// (projections summed in coordinate order, Gram entries from the transform of
+// the tile's weights or, per column, the fp64 factor): for candidates on a
+// knife edge, see screen_valu.h.  r, d: the tile's LDS rows.
+template <bool POW2>
+__device__ __forceinline__ float general_score(const EncodeArgs& a, const SeedInfo& si, const float* r, const float* d,
+                                               float qmax, float inv_qmax, bool* edge) {
+  constexpr int PB = kPB;
+  const int P = a.P;
+  const uint32_t m[PB] = {si.mask[0] & 0xFFFFu, si.mask[0] >> 16, si.mask[1] & 0xFFFFu, si.mask[1] >> 16};
+  float bv[PB] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int j = 0; j < kC; ++j) {
+    const float u = d[j] * r[j];
+#pragma unroll
+    for (int p = 0; p < PB; ++p) bv[p] += ((m[p] >> j) & 1u) ? -u : u;
+  }
+#pragma unroll
+  for (int p = 0; p < PB; ++p) bv[p] = p < P ? bv[p] * 0.25f : 0.0f;
+  uint32_t c[PB];
+#pragma unroll
+  for (int p = 0; p < PB; ++p) c[p] = (si.col >> (8 * p)) & 15u;
+  if (a.d_mode == AWSRC_D_PER_ELEM) {
+    float x[kC], G[PB][PB];
+#pragma unroll
+    for (int i = 0; i < kC; ++i) x[i] = d[(uint32_t)(si.inv >> (4 * i)) & 15u];
+    const float sum = wht16_entry(x, 0);
+    const float eps = (float)a.lambda * sum * 0.0625f;
+#pragma unroll
+    for (int p = 0; p < PB; ++p) {
+#pragma unroll
+      for (int q = 0; q < p; ++q) G[p][q] = p < P ? wht16_entry(x, c[p] ^ c[q]) * 0.0625f : 0.0f;
+      G[p][p] = p < P ? sum * 0.0625f + eps : 1.0f;
+    }
+    return chol_score32<PB>(bv, G, eps, qmax, inv_qmax, POW2, edge);
+  }
+  double sum = 0.0, G[PB][PB];
+#pragma unroll
+  for (int p = 0; p < PB; ++p)
+#pragma unroll
+    for (int q = 0; q < p; ++q) G[p][q] = 0.0;
+#pragma unroll
+  for (int j = 0; j < kC; ++j) {
+    const double x = (double)d[j];
+    sum += x;
+#pragma unroll
+    for (int p = 0; p < PB; ++p)
+#pragma unroll
+      for (int q = 0; q < p; ++q) G[p][q] += flip(x, m[p] ^ m[q], j);
+  }
+  const double eps = a.lambda * (sum / kC);
+#pragma unroll
+  for (int p = 0; p < PB; ++p) {
+#pragma unroll
+    for (int q = 0; q < p; ++q) G[p][q] = p < P ? G[p][q] / kC : 0.0;
+    G[p][p] = p < P ? sum / kC + eps : 1.0;
+  }
+  float f[PB * (PB - 1) / 2 + 2 * PB];
+  col_factor64<PB>(G, f);
+  return screen_score_ldl<PB, POW2, 0>(bv, f, qmax, inv_qmax, edge);
+}
+
 }  // namespace
 
-// Tables of four seeds per block: the sign columns of each seed as four
-// 16-bit patterns (bit j set: B_s[j, p] < 0; 0 for p >= P), and the +-1 row
+// Tables of four seeds per block: each seed's SeedInfo, and the +-1 row
 // tables of the matrix products, row 4 q + k belonging to seed 4 R + q:
 //   table 0  column k;   table 1  column products (1,0) (2,0) (2,1) (3,0);
 //   table 2  column products (3,1) (3,2), all ones, zeros.
 // Rows of seeds >= S and of columns >= P are zero.  Lane l < 32 holds
 // coordinates 8 (l / 16) .. + 7 of row l % 16.
 __global__ __launch_bounds__(64) void k_c16_tables(uint64_t key, int P, int S, int gen_version,
-                                                   u32x4* __restrict__ frag, uint2* __restrict__ masks,
+                                                   u32x4* __restrict__ frag, SeedInfo* __restrict__ info,
                                                    unsigned long long* scored, unsigned long long n_scored) {
   __shared__ uint64_t s_key[4][kC];
   __shared__ uint8_t s_at[4][kC];    // Hadamard row of coordinate j
@@ -141,8 +232,14 @@ __global__ __launch_bounds__(64) void k_c16_tables(uint64_t key, int P, int S, i
     s_mask[q][j] = m;
   }
   __syncthreads();
-  if (j == 0 && s < S)
-    masks[s] = make_uint2(s_mask[q][0] | (s_mask[q][1] << 16), s_mask[q][2] | (s_mask[q][3] << 16));
+  if (j == 0 && s < S) {
+    SeedInfo si{};
+    si.mask[0] = s_mask[q][0] | (s_mask[q][1] << 16);
+    si.mask[1] = s_mask[q][2] | (s_mask[q][3] << 16);
+    for (int p = 0; p < kPB; ++p) si.col |= s_col[q][p] << (8 * p);
+    for (int i = 0; i < kC; ++i) si.inv |= (uint64_t)i << (4 * s_at[q][i]);
+    info[s] = si;
+  }
   for (int i = threadIdx.x; i < kBlocks * 32; i += 64) {
     const int tb = i >> 5, l = i & 31, m = l & 15;
     const int mq = m >> 2, k = m & 3;
@@ -170,7 +267,7 @@ __global__ __launch_bounds__(64) void k_c16_tables(uint64_t key, int P, int S, i
 template <bool POW2, bool FULLP>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_encode_c16(EncodeArgs a, ModEntry one, const ModEntry* __restrict__ mods,
                                                    int n_mods, const u32x4* __restrict__ frag,
-                                                   const uint2* __restrict__ masks) {
+                                                   const SeedInfo* __restrict__ info) {
   constexpr int LS = kPB * (kPB - 1) / 2;
   __shared__ __attribute__((aligned(16))) float rsh[kNT * kRow], dsh[kNT * kRow];
   __shared__ float tgs[2][kNT];
@@ -224,6 +321,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
         *reinterpret_cast<f32x4*>(dsh + row + 4 * h) = f32x4{dv[2 * i + h][0], dv[2 * i + h][1], dv[2 * i + h][2], dv[2 * i + h][3]};
       }
     }
+    wave_sync();
     // operands of the two groups of 16 tiles: [hi | mid] and [lo | 0]
     u32x4 U0[2], U1[2], D0[2], D1[2];
     split3(u, U0[0], U0[1], U1[0]);
@@ -265,27 +363,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
         const float gq[LS] = {ga[k][0], ga[k][1], ga[k][2], ga[k][3], gb[k][0], gb[k][1]};
         const float d0 = gb[k][2], diag = fmaf(lam, d0, d0);
         float f[LS + 2 * kPB];
-#pragma unroll
-        for (int p = 0; p < kPB; ++p) {
-          float E[kPB];
-#pragma unroll
-          for (int q = 0; q < p; ++q) {
-            float t = gq[ltri(p, q)];
-#pragma unroll
-            for (int kk = 0; kk < q; ++kk) t = fmaf(-E[kk], f[ltri(q, kk)], t);
-            E[q] = t;
-            f[ltri(p, q)] = t * f[LS + q];
-          }
-          float t = FULLP || p < P ? diag : 1.0f;
-#pragma unroll
-          for (int kk = 0; kk < p; ++kk) t = fmaf(-E[kk], f[ltri(p, kk)], t);
-          t = fmaxf(t, 1e-30f);
-          f[LS + kPB + p] = t;
-          f[LS + p] = __builtin_amdgcn_rcpf(t);
-        }
+        screen_factor<kPB, FULLP>(gq, diag, P, f);
         const float b[kPB] = {bq[k][0], bq[k][1], bq[k][2], bq[k][3]};
         bool edge;
-        const float gain = screen_score_ldl<kPB, POW2, 0>(b, f, qmax, inv_qmax, &edge);
+        float gain = screen_score_ldl<kPB, POW2, 0>(b, f, qmax, inv_qmax, &edge);
+        edge = edge && s < a.S;
+        if (__ballot(edge) != 0) {
+          if (edge) {
+            const int at = (32 * i + 16 * k + n) * kRow;
+            gain = general_score<POW2>(a, info[s], rsh + at, dsh + at, qmax, inv_qmax, &edge);
+          }
+        }
         top[k].add(s < a.S ? gain : -INFINITY, (uint32_t)s | (edge ? kEdge : 0u));
       }
     }
@@ -329,7 +417,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
   const double eps = a.lambda * (sumd / kC);
   const int iqmax = (1 << (a.b - 1)) - 1;
   auto score64 = [&](int s, int (&q)[kPB], double (&al)[kPB], uint16_t* bits) -> double {
-    const uint2 mw = masks[s];
+    const uint2 mw = *reinterpret_cast<const uint2*>(info[s].mask);
     const uint32_t m[kPB] = {mw.x & 0xFFFFu, mw.x >> 16, mw.y & 0xFFFFu, mw.y >> 16};
     double bv[kPB], gr[kPB * (kPB + 1) / 2];
 #pragma unroll
@@ -406,12 +494,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
 bool c16_supported(int C, int P) { return C == kC && P <= kPB; }
 int64_t c16_items(int64_t tiles) { return (tiles + kNT - 1) / kNT; }
 size_t c16_frag_bytes(int S) { return (size_t)((S + 3) / 4) * kBlocks * 32 * 16; }
-size_t c16_mask_bytes(int S) { return (size_t)S * 8; }
+size_t c16_info_bytes(int S) { return (size_t)S * sizeof(SeedInfo); }
 
 hipError_t launch_encode_c16(const EncodeArgs& a, uint64_t key, const ModEntry& one, const ModEntry* mods, int n_mods,
-                             int64_t items, unsigned long long candidates, void* frag, void* masks, hipStream_t st) {
+                             int64_t items, unsigned long long candidates, void* frag, void* info, hipStream_t st) {
   u32x4* fr = static_cast<u32x4*>(frag);
-  uint2* mk = static_cast<uint2*>(masks);
+  SeedInfo* mk = static_cast<SeedInfo*>(info);
   hipLaunchKernelGGL(k_c16_tables, dim3((unsigned)((a.S + 3) / 4)), dim3(64), 0, st, key, a.P, a.S, a.gen_version, fr, mk,
                      a.scored, candidates);
   const dim3 grid((unsigned)items), blk(64);

@@ -123,37 +123,6 @@ __device__ __forceinline__ void gather_pe(const float* wdl, const uint32_t (&cs)
     for (int q = 0; q < p; ++q) gq[ltri(p, q)] = *reinterpret_cast<const float*>(wb + (cs[p] ^ cs[q] ^ tl4));
 }
 
-// G + eps I = L diag(e) L^T of one candidate, in the layout of the
-// per-column factor table (strict lower L by rows, then 1/e, then e), from
-// its gathers gq and the diagonal d0 = mean_j d_j.  Padded columns (p >= P)
-// get L = 0, e = 1; FULLP: P == PB, so that no column is padding (the P = 8
-// workloads).
-template <int PB, bool FULLP>
-__device__ __forceinline__ void factor_pe(const float (&gq)[PB * (PB - 1) / 2], float d0, float eps, int P,
-                                          float (&f)[PB * (PB - 1) / 2 + 2 * PB]) {
-  constexpr int LS = PB * (PB - 1) / 2;
-  const float diag = d0 + eps;
-#pragma unroll
-  for (int p = 0; p < PB; ++p) {
-    const bool real = FULLP || p < P;
-    float E[PB];
-#pragma unroll
-    for (int q = 0; q < p; ++q) {
-      float t = real ? gq[ltri(p, q)] : 0.0f;
-#pragma unroll
-      for (int kk = 0; kk < q; ++kk) t = fmaf(-E[kk], f[ltri(q, kk)], t);
-      E[q] = t;
-      f[ltri(p, q)] = t * f[LS + q];
-    }
-    float t = real ? diag : 1.0f;
-#pragma unroll
-    for (int kk = 0; kk < p; ++kk) t = fmaf(-E[kk], f[ltri(p, kk)], t);
-    t = fmaxf(t, 1e-30f);
-    f[LS + PB + p] = t;
-    f[LS + p] = __builtin_amdgcn_rcpf(t);
-  }
-}
-
 template <int PB>
 __device__ __forceinline__ void unpack_cols(const u32x4& c0, const u32x4& c1, uint32_t (&cs)[PB]) {
 #pragma unroll
@@ -241,7 +210,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
   const float qmax = (float)((1 << (a.b - 1)) - 1);
   const float inv_qmax = 1.0f / qmax;
   const float d0 = wdl[tl];  // G_pp = mean_j d_j
-  const float eps = (float)a.lambda * d0;
+  const float diag = d0 + (float)a.lambda * d0;
 
   // this lane's top two (its seeds increase, so strict comparisons keep the
   // earlier seed first among equal scores) and the tile's pruning threshold
@@ -292,7 +261,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
       unpack_cols<PB>(colsh[2 * (size_t)es], colsh[2 * (size_t)es + 1], cs);
       float gr[NL], f[NF];
       gather_pe<PB>(wdl, cs, 4u * (uint32_t)et, gr);
-      factor_pe<PB, FULLP>(gr, ed0, lam * ed0, P, f);
+      screen_factor<PB, FULLP>(gr, ed0 + lam * ed0, P, f);
       bool edge;
       const float gsc = screen_gain_w<PB, POW2, 3>(wv, f, qmax, inv_qmax, &edge);
       qb[slot] = gsc;
@@ -367,7 +336,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
     C0n = colsh[2 * (size_t)(s + 2)];
     C1n = colsh[2 * (size_t)(s + 2) + 1];
     float f[NF];
-    factor_pe<PB, FULLP>(gq, d0, eps, P, f);
+    screen_factor<PB, FULLP>(gq, diag, P, f);
     float wv[PB];
     const float bnd = screen_fwd<PB>(bt, f, wv);
     const bool keep = (int)(bnd > thr) & (int)valid & (int)(s < a.S);

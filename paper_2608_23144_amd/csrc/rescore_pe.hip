@@ -1,5 +1,5 @@
-// fp64 re-score of the batched per-element encoder (C = 64, P <= 8,
-// generator version 1): the kept seeds of every tile of every module are
+// fp64 re-score of the batched per-element encoders (C = 64, P <= 8; either
+// generator version): the kept seeds of every tile of every module are
 // re-scored with the complete chain of Sec. 3.2 in fp64 (projection through
 // the Walsh-Hadamard transform of sigma .* d .* r, Gram entries through the
 // transform of the tile's own d, Cholesky solve of Eq. (3), quantization,
@@ -41,6 +41,76 @@ __device__ __forceinline__ void wave_sync() {
 __device__ __forceinline__ double tentry(const double* row, int k) {
   const double x = row[k & (kH - 1)], y = row[kH + (k & (kH - 1))];
   return (k & kH) ? x - y : x + y;
+}
+
+// The better of a tile's two results (ties: the lower seed), held by its two
+// lanes (h = 0: the best kept seed s0, h = 1: the second, s1, where `need`),
+// is written by the lane that holds it.
+template <int PB>
+__device__ __forceinline__ void write_better(const EncodeArgs& a, const ModEntry& md, int h, bool valid, bool need,
+                                             int s0, int s1, int s_me, int64_t row, int blk, int nb, double gk,
+                                             const int (&q)[PB], const double (&al)[PB], uint16_t bits) {
+  const int P = a.P;
+  const uint64_t gb = (uint64_t)__double_as_longlong(gk);
+  const auto xl = __builtin_amdgcn_permlane32_swap((uint32_t)gb, (uint32_t)gb, false, false);
+  const auto xh = __builtin_amdgcn_permlane32_swap((uint32_t)(gb >> 32), (uint32_t)(gb >> 32), false, false);
+  const double go = __longlong_as_double(
+      (long long)((uint64_t)(h ? xl[0] : xl[1]) | ((uint64_t)(h ? xh[0] : xh[1]) << 32)));
+  const bool second_wins = need && (h ? (gk > go || (gk == go && s1 < s0)) : (go > gk || (go == gk && s1 < s0)));
+  if (valid && (h == 1) == second_wins) {
+    const int64_t t = md.tile_off + row * nb + blk;
+    a.seed_out[t] = (uint16_t)s_me;
+    a.scale_out[t] = bits;
+    a.gain_out[t] = gk;
+    // the codes in one store when they fill an aligned word (P = 8 or 4)
+    int8_t* cp = a.code_out + t * P;
+    if (P == PB && (PB == 8 || PB == 4) && (reinterpret_cast<uintptr_t>(cp) & (PB - 1)) == 0) {
+      uint64_t w = 0;
+#pragma unroll
+      for (int p = 0; p < PB; ++p) w |= (uint64_t)(uint8_t)q[p] << (8 * p);
+      if (PB == 8) *reinterpret_cast<uint64_t*>(cp) = w;
+      else *reinterpret_cast<uint32_t*>(cp) = (uint32_t)w;
+    } else {
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+        if (p < P) cp[p] = (int8_t)q[p];
+    }
+    if (a.alpha_out) {
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+        if (p < P) a.alpha_out[t * P + p] = (float)al[p];
+    }
+  }
+}
+
+// Stages the 32 x 64 residual and weight blocks in LDS (rows of kRowD floats;
+// 16 lanes per row segment, 4 rows per pass: each instruction reads whole
+// cache lines); rows past the end repeat the last row.
+__device__ __forceinline__ void stage_rows(const EncodeArgs& a, const ModEntry& md, int64_t row0, int64_t c0, int lane,
+                                           float* rsh, float* dsh) {
+  const int pc = lane & 15;
+  constexpr int NP = kPeRows / 4;
+  int64_t o[NP];
+#pragma unroll
+  for (int pass = 0; pass < NP; ++pass) {
+    const int rl = 4 * pass + (lane >> 4);
+    const int64_t rg = row0 + rl < md.rows ? row0 + rl : md.rows - 1;
+    o[pass] = rg * md.cols + c0 + 4 * pc;
+  }
+  gf32x4 z[NP];
+#pragma unroll
+  for (int pass = 0; pass < NP; ++pass) z[pass] = gload4f(md.d + o[pass]);
+  float rv[NP][4];
+  load_residual4<NP>(md.W, a.w_dtype, md.W0, o, rv);
+#pragma unroll
+  for (int pass = 0; pass < NP; ++pass) {
+    const int at = (4 * pass + (lane >> 4)) * kRowD + 4 * pc;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      rsh[at + k] = rv[pass][k];
+      dsh[at + k] = z[pass][k];
+    }
+  }
 }
 
 }  // namespace
@@ -218,47 +288,134 @@ __global__ __launch_bounds__(64, 2) void k_finalize_pe_modules(EncodeArgs a, con
   uint16_t bits;
   const double gk = solve_score_ldl<PB>(a, bv, L, e, inv, eps, qmax, q, al, &bits);
 
-  // the better of the tile's two results (ties: the lower seed) is written
-  // by the lane that holds it
-  const uint64_t gb = (uint64_t)__double_as_longlong(gk);
-  const auto xl = __builtin_amdgcn_permlane32_swap((uint32_t)gb, (uint32_t)gb, false, false);
-  const auto xh = __builtin_amdgcn_permlane32_swap((uint32_t)(gb >> 32), (uint32_t)(gb >> 32), false, false);
-  const double go = __longlong_as_double(
-      (long long)((uint64_t)(h ? xl[0] : xl[1]) | ((uint64_t)(h ? xh[0] : xh[1]) << 32)));
-  const bool second_wins = need && (h ? (gk > go || (gk == go && s1 < s0)) : (go > gk || (go == gk && s1 < s0)));
-  if (valid && (h == 1) == second_wins) {
-    const int64_t t = md.tile_off + row * nb + blk;
-    a.seed_out[t] = (uint16_t)s_me;
-    a.scale_out[t] = bits;
-    a.gain_out[t] = gk;
-    // the codes in one store when they fill an aligned word (P = 8 or 4)
-    int8_t* cp = a.code_out + t * P;
-    if (P == PB && (PB == 8 || PB == 4) && (reinterpret_cast<uintptr_t>(cp) & (PB - 1)) == 0) {
-      uint64_t w = 0;
-#pragma unroll
-      for (int p = 0; p < PB; ++p) w |= (uint64_t)(uint8_t)q[p] << (8 * p);
-      if (PB == 8) *reinterpret_cast<uint64_t*>(cp) = w;
-      else *reinterpret_cast<uint32_t*>(cp) = (uint32_t)w;
-    } else {
-#pragma unroll
-      for (int p = 0; p < PB; ++p)
-        if (p < P) cp[p] = (int8_t)q[p];
-    }
-    if (a.alpha_out) {
-#pragma unroll
-      for (int p = 0; p < PB; ++p)
-        if (p < P) a.alpha_out[t * P + p] = (float)al[p];
-    }
-  }
+  write_better<PB>(a, md, h, valid, need, s0, s1, s_me, row, blk, nb, gk, q, al, bits);
 }
 
-hipError_t launch_finalize_pe_modules(const EncodeArgs& a, const ModEntry* mods, int n_mods, int64_t items,
-                                      hipStream_t st) {
+// The re-score after the version-2 screen: the coordinates of both transforms
+// are those of the kept seed's permutation, B_s[j, p] = sigma_j H[pi(j), c_p],
+// so each lane gathers coordinates pi^-1(32 h) .. pi^-1(32 h + 31) of r and d
+// from the staged rows, and the Gram transform belongs to the seed too.  The
+// gather rows take the staging blocks' place, so a second pass (a tile of the
+// wavefront needs its second seed, rare) stages them again.  Lists are in
+// tile order.  Attention projections of a 3B layer (147,456 tiles): 4 launches
+// of 47 us on the general re-score, one of 88 us here (same profiler).
+template <int PB>
+__global__ __launch_bounds__(64, 2) void k_finalize_perm_modules(EncodeArgs a, ModEntry one,
+                                                                 const ModEntry* __restrict__ mods, int n_mods) {
+  constexpr int NG = PB * (PB + 1) / 2;
+  __shared__ __attribute__((aligned(16))) float lds[kLdsFloats];
+  const int lane = threadIdx.x;
+  const int tl = lane & 31, h = lane >> 5;
+  const int64_t item = xcd_item(blockIdx.x, gridDim.x);
+  ModEntry md = one;
+  if (n_mods > 1) md = mods[find_module(mods, n_mods, item)];
+  const int nb = (int)(md.cols / kC);
+  const int64_t local = item - md.item_off;
+  const int blk = (int)(local % nb);
+  const int64_t row0 = (local / nb) * kPeRows;
+  const int64_t row = row0 + tl;
+  const bool valid = row < md.rows;
+  const int64_t at = (md.tile_off + (valid ? row : md.rows - 1) * nb + blk) * kTop;
+  const float2 tg = *reinterpret_cast<const float2*>(a.top_gain + at);
+  const uint2 ts = *reinterpret_cast<const uint2*>(a.top_seed + at);
+  const int s0r = list_seed(ts.x), s1r = list_seed(ts.y);
+  const int s0 = s0r < a.S ? s0r : 0, s1 = s1r < a.S ? s1r : 0;
+  const int P = a.P;
+  const double isq = 1.0 / sqrt((double)kC);
+  const int qmax = (1 << (a.b - 1)) - 1;
+  float* rsh = lds;
+  float* dsh = lds + kPeRows * kRowD;
+  double* grow = reinterpret_cast<double*>(lds) + tl * kRowD;
+  double bv[PB], g[NG], eps = 0.0;
+  int c[PB];
+  bool need = false, mine2 = false, two = false;
+#pragma unroll 1
+  for (int pass = 0; pass < 2; ++pass) {
+    if (pass == 1 && !two) break;
+    const int sp = pass ? s1 : s0;
+    const uint64_t sw = a.basis.sign[(size_t)sp * 2];
+    const uint4* ipp = reinterpret_cast<const uint4*>(a.basis.iperm + (size_t)sp * kMaxC + kH * h);
+    const uint4 i0 = ipp[0], i1 = ipp[1];
+    const uint32_t ip[8] = {i0.x, i0.y, i0.z, i0.w, i1.x, i1.y, i1.z, i1.w};
+    const uint8_t* cp = a.basis.col + (size_t)sp * kMaxP;
+    int cs[PB];
+#pragma unroll
+    for (int p = 0; p < PB; ++p) cs[p] = p < P ? cp[p] : 0;
+    wave_sync();
+    stage_rows(a, md, row0, (int64_t)blk * kC, lane, rsh, dsh);
+    wave_sync();
+    if (pass == 0) {
+      float eh = 0.0f;
+      double sh = 0.0;
+#pragma unroll
+      for (int j = 0; j < kH; ++j) {
+        const float r = rsh[tl * kRowD + kH * h + j], d = dsh[tl * kRowD + kH * h + j];
+        eh = fmaf(d * r, r, eh);
+        sh += (double)d;
+      }
+      const float e32 = eh + __shfl_xor(eh, 32, 64);
+      eps = a.lambda * ((sh + __shfl_xor(sh, 32, 64)) / kC);
+      const float thr = tg.x - rescore_window(tg.x, e32, ((ts.x | ts.y) & kEdge) != 0);
+      need = valid && tg.y >= thr && tg.y > -INFINITY;
+      two = __ballot(need) != 0;
+      mine2 = h == 1 && need;
+    }
+    double v[kH];
+    float dd[kH];
+#pragma unroll
+    for (int i = 0; i < kH; ++i) {
+      const int j = (int)((ip[i >> 2] >> (8 * (i & 3))) & (kC - 1));
+      dd[i] = dsh[tl * kRowD + j];
+      const double u = (double)dd[i] * (double)rsh[tl * kRowD + j];
+      v[i] = ((sw >> j) & 1ull) ? -u : u;
+    }
+    fwht<kH>(v);
+    wave_sync();
+#pragma unroll
+    for (int j = 0; j < kH; ++j) grow[kH * h + j] = v[j];
+    wave_sync();
+    const bool mine = mine2 == (pass == 1);
+    if (mine) {
+#pragma unroll
+      for (int p = 0; p < PB; ++p) {
+        c[p] = cs[p];
+        bv[p] = (p < P) ? tentry(grow, cs[p]) * isq : 0.0;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kH; ++j) v[j] = (double)dd[j];
+    fwht<kH>(v);
+    wave_sync();
+#pragma unroll
+    for (int j = 0; j < kH; ++j) grow[kH * h + j] = v[j];
+    wave_sync();
+    if (mine) {
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+#pragma unroll
+        for (int r = 0; r <= p; ++r) g[p * (p + 1) / 2 + r] = tentry(grow, c[p] ^ c[r]);
+    }
+  }
+  double L[PB * (PB - 1) / 2], e[PB], inv[PB];
+  ldl64<kC, PB>(P, g, eps, L, e, inv);
+  int q[PB];
+  double al[PB];
+  uint16_t bits;
+  const double gk = solve_score_ldl<PB>(a, bv, L, e, inv, eps, qmax, q, al, &bits);
+  write_better<PB>(a, md, h, valid, need, s0, s1, mine2 ? s1 : s0, row, blk, nb, gk, q, al, bits);
+}
+
+hipError_t launch_finalize_pe_modules(const EncodeArgs& a, const ModEntry& one, const ModEntry* mods, int n_mods,
+                                      int64_t items, hipStream_t st) {
   if (items == 0) return hipSuccess;
-  if (a.P <= 4)
-    hipLaunchKernelGGL((k_finalize_pe_modules<4>), dim3((unsigned)items), dim3(64), 0, st, a, mods, n_mods);
-  else
-    hipLaunchKernelGGL((k_finalize_pe_modules<8>), dim3((unsigned)items), dim3(64), 0, st, a, mods, n_mods);
+  const dim3 grid((unsigned)items), blk(64);
+  if (a.gen_version == 2) {
+    if (a.P <= 4) hipLaunchKernelGGL((k_finalize_perm_modules<4>), grid, blk, 0, st, a, one, mods, n_mods);
+    else hipLaunchKernelGGL((k_finalize_perm_modules<8>), grid, blk, 0, st, a, one, mods, n_mods);
+  } else {
+    if (a.P <= 4) hipLaunchKernelGGL((k_finalize_pe_modules<4>), grid, blk, 0, st, a, mods, n_mods);
+    else hipLaunchKernelGGL((k_finalize_pe_modules<8>), grid, blk, 0, st, a, mods, n_mods);
+  }
   return hipGetLastError();
 }
 

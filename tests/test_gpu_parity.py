@@ -229,6 +229,43 @@ def test_encode_c16(P, b, S, d_mode, gen, fmt, name):
         off += T
 
 
+@pytest.mark.parametrize("P,b,S,fmt,name", [(8, 4, 40, 0, "block3b"), (8, 4, 2, 1, "linear256"), (5, 3, 7, 0, "block3b"),
+                                            (1, 4, 9, 0, "linear256"), (4, 5, 64, 1, "block3b")])
+def test_encode_perm_modules(P, b, S, fmt, name):
+    """Per-element weights on generator version 2 at C = 64 (64-row work
+    groups, four seeds per step): padded columns, seed counts off a multiple of
+    four, row counts around the group sizes, an empty module, a workspace of
+    0xFF bytes; one call over all modules equals one per module."""
+    wl = workload(name, P=P, b=b, S=S, d_mode="elem")
+    mods = [Module("a", 65, 256, 0, 1, 1), Module("none", 0, 128, 0, 2, 2), Module("row", 1, 384, 0, 3, 3),
+            Module("c", 33, 128, 0, 4, 4)]
+    p = _params(wl, fmt, 2)
+    inps = [gen_module_inputs(wl, m, DEV) for m in mods]
+    W0s = [awsrc.awsrc_backbone_rtn(i["W"])[3] if m.rows else torch.empty(0, m.cols, device=DEV)
+           for m, i in zip(mods, inps)]
+    shapes = [(m.rows, m.cols) for m in mods]
+    dt = awsrc.AWSRC_DTYPE_F32 if wl.w_dtype == "f32" else awsrc.AWSRC_DTYPE_BF16
+    ws = torch.full((awsrc.encode_modules_workspace_bytes(p, shapes, dt, awsrc.AWSRC_D_PER_ELEM),), 0xFF,
+                    dtype=torch.uint8, device=DEV)
+    got = awsrc.awsrc_encode_modules(p, [i["W"] for i in inps], W0s, [i["d"] for i in inps], want_alpha=True,
+                                     workspace=ws)
+    assert 0 < awsrc.awsrc_encode_scored(got) <= got["seed"].numel() * S
+    off = 0
+    for m, inp, W0 in zip(mods, inps, W0s):
+        T = m.rows * m.cols // 64
+        if not T:
+            continue
+        ref = awsrc.awsrc_encode_tiles(p, inp["W"], W0, inp["d"], want_alpha=True)
+        for k in ("seed", "codes", "scale", "gain", "alpha"):
+            assert torch.equal(got[k][off:off + T], ref[k]), (m.name, k)
+        g32, w32 = awsrc.awsrc_encode_screen_lists(p, [(m.rows, m.cols)], awsrc.AWSRC_D_PER_ELEM, ref["workspace"])
+        assert g32.shape == (T, 1, 2) and bool(((w32 & 0xFFFF) < S).all())
+        kept = (w32[:, 0] & 0xFFFF) == (ref["seed"].to(torch.int32) & 0xFFFF)[:, None]
+        assert bool(kept.any(1).all())
+        assert _check_encode_sample(wl, m, inp, W0, ref, np.arange(T), fmt, 2) <= max(1, T // 50)
+        off += T
+
+
 def test_pipeline_generator_v2_matches_oracle():
     """Version-2 encode, rank and decode against the oracle's stream: the
     records the GPU ranks are the oracle's where seeds agree, the stream's
