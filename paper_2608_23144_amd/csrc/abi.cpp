@@ -78,6 +78,72 @@ uint64_t get_le(const uint8_t* p, int n) {
 
 constexpr int kHeaderFixed = 40;
 
+// A small piece of pinned host memory that kernels write results of a call to,
+// so that the host reads them after one stream synchronization (a copy into
+// pageable memory costs 11 us more).  64 slots of 1 KiB in one block, allocated
+// on first use and kept until the process ends; a slot is taken for the length
+// of a call and given back, and a call that finds none free (more than 64 in
+// flight, or no pinned memory) reads through a copy instead.
+class HostSlot {
+ public:
+  static constexpr size_t kBytes = 1024;
+  HostSlot() {
+    std::lock_guard<std::mutex> lock(mu());
+    Block& b = block();
+    if (!b.tried) {
+      b.tried = true;
+      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // another thread may be capturing
+      const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+      void* h = nullptr;
+      if (hipHostMalloc(&h, 64 * kBytes, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) {
+        b.host = static_cast<char*>(h);
+      } else {
+        (void)hipGetLastError();
+      }
+      if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    if (b.host && ~b.used) {
+      at_ = __builtin_ctzll(~b.used);
+      b.used |= 1ull << at_;
+      host_ = b.host + (size_t)at_ * kBytes;
+      void* d = nullptr;
+      if (hipHostGetDevicePointer(&d, host_, 0) == hipSuccess) dev_ = d;
+      else (void)hipGetLastError();
+    }
+  }
+  ~HostSlot() {
+    if (at_ < 0) return;
+    std::lock_guard<std::mutex> lock(mu());
+    block().used &= ~(1ull << at_);
+  }
+  HostSlot(const HostSlot&) = delete;
+  HostSlot& operator=(const HostSlot&) = delete;
+  // where a kernel writes the results: the slot, or `device` when there is none
+  uint64_t* device_or(uint64_t* device) const { return dev_ ? static_cast<uint64_t*>(dev_) : device; }
+  // waits for the stream and fetches n bytes of results
+  hipError_t read(void* dst, size_t n, const void* device, hipStream_t s) const {
+    if (!dev_) {
+      const hipError_t e = hipMemcpyAsync(dst, device, n, hipMemcpyDeviceToHost, s);
+      if (e != hipSuccess) return e;
+    }
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e == hipSuccess && dev_) memcpy(dst, host_, n);
+    return e;
+  }
+
+ private:
+  struct Block {
+    char* host = nullptr;
+    uint64_t used = 0;
+    bool tried = false;
+  };
+  static std::mutex& mu() { static std::mutex m; return m; }
+  static Block& block() { static Block b; return b; }
+  int at_ = -1;
+  char* host_ = nullptr;
+  void* dev_ = nullptr;
+};
+
 }  // namespace
 
 extern "C" int32_t awsrc_abi_version(void) { return AWSRC_ABI_VERSION; }
@@ -638,24 +704,15 @@ extern "C" awsrc_status awsrc_rank_prefix(const awsrc_params* p, int32_t n_modul
     if ((size_t)seg_n[i] > max_n) max_n = (size_t)seg_n[i];
     if ((size_t)k > max_k) max_k = (size_t)k;
   }
-  const size_t need = 256 + 256 + rank_ws_bytes(max_n, max_k);
+  const size_t need = 256 + 256 + rank_ws_bytes(max_n, max_k, seg_n.size());
   if (!workspace) { *ws_bytes = need; return AWSRC_OK; }
   if (*ws_bytes < need) return fail(AWSRC_ENOSPC, "workspace %zu < %zu bytes", *ws_bytes, need);
   if (!seed || !code || !scale || !gain || !stream_out || !stream_len || !K_out) return fail(AWSRC_EINVAL, "NULL buffer");
   if (stream_cap < (uint64_t)h) return fail(AWSRC_ENOSPC, "stream capacity below the header size");
 
   char* ws = reinterpret_cast<char*>(align_up(reinterpret_cast<uintptr_t>(workspace), 256));
-  const RankWs rw = carve_rank(ws + 256, max_n, max_k);
+  const RankWs rw = carve_rank(ws + 256, max_n, max_k, seg_n.size());
   hipStream_t s = (hipStream_t)stream;
-
-  // every segment runs on the device back to back (K is found there); one
-  // read of the totals at the end
-  HIPCHK(launch_rank_init(rw, s));
-  for (size_t i = 0; i < seg_n.size(); ++i) {
-    const int64_t cap = seg_cap[i] < seg_n[i] ? seg_cap[i] : seg_n[i];
-    HIPCHK(launch_rank_segment(gain, seg_t0[i], seg_n[i], cap, rw, seed, code, scale, p->P, p->b, ib, sb, scb, (int)L,
-                               (uint64_t)h, stream_cap, stream_out, s));
-  }
   // header: fixed fields, then the module table
   std::vector<uint8_t> hdr;
   hdr.reserve(h);
@@ -678,12 +735,36 @@ extern "C" awsrc_status awsrc_rank_prefix(const awsrc_params* p, int32_t n_modul
     put_le(hdr, (uint64_t)module_rows[m], 4);
     put_le(hdr, (uint64_t)module_cols[m], 4);
   }
-  // host buffers of this call (the header and the totals) stay alive until
-  // the stream synchronization below
-  uint64_t tot[3] = {0, 0, 0};
-  HIPCHK(hipMemcpyAsync(stream_out, hdr.data(), hdr.size(), hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(tot, rank_totals(rw), 3 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
+  // every segment runs on the device back to back (K is found there); one
+  // read of the totals at the end
+  const PackArgs pa{seed, code, scale, p->P, p->b, ib, sb, scb, (int)L, (uint64_t)h, stream_cap, stream_out};
+  uint64_t tot[kRankTotals] = {};
+  HostSlot slot;
+  if (rank_small((int64_t)max_n, seg_n.size())) {
+    SmallTable tb;
+    for (size_t i = 0; i < seg_n.size(); ++i) {
+      tb.t0[i] = (uint32_t)seg_t0[i];
+      tb.t0[i + 1] = (uint32_t)(seg_t0[i] + seg_n[i]);
+      tb.cap[i] = (uint16_t)(seg_cap[i] < seg_n[i] ? seg_cap[i] : seg_n[i]);
+    }
+    HeaderChunk hc;
+    const bool whole = hdr.size() <= sizeof hc;  // a global ranking of many modules has a longer header
+    if (whole) memcpy(hc.b, hdr.data(), hdr.size());
+    else HIPCHK(launch_rank_init(nullptr, hdr.data(), hdr.size(), stream_out, s));
+    HIPCHK(launch_rank_small(gain, tb, (int)seg_n.size(), (int64_t)max_n, rw, hc, whole ? (int)hdr.size() : 0, pa,
+                             slot.device_or(rw.state), s));
+    HIPCHK(slot.read(tot, sizeof tot, rw.state, s));
+  } else {
+    for (bool exact : {false, true}) {
+      HIPCHK(launch_rank_init(&rw, hdr.data(), hdr.size(), stream_out, s));
+      for (size_t i = 0; i < seg_n.size(); ++i)
+        HIPCHK(launch_rank_segment(gain, seg_t0[i], seg_n[i], seg_cap[i] < seg_n[i] ? seg_cap[i] : seg_n[i], rw, pa,
+                                   exact, s));
+      HIPCHK(launch_rank_totals(rw, slot.device_or(rw.blk_a), s));
+      HIPCHK(slot.read(tot, sizeof tot, rw.blk_a, s));
+      if (!tot[3]) break;  // else more equal gains than the fast path takes
+    }
+  }
   const int64_t K_total = (int64_t)tot[0];
   if (tot[2]) return fail(AWSRC_ENOSPC, "stream capacity %llu < %lld bytes", (unsigned long long)stream_cap, (long long)(h + K_total * L));
   *stream_len = (uint64_t)(h + K_total * L);

@@ -431,26 +431,55 @@ struct RankWs {
   uint64_t* blk_a;       // [max_blocks + 1] per-block counts / offsets
   uint64_t* blk_b;       // [max_blocks + 1]
   uint64_t* state;       // [kStateWords] select state, counters, totals, histogram
-  uint32_t* rs_hist;     // [256][rs_nblk] radix-sort digit counts per block (large record caps)
-  uint32_t* rs_tot;      // [256] digit totals
+  uint32_t* rs_hist;     // [512][blocks] radix-sort digit counts per block (large record caps)
+  uint32_t* rs_tot;      // [512] digit totals
+  uint64_t* kseg;        // [segments][2] records and eligible tiles (small segments)
   size_t rs_nblk;
   size_t cap;
   size_t max_blocks;
 };
-size_t rank_ws_bytes(size_t n_tiles, size_t k_cap);
-RankWs carve_rank(void* base, size_t n_tiles, size_t k_cap);
+size_t rank_ws_bytes(size_t n_tiles, size_t k_cap, size_t n_seg);
+RankWs carve_rank(void* base, size_t n_tiles, size_t k_cap, size_t n_seg);
+
+// Encoder outputs, record format and destination of a ranking.
+struct PackArgs {
+  const uint16_t* seed;
+  const int8_t* code;
+  const uint16_t* scale;
+  int P, b, idx_bits, seed_bits, scale_bits, L;
+  uint64_t h, cap;
+  uint8_t* out;
+};
 
 constexpr int kStateWords = 32 + 3 * 4096;  // rank state: scalars, pick states, three select histograms
-hipError_t launch_rank_init(const RankWs& ws, hipStream_t st);
+constexpr int64_t kSmallMax = 8192;         // tiles of a small segment
+constexpr int kSmallSegs = 256;             // segments of a call on the small path
+constexpr int kRankTotals = 4;              // records, eligible tiles, no-space flag, run-again flag
+
+// Header bytes passed by value: one chunk holds the header of kSmallSegs modules.
+struct HeaderChunk {
+  uint8_t b[40 + 8 * kSmallSegs];
+};
+// First tiles (one past the last segment's end too) and record caps of small segments.
+struct SmallTable {
+  uint32_t t0[kSmallSegs + 1];
+  uint16_t cap[kSmallSegs];
+};
+
+// Clears the state (ws not null) and writes the n_hdr header bytes.
+hipError_t launch_rank_init(const RankWs* ws, const uint8_t* hdr, size_t n_hdr, uint8_t* stream_out, hipStream_t st);
 // Top-K of one tile segment (K = min(cap, eligible), found on the device),
 // ordered by (gain desc, tile asc), packed at the segment's first free record
 // slot of the stream; no host synchronization.
 hipError_t launch_rank_segment(const double* gain, int64_t t0, int64_t n, int64_t cap, const RankWs& ws,
-                               const uint16_t* seed, const int8_t* code, const uint16_t* scale, int P, int b,
-                               int idx_bits, int seed_bits, int scale_bits, int L, uint64_t h,
-                               uint64_t stream_cap, uint8_t* stream_out, hipStream_t st);
-// Device words after all segments: [0] records, [1] eligible tiles, [2] no-space flag.
-const uint64_t* rank_totals(const RankWs& ws);
+                               const PackArgs& pa, bool exact, hipStream_t st);
+// Writes the kRankTotals totals of the segments so far to dst.
+hipError_t launch_rank_totals(const RankWs& ws, uint64_t* dst, hipStream_t st);
+// Every segment of a call at once, header and totals included, when none has
+// more than kSmallMax tiles.
+bool rank_small(int64_t max_n, size_t n_seg);
+hipError_t launch_rank_small(const double* gain, const SmallTable& tb, int n_seg, int64_t max_n, const RankWs& ws,
+                             const HeaderChunk& hc, int n_hdr, const PackArgs& pa, uint64_t* totals, hipStream_t st);
 
 // ---------------------------------------------------------------- decoding
 struct DecodeArgs {

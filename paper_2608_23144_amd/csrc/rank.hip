@@ -21,6 +21,12 @@
 // state over two, so no launch overwrites what another block of the same
 // launch still reads.  A segment is a chain of launches with no host round
 // trip and one read of the totals ends the call.
+//
+// That is the exact path, which takes any number of equal gains.  The fast
+// path, tried first, stops the select after two digits and sorts a few more
+// keys than it keeps; small segments are ranked whole by one workgroup each.
+#include <string.h>
+
 #include "awsrc_internal.h"
 
 namespace awsrc {
@@ -28,13 +34,14 @@ namespace awsrc {
 constexpr int kThreads = 256;
 constexpr int kRounds = 16;
 constexpr int kItems = kThreads * kRounds;  // items per block in the compaction
-constexpr int kChunk = 256;                 // items per LDS-sorted chunk
-constexpr int kChunkThreads = 128;
-constexpr int kLogChunk = 8;
+constexpr int kChunk = 4096;                // items per LDS-sorted chunk
+constexpr int kChunkThreads = 1024;
+constexpr int kLogChunk = 12;
 constexpr int kFan = 16;                    // runs per multiway merge
 constexpr int kLogFan = 4;
 constexpr int kSelBits = 12;                // radix-select digit width
 constexpr int kSelBins = 1 << kSelBits;
+constexpr int kCellBits = 27;               // leading bits that the fast path sorts by (three 9-bit digits)
 
 // Words of RankWs::state.
 enum : int {
@@ -42,6 +49,9 @@ enum : int {
   kSegK = 4, kSegOff = 5,                       // records of the segment, its first record slot
   kElig = 6, kArrive = 7,                       // per-launch accumulators, reset after use
   kTotK = 8, kTotElig = 9, kNoSpace = 10,       // totals over the segments of one call
+  kAgain = 11,                                  // the fast path could not finish: run the exact path
+  kCnt = 12,                                    // survivors of the segment (fast path)
+  kBase = 13, kShift = 14,                      // fast path: smallest ~key of the segment, cell width
   kSel = 16,                                    // [2][4] pick state of alternate passes
   kHist = 32                                    // [3][kSelBins] histograms of rotating passes
 };
@@ -79,8 +89,18 @@ __device__ __forceinline__ uint32_t block_scan_flag(bool f, uint32_t* sh_w, uint
   return before + in_wave;
 }
 
-__global__ void k_rank_init(uint64_t* state) {
-  for (int i = threadIdx.x; i < kStateWords; i += blockDim.x) state[i] = 0;
+// Clears the state and writes a piece of the stream header (passed by value,
+// so the call needs no host copy).
+__global__ void k_rank_init(uint64_t* state, HeaderChunk hc, int n, uint8_t* __restrict__ out) {
+  if (state)
+    for (int i = threadIdx.x; i < kStateWords; i += blockDim.x) state[i] = 0;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) out[i] = hc.b[i];
+}
+
+// The totals of a call (records, eligible tiles, no-space and run-again
+// flags) for the host.
+__global__ void k_rank_totals(const uint64_t* state, uint64_t* dst) {
+  if (threadIdx.x < kRankTotals) dst[threadIdx.x] = state[kTotK + threadIdx.x];
 }
 
 // ---------------------------------------------------------------- radix select
@@ -197,9 +217,26 @@ __device__ SelState pick_bin(const uint64_t* hist, SelState in, int shift, int w
 // under the new prefix.  Pass 1 forms K = min(cap, eligible) itself.
 __global__ __launch_bounds__(kThreads) void k_select_pass(const double* __restrict__ gain, int64_t n,
                                                           uint64_t* state, int64_t cap, int pass, int prev_shift,
-                                                          int prev_width, int shift, int width) {
+                                                          int prev_width, int shift, int width, int fast) {
   __shared__ uint32_t h[kSelBins];
   SelState cur;
+  if (fast && blockIdx.x == 0) {
+    // the fast path's segment bookkeeping (no other block reads these words)
+    __shared__ int top;
+    if (threadIdx.x == 0) top = 0;
+    __syncthreads();
+    for (int b = threadIdx.x; b < kSelBins; b += kThreads)
+      if (state[kHist + b]) atomicMax(&top, b);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const uint64_t ne = state[kElig];
+      state[kSegOff] = state[kTotK];
+      state[kTotK] += ne < (uint64_t)cap ? ne : (uint64_t)cap;
+      state[kTotElig] += ne;
+      state[kCnt] = 0;
+      state[kBase] = ~(((uint64_t)top << (64 - kSelBits)) | ((1ull << (64 - kSelBits)) - 1ull));
+    }
+  }
   if (pass == 1) {
     const uint64_t ne = state[kElig];
     const uint64_t K = ne < (uint64_t)cap ? ne : (uint64_t)cap;
@@ -217,6 +254,14 @@ __global__ __launch_bounds__(kThreads) void k_select_pass(const double* __restri
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     uint64_t* so = state + kSel + 4 * (pass & 1);
     so[0] = nw.prefix; so[1] = nw.mask; so[2] = nw.rem; so[3] = nw.done;
+    if (fast) {
+      // cells of the fast path's sort: the 2^kCellBits top values of ~key - base
+      // over the bins from the topmost one down to the K-th key's
+      const uint64_t bins = ((~state[kBase]) >> (64 - kSelBits)) - (nw.prefix >> (64 - kSelBits)) + 1;
+      int lg = 0;
+      while ((1ull << lg) < bins) ++lg;
+      state[kShift] = (uint64_t)(64 - kSelBits + lg - kCellBits);
+    }
   }
   if (nw.done) return;  // uniform
   for (int b = threadIdx.x; b < kSelBins; b += kThreads) h[b] = 0;
@@ -331,6 +376,7 @@ __global__ __launch_bounds__(1024) void k_compact_scan(uint64_t* blk_gt, uint64_
                                                        uint64_t* state) {
   // every histogram has been read: leave them cleared for the next segment
   for (int b = threadIdx.x; b < 3 * kSelBins; b += 1024) state[kHist + b] = 0;
+  if (threadIdx.x == 0) state[kCnt] = state[kSegK];  // exactly K items to sort
   if (state[kSegK] == 0) return;
   __shared__ uint64_t s_wave[16];
   const uint64_t rem = state[kRem];
@@ -387,16 +433,89 @@ __global__ __launch_bounds__(kThreads) void k_compact_write(const double* __rest
   }
 }
 
-// ---------------------------------------------------------------- packing
-struct PackArgs {
-  const uint16_t* seed;
-  const int8_t* code;
-  const uint16_t* scale;
-  int P, b, idx_bits, seed_bits, scale_bits, L;
-  uint64_t h, cap;
-  uint8_t* out;
-};
+// ---------------------------------------------------------------- fast selection
+// Two digits (24 bits) of the select leave the K-th key's bin a few keys wide
+// (its keys agree in 12 mantissa bits), so the fast path stops there: it takes
+// every key of that bin and above, a few more than K, sorts them by the total
+// order (key, tile) and packs the first K.  That leaves out three select
+// passes over the gains, the counting pass of the stable compaction and its
+// scan (43 M gains: 5 x 60, 71 and 31 of 2,089 us; here one of 60).  The
+// order of the survivors is free (slots are reserved by block), since the
+// sort breaks ties by tile.  More survivors than the items hold (many equal
+// gains) sets kAgain and the call runs the exact path instead.
+template <int ROUNDS>
+__global__ __launch_bounds__(kThreads) void k_compact_fast(const double* __restrict__ gain,
+                                                           const uint16_t* __restrict__ seed,
+                                                           const uint16_t* __restrict__ scale, int64_t t0, int64_t n,
+                                                           uint64_t* state, uint64_t cap_items,
+                                                           SortItem* __restrict__ items_out) {
+  __shared__ uint32_t s_cnt[kThreads / 64];
+  __shared__ uint64_t s_base;
+  const uint64_t K = state[kSegK];
+  const uint64_t* sp = state + kSel + 4;  // the pick of pass 1
+  SelState fin = SelState{sp[0], sp[1], sp[2], sp[3]};
+  if (!fin.done) fin = pick_bin(state + kHist + kSelBins, fin, 64 - 2 * kSelBits, kSelBits);
+  if (blockIdx.x == 0) {  // the first histogram has been read: clear it and the count for the next segment
+    for (int b = threadIdx.x; b < kSelBins; b += kThreads) state[kHist + b] = 0;
+    if (threadIdx.x == 0) state[kElig] = 0;
+  }
+  if (K == 0) return;  // uniform
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const uint64_t lt = lanemask_lt();
+  constexpr int kBlock = kThreads * ROUNDS;
+  for (int64_t base = (int64_t)blockIdx.x * kBlock; base < n; base += (int64_t)gridDim.x * kBlock) {
+    double gv[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const int64_t i = base + r * kThreads + threadIdx.x;
+      gv[r] = i < n ? gain[i] : 0.0;
+    }
+    uint32_t cnt = 0;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const uint64_t k = gain_key(gv[r]);
+      cnt += __popcll(__ballot(k != 0 && (k & fin.mask) >= fin.prefix));
+    }
+    if (lane == 0) s_cnt[wv] = cnt;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t tot = 0;
+      for (int w = 0; w < kThreads / 64; ++w) tot += s_cnt[w];
+      s_base = tot ? atomicAdd((unsigned long long*)&state[kCnt], (unsigned long long)tot) : 0;
+    }
+    __syncthreads();
+    uint64_t at = s_base;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) at += w < wv ? s_cnt[w] : 0u;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const int64_t i = base + r * kThreads + threadIdx.x;
+      const uint64_t k = gain_key(gv[r]);
+      const bool take = k != 0 && (k & fin.mask) >= fin.prefix;
+      const uint64_t bal = __ballot(take);
+      const uint64_t slot = at + (uint64_t)__popcll(bal & lt);
+      if (take && slot < cap_items) {
+        SortItem it;
+        it.key = ~k;  // ascending ~key = descending gain
+        it.tile = (uint32_t)(t0 + i);
+        it.aux = (uint32_t)seed[t0 + i] | ((uint32_t)scale[t0 + i] << 16);
+        items_out[slot] = it;
+      } else if (take) {
+        state[kAgain] = 1;
+      }
+      at += (uint64_t)__popcll(bal);
+    }
+    __syncthreads();  // s_cnt and s_base are reused
+  }
+}
 
+// Items to sort in the current segment.
+__device__ __forceinline__ int64_t sort_count(const uint64_t* state, int64_t cap_items) {
+  const int64_t c = (int64_t)state[kCnt];
+  return c < cap_items ? c : cap_items;
+}
+
+// ---------------------------------------------------------------- packing
 __device__ __forceinline__ void put_bits(uint64_t (&w)[3], int& pos, uint64_t v, int nbits) {
   if (nbits <= 0) return;
   const int o = pos & 63, k = pos >> 6;
@@ -405,18 +524,10 @@ __device__ __forceinline__ void put_bits(uint64_t (&w)[3], int& pos, uint64_t v,
   pos += nbits;
 }
 
-// Record i of the segment (tile t) goes to byte h + (first slot + i) * L of
-// the stream; a stream buffer too small for the running total raises the
-// no-space flag instead.
-// Record i of the stream from tile t; aux = the tile's seed | scale << 16.
+// Record of tile t (aux = its seed | scale << 16) into a slot of the stream.
 // A record at a 4-byte aligned place whose size is a multiple of 4 goes out
 // as whole words.
-__device__ void pack_record(const PackArgs& pa, uint64_t* state, int64_t i, uint32_t t, uint32_t aux) {
-  const uint64_t K = state[kSegK], off = state[kSegOff];
-  if (pa.h + (off + K) * (uint64_t)pa.L > pa.cap) {
-    if (i == 0) state[kNoSpace] = 1;
-    return;
-  }
+__device__ __forceinline__ void write_record(const PackArgs& pa, uint64_t slot, uint32_t t, uint32_t aux) {
   uint64_t w[3] = {0, 0, 0};
   int pos = 0;
   put_bits(w, pos, (uint64_t)t, pa.idx_bits);
@@ -424,13 +535,26 @@ __device__ void pack_record(const PackArgs& pa, uint64_t* state, int64_t i, uint
   const uint64_t cm = (1ull << pa.b) - 1ull;
   for (int p = 0; p < pa.P; ++p) put_bits(w, pos, (uint64_t)(int64_t)pa.code[(int64_t)t * pa.P + p] & cm, pa.b);
   put_bits(w, pos, (uint64_t)(aux >> 16) & ((1ull << pa.scale_bits) - 1ull), pa.scale_bits);
-  uint8_t* o = pa.out + pa.h + (off + (uint64_t)i) * (uint64_t)pa.L;
+  uint8_t* o = pa.out + pa.h + slot * (uint64_t)pa.L;
   if (((reinterpret_cast<uintptr_t>(o) | (uintptr_t)pa.L) & 3) == 0) {
     uint32_t* o32 = reinterpret_cast<uint32_t*>(o);
     for (int k = 0; k < pa.L / 4; ++k) o32[k] = (uint32_t)(w[k >> 1] >> (32 * (k & 1)));
   } else {
     for (int k = 0; k < pa.L; ++k) o[k] = (uint8_t)(w[k >> 3] >> (8 * (k & 7)));
   }
+}
+
+// Record i of the segment (tile t) goes to byte h + (first slot + i) * L of
+// the stream; a stream buffer too small for the running total raises the
+// no-space flag instead.
+__device__ void pack_record(const PackArgs& pa, uint64_t* state, int64_t i, uint32_t t, uint32_t aux) {
+  const uint64_t K = state[kSegK], off = state[kSegOff];
+  if ((uint64_t)i >= K) return;  // the fast path sorts a few more items than it keeps
+  if (pa.h + (off + K) * (uint64_t)pa.L > pa.cap) {
+    if (i == 0) state[kNoSpace] = 1;
+    return;
+  }
+  write_record(pa, off + (uint64_t)i, t, aux);
 }
 
 // the same, with the seed and scale read from the encoder outputs
@@ -452,38 +576,20 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// In-place bitonic sort of each chunk of kChunk items in LDS; the tail chunk
-// is padded with sentinels that sort last and are not written back.  Pair q of
-// a stage with distance j compares elements i = (q with a zero inserted at bit
-// log2 j) and i + j; thread t takes pairs t + r kChunkThreads (one pair per
-// thread with kChunk = 2 kChunkThreads), so for j <= 64 every wavefront works
-// inside its own 128-element windows and a wavefront-level barrier suffices
-// between stages.
-// With `pack` set (the final pass) the sorted items are packed as records.
-__global__ __launch_bounds__(kChunkThreads) void k_sort_chunks(SortItem* __restrict__ items, uint64_t* state,
-                                                               int pack, PackArgs pa) {
-  __shared__ uint64_t sk[kChunk];
-  __shared__ uint32_t st[kChunk];
-  const int64_t n = (int64_t)state[kSegK];
-  const int64_t base = (int64_t)blockIdx.x * kChunk;
-  if (base >= n) return;  // uniform per block
-#pragma unroll
-  for (int r = 0; r < kChunk / kChunkThreads; ++r) {
-    const int j = r * kChunkThreads + threadIdx.x;
-    const int64_t i = base + j;
-    uint64_t key = ~0ull;
-    uint32_t tile = 0xFFFFFFFFu;
-    if (i < n) { key = items[i].key; tile = items[i].tile; }
-    sk[j] = key;
-    st[j] = tile;
-  }
-  int prev = kChunk;
-  for (int k = 2; k <= kChunk; k <<= 1) {
+// Bitonic sort of M (key, tile) pairs in LDS by THREADS threads.  Pair q of a
+// stage with distance j compares elements i = (q with a zero inserted at bit
+// log2 j) and i + j; thread t takes pairs t + r THREADS, so for j <= 64 every
+// wavefront works inside its own 128-element windows and a wavefront-level
+// barrier suffices between stages.
+template <int M, int THREADS>
+__device__ __forceinline__ void bitonic_lds(uint64_t* sk, uint32_t* st) {
+  int prev = M;
+  for (int k = 2; k <= M; k <<= 1) {
     for (int j = k >> 1; j > 0; j >>= 1) {
       if (j > 64 || prev > 64) __syncthreads(); else wave_sync();
 #pragma unroll
-      for (int r = 0; r < kChunk / (2 * kChunkThreads); ++r) {
-        const int q = r * kChunkThreads + threadIdx.x;
+      for (int r = 0; r < M / (2 * THREADS); ++r) {
+        const int q = r * THREADS + threadIdx.x;
         const int i = ((q & ~(j - 1)) << 1) | (q & (j - 1));
         const uint64_t ka = sk[i], kb = sk[i + j];
         const uint32_t ta = st[i], tb = st[i + j];
@@ -498,6 +604,33 @@ __global__ __launch_bounds__(kChunkThreads) void k_sort_chunks(SortItem* __restr
     }
   }
   __syncthreads();
+}
+
+// In-place sort of each chunk of kChunk items; the tail chunk is padded with
+// sentinels that sort last and are not written back.  With `pack` set (the
+// final pass) the sorted items are packed as records.  clear_hist: the fast
+// path's second histogram has been read by now and is cleared here.
+__global__ __launch_bounds__(kChunkThreads) void k_sort_chunks(SortItem* __restrict__ items, uint64_t* state,
+                                                               int64_t cap_items, int clear_hist, int pack,
+                                                               PackArgs pa) {
+  __shared__ uint64_t sk[kChunk];
+  __shared__ uint32_t st[kChunk];
+  if (clear_hist && blockIdx.x == 0)
+    for (int b = threadIdx.x; b < kSelBins; b += kChunkThreads) state[kHist + kSelBins + b] = 0;
+  const int64_t n = sort_count(state, cap_items);
+  const int64_t base = (int64_t)blockIdx.x * kChunk;
+  if (base >= n) return;  // uniform per block
+#pragma unroll
+  for (int r = 0; r < kChunk / kChunkThreads; ++r) {
+    const int j = r * kChunkThreads + threadIdx.x;
+    const int64_t i = base + j;
+    uint64_t key = ~0ull;
+    uint32_t tile = 0xFFFFFFFFu;
+    if (i < n) { key = items[i].key; tile = items[i].tile; }
+    sk[j] = key;
+    st[j] = tile;
+  }
+  bitonic_lds<kChunk, kChunkThreads>(sk, st);
 #pragma unroll
   for (int r = 0; r < kChunk / kChunkThreads; ++r) {
     const int j = r * kChunkThreads + threadIdx.x;
@@ -516,6 +649,83 @@ __global__ __launch_bounds__(kChunkThreads) void k_sort_chunks(SortItem* __restr
   }
 }
 
+// ---------------------------------------------------------------- small segments
+// Segments of at most kSmallMax tiles: one workgroup sorts all of a segment's
+// keys in LDS and packs the first K, so a call over small modules is one
+// launch (two with several segments) instead of a dozen for each.  The path
+// above costs about 70 us of launches and their latencies whatever the size;
+// this one 10 to 25.
+struct SmallSeg {
+  int64_t t0, n, cap;
+};
+__device__ __forceinline__ SmallSeg small_seg(const SmallTable& tb, int i) {
+  return SmallSeg{tb.t0[i], tb.t0[i + 1] - tb.t0[i], tb.cap[i]};
+}
+
+// K and the eligible tiles of every segment.
+__global__ __launch_bounds__(256) void k_small_count(const double* __restrict__ gain, SmallTable tb, uint64_t* kseg) {
+  __shared__ uint32_t sw[4];
+  const SmallSeg sg = small_seg(tb, blockIdx.x);
+  uint32_t c = 0;
+  for (int64_t i = threadIdx.x; i < sg.n; i += 256) c += gain_key(gain[sg.t0 + i]) != 0;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off, 64);
+  if ((threadIdx.x & 63) == 0) sw[threadIdx.x >> 6] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint64_t e = (uint64_t)sw[0] + sw[1] + sw[2] + sw[3];
+    kseg[2 * blockIdx.x] = e < (uint64_t)sg.cap ? e : (uint64_t)sg.cap;
+    kseg[2 * blockIdx.x + 1] = e;
+  }
+}
+
+template <int M>
+__global__ __launch_bounds__(1024) void k_small_rank(const double* __restrict__ gain, SmallTable tb, int n_seg,
+                                                     const uint64_t* __restrict__ kseg, uint64_t* state, HeaderChunk hc,
+                                                     int n_hdr, PackArgs pa, uint64_t* __restrict__ totals) {
+  __shared__ uint64_t sk[M];
+  __shared__ uint32_t st[M];
+  __shared__ uint64_t s_sum[2];
+  __shared__ uint32_t s_el;
+  const SmallSeg sg = small_seg(tb, blockIdx.x);
+  const bool last = (int)blockIdx.x == n_seg - 1;
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < n_hdr; i += 1024) pa.out[i] = hc.b[i];
+  if (threadIdx.x < 2) s_sum[threadIdx.x] = 0;
+  if (threadIdx.x == 0) s_el = 0;
+  __syncthreads();
+  // records and eligible tiles of the earlier segments
+  for (int i = threadIdx.x; i < (int)blockIdx.x; i += 1024) {
+    atomicAdd((unsigned long long*)&s_sum[0], (unsigned long long)kseg[2 * i]);
+    atomicAdd((unsigned long long*)&s_sum[1], (unsigned long long)kseg[2 * i + 1]);
+  }
+  uint32_t c = 0;
+  for (int i = threadIdx.x; i < M; i += 1024) {
+    const uint64_t k = i < sg.n ? gain_key(gain[sg.t0 + i]) : 0ull;
+    c += k != 0;
+    sk[i] = ~k;  // ineligible tiles and padding sort last
+    st[i] = (uint32_t)i;
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off, 64);
+  if ((threadIdx.x & 63) == 0 && c) atomicAdd(&s_el, c);
+  bitonic_lds<M, (M / 2 < 1024 ? M / 2 : 1024)>(sk, st);
+  const uint64_t elig = s_el, off = s_sum[0];
+  const uint64_t K = elig < (uint64_t)sg.cap ? elig : (uint64_t)sg.cap;
+  const bool fits = pa.h + (off + K) * (uint64_t)pa.L <= pa.cap;
+  if (fits)
+    for (int i = threadIdx.x; i < (int)K; i += 1024) {
+      const uint32_t t = (uint32_t)sg.t0 + st[i];
+      write_record(pa, off + (uint64_t)i, t, (uint32_t)pa.seed[t] | ((uint32_t)pa.scale[t] << 16));
+    }
+  if (last && threadIdx.x == 0) {
+    totals[0] = off + K;
+    totals[1] = s_sum[1] + elig;
+    totals[2] = fits ? 0 : 1;  // the totals only grow, so the last segment knows
+    totals[3] = 0;
+  }
+}
+
 // One multiway merge pass: runs of 2^logw sorted items, groups of F runs.
 // An item's output slot is the first slot of its group, plus its index in its
 // own run, plus, for every other run of the group, the number of that run's
@@ -526,10 +736,11 @@ __global__ __launch_bounds__(kChunkThreads) void k_sort_chunks(SortItem* __restr
 // digits (F loads per level); the last pass over a few long runs uses base-8
 // digits, which cuts the number of round trips by three.
 template <int LOGR, int F>
-__global__ __launch_bounds__(256) void k_merge_runs(const SortItem* __restrict__ in, uint64_t* state, int logw,
-                                                    SortItem* __restrict__ out, int pack, PackArgs pa) {
+__global__ __launch_bounds__(256) void k_merge_runs(const SortItem* __restrict__ in, uint64_t* state,
+                                                    int64_t cap_items, int logw, SortItem* __restrict__ out, int pack,
+                                                    PackArgs pa) {
   constexpr int NP = (1 << LOGR) - 1;  // probes per run per level
-  const int64_t n = (int64_t)state[kSegK];
+  const int64_t n = sort_count(state, cap_items);
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
   const SortItem x = in[i];
@@ -573,29 +784,47 @@ __global__ __launch_bounds__(256) void k_merge_runs(const SortItem* __restrict__
 }
 
 // ---------------------------------------------------------------- radix sort of large survivor sets
-// Least-significant-digit radix sort on the 64-bit key, 8-bit digits, eight
-// stable passes (the items enter in tile order, so equal keys keep
-// increasing tiles, the same total order as the merge path).  A pass is a
-// block histogram (kRsItems items per block), a scan per digit over the
-// blocks, and a scatter in which every block first orders its items by digit
-// in LDS (index order within a digit: within a wavefront by matching digits
-// with ballots, across the block's four wavefronts and its rounds through LDS
-// counters) and then writes them in that order, so that each digit's run of
-// the block goes out as adjacent stores rather than one scattered 16-byte
-// store per lane.  The last pass packs the records instead of writing items.
-constexpr int kRsBits = 8;
-constexpr int kRsBins = 1 << kRsBits;
+// Least-significant-digit radix sort.  A pass is a block histogram (kRsItems
+// items per block), a scan per digit over the blocks, and a scatter in which
+// every block first orders its items by digit in LDS (index order within a
+// digit: within a wavefront by matching digits with ballots, across the
+// block's four wavefronts and its rounds through LDS counters) and then writes
+// them in that order, so that each digit's run of the block goes out as
+// adjacent stores rather than one scattered 16-byte store per lane.
+//
+// The exact path sorts the whole 64-bit key, eight stable passes of 8 bits
+// (the items enter in tile order, so equal keys keep increasing tiles, the
+// same total order as the merge path), and packs in the last one.  The fast
+// path (CELL) sorts by the 27 leading bits of the range the survivors span,
+// three passes of 9 bits; items that share those bits (a handful: 9.2 M
+// records of 43 M log-normal gains spread over more cells than there are
+// records) are put in order by k_pack_cells.  Each pass moves every item once,
+// 0.17 ms for 9.2 M, so the five passes left out are worth 0.85 ms.
 constexpr int kRsThreads = 256;
 constexpr int kRsRounds = 16;
 constexpr int kRsItems = kRsThreads * kRsRounds;
+constexpr int kRsMaxBins = 512;
 constexpr int64_t kRadixMin = int64_t(1) << 20;  // record caps above this use the radix sort
 
-__global__ __launch_bounds__(kRsThreads) void k_rs_hist(const SortItem* __restrict__ in, const uint64_t* state,
-                                                        int shift, uint32_t* __restrict__ hist, int nblk) {
-  __shared__ uint32_t h[kRsBins];
-  h[threadIdx.x] = 0;
+// An item's sort value: the whole key, or its cell.
+template <bool CELL>
+__device__ __forceinline__ uint64_t sort_value(const uint64_t key, uint64_t base, int shift0) {
+  return CELL ? (key - base) >> shift0 : key;
+}
+
+template <int BITS, bool CELL>
+__global__ __launch_bounds__(kRsThreads) void k_rs_hist(const SortItem* __restrict__ in, uint64_t* state,
+                                                        int64_t cap_items, int clear_hist, int shift,
+                                                        uint32_t* __restrict__ hist, int nblk) {
+  constexpr int BINS = 1 << BITS;
+  __shared__ uint32_t h[BINS];
+  for (int d = threadIdx.x; d < BINS; d += kRsThreads) h[d] = 0;
+  if (clear_hist && blockIdx.x == 0)  // the fast path's second histogram has been read by now
+    for (int b = threadIdx.x; b < kSelBins; b += kRsThreads) state[kHist + kSelBins + b] = 0;
   __syncthreads();
-  const int64_t n = (int64_t)state[kSegK];
+  const int64_t n = sort_count(state, cap_items);
+  const uint64_t kb = state[kBase];
+  const int s0 = (int)state[kShift];
   const int64_t base = (int64_t)blockIdx.x * kRsItems;
   uint64_t keys[kRsRounds];  // every load issued before the first count
 #pragma unroll
@@ -606,10 +835,10 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const SortItem* __restri
 #pragma unroll
   for (int r = 0; r < kRsRounds; ++r) {
     const int64_t i = base + r * kRsThreads + threadIdx.x;
-    if (i < n) atomicAdd(&h[(uint32_t)(keys[r] >> shift) & (kRsBins - 1)], 1u);
+    if (i < n) atomicAdd(&h[(uint32_t)(sort_value<CELL>(keys[r], kb, s0) >> shift) & (BINS - 1)], 1u);
   }
   __syncthreads();
-  hist[(int64_t)threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
+  for (int d = threadIdx.x; d < BINS; d += kRsThreads) hist[(int64_t)d * nblk + blockIdx.x] = h[d];
 }
 
 // One block per digit: exclusive scan of the digit's counts over the blocks
@@ -629,24 +858,35 @@ __global__ __launch_bounds__(1024) void k_rs_scan(uint32_t* __restrict__ hist, i
   if (threadIdx.x == 0) tot[blockIdx.x] = (uint32_t)carry;
 }
 
+template <int BITS, bool CELL>
 __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const SortItem* __restrict__ in, SortItem* __restrict__ out,
-                                                           uint64_t* state, int shift,
+                                                           uint64_t* state, int64_t cap_items, int shift,
                                                            const uint32_t* __restrict__ hist, int nblk,
                                                            const uint32_t* __restrict__ tot, int pack, PackArgs pa) {
-  __shared__ uint32_t dbase[kRsBins];         // first slot of each digit for this block
-  __shared__ uint32_t lstart[kRsBins];        // first place of each digit in the block's digit order
-  __shared__ uint32_t lcur[kRsBins];          // next place of each digit in that order
-  __shared__ uint32_t wc[kRsThreads / 64][kRsBins];  // items per digit of each wavefront in the round
-  __shared__ uint64_t s_wave[kRsThreads / 64];
+  constexpr int BINS = 1 << BITS;
+  constexpr int NB = BINS / kRsThreads;       // digits per thread: NB t .. NB t + NB - 1
+  __shared__ uint32_t dbase[BINS];            // first slot of each digit for this block
+  __shared__ uint32_t lstart[BINS];           // first place of each digit in the block's digit order
+  __shared__ uint32_t lcur[BINS];             // next place of each digit in that order
+  __shared__ uint32_t wc[kRsThreads / 64][BINS];  // items per digit of each wavefront in the round
+  __shared__ uint32_t s_wave[kRsThreads / 64];
   __shared__ SortItem s_items[kRsItems];      // the block's items in digit order (stable within a digit)
-  const int64_t n = (int64_t)state[kSegK];
+  const int64_t n = sort_count(state, cap_items);
   const int64_t base = (int64_t)blockIdx.x * kRsItems;
   if (base >= n) return;  // uniform per block
+  const uint64_t kb = state[kBase];
+  const int s0 = (int)state[kShift];
+  auto digit = [&](uint64_t key) -> uint32_t {
+    return (uint32_t)(sort_value<CELL>(key, kb, s0) >> shift) & (BINS - 1);
+  };
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  // exclusive scan of one value per digit (thread t holds digit t's) over the
-  // block's 256 threads
-  auto scan256 = [&](uint32_t v) -> uint32_t {
-    uint32_t x = v;
+  // exclusive scan of the digits' values (thread t holds digits NB t ..) over
+  // the block's threads, in place
+  auto scan_digits = [&](uint32_t (&v)[NB]) {
+    uint32_t own = 0;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) own += v[q];
+    uint32_t x = own;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const uint32_t y = __shfl_up(x, o, 64);
@@ -654,14 +894,27 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const SortItem* __res
     }
     if (lane == 63) s_wave[w] = x;
     __syncthreads();
-    uint32_t before = 0;
+    uint32_t run = x - own;
 #pragma unroll
-    for (int k = 0; k < kRsThreads / 64; ++k) before += k < w ? (uint32_t)s_wave[k] : 0u;
+    for (int k = 0; k < kRsThreads / 64; ++k) run += k < w ? s_wave[k] : 0u;
     __syncthreads();  // s_wave is reused by the next scan
-    return before + x - v;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const uint32_t c = v[q];
+      v[q] = run;
+      run += c;
+    }
   };
-  // digit bases: exclusive scan of the 256 totals, plus this block's prefix
-  dbase[t] = scan256(tot[t]) + hist[(int64_t)t * nblk + blockIdx.x];
+  // digit bases: exclusive scan of the digit totals, plus this block's prefix
+  uint32_t dv[NB];
+#pragma unroll
+  for (int q = 0; q < NB; ++q) dv[q] = tot[NB * t + q];
+  scan_digits(dv);
+#pragma unroll
+  for (int q = 0; q < NB; ++q) {
+    dbase[NB * t + q] = dv[q] + hist[(int64_t)(NB * t + q) * nblk + blockIdx.x];
+    lcur[NB * t + q] = 0;
+  }
   const uint64_t lt = lanemask_lt();
   // every round's item is loaded before the first round (one wait, not one
   // per round)
@@ -674,31 +927,37 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const SortItem* __res
   }
   // the block's count of each digit, then where each digit's run starts in
   // the block's digit order
-  lcur[t] = 0;
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < kRsRounds; ++r)
-    if (base + r * kRsThreads + t < n) atomicAdd(&lcur[(uint32_t)(xs[r].key >> shift) & (kRsBins - 1)], 1u);
+    if (base + r * kRsThreads + t < n) atomicAdd(&lcur[digit(xs[r].key)], 1u);
   __syncthreads();
-  const uint32_t ls = scan256(lcur[t]);
-  lstart[t] = ls;
-  lcur[t] = ls;
+#pragma unroll
+  for (int q = 0; q < NB; ++q) dv[q] = lcur[NB * t + q];
+  scan_digits(dv);
+#pragma unroll
+  for (int q = 0; q < NB; ++q) {
+    lstart[NB * t + q] = dv[q];
+    lcur[NB * t + q] = dv[q];
+  }
   // place every item in the block's digit order: within a wavefront by
   // matching digits with ballots, across the block's wavefronts and its
   // rounds through LDS counters (index order within a digit)
 #pragma unroll
   for (int r = 0; r < kRsRounds; ++r) {
 #pragma unroll
-    for (int k = 0; k < kRsThreads / 64; ++k) wc[k][t] = 0;
+    for (int k = 0; k < kRsThreads / 64; ++k)
+#pragma unroll
+      for (int q = 0; q < NB; ++q) wc[k][NB * t + q] = 0;
     __syncthreads();
     const int64_t i = base + r * kRsThreads + t;
     const bool valid = i < n;
     const SortItem x = xs[r];
-    const uint32_t d = (uint32_t)(x.key >> shift) & (kRsBins - 1);
+    const uint32_t d = digit(x.key);
     // lanes of this wavefront holding the same digit
     uint64_t same = __ballot(valid);
 #pragma unroll
-    for (int b = 0; b < kRsBits; ++b) {
+    for (int b = 0; b < BITS; ++b) {
       const uint64_t bal = __ballot((d >> b) & 1u);
       same &= ((d >> b) & 1u) ? bal : ~bal;
     }
@@ -712,10 +971,13 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const SortItem* __res
       s_items[lp] = x;
     }
     __syncthreads();
-    uint32_t add = 0;
 #pragma unroll
-    for (int k = 0; k < kRsThreads / 64; ++k) add += wc[k][t];
-    lcur[t] += add;
+    for (int q = 0; q < NB; ++q) {
+      uint32_t add = 0;
+#pragma unroll
+      for (int k = 0; k < kRsThreads / 64; ++k) add += wc[k][NB * t + q];
+      lcur[NB * t + q] += add;
+    }
   }
   __syncthreads();
   // write the block's items in digit order: consecutive threads take
@@ -726,7 +988,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const SortItem* __res
     const int j = r * kRsThreads + t;
     if (j < m) {
       const SortItem x = s_items[j];
-      const uint32_t d = (uint32_t)(x.key >> shift) & (kRsBins - 1);
+      const uint32_t d = digit(x.key);
       const uint32_t off = dbase[d] + ((uint32_t)j - lstart[d]);
       if (pack) pack_record(pa, state, (int64_t)off, x.tile, x.aux);
       else out[off] = x;
@@ -734,21 +996,62 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const SortItem* __res
   }
 }
 
+// Last step of the fast path's radix sort: the items are in cell order; each
+// finds its place among the items of its own cell (by key, then tile) and is
+// packed.  A cell of more than kCellMax items (gains that agree in more than
+// 20 mantissa bits, many times over) sets kAgain.
+constexpr int kCellMax = 64;
+__global__ __launch_bounds__(256) void k_pack_cells(const SortItem* __restrict__ in, uint64_t* state, int64_t cap_items,
+                                                    PackArgs pa) {
+  const int64_t n = sort_count(state, cap_items);
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const uint64_t kb = state[kBase];
+  const int s0 = (int)state[kShift];
+  const SortItem x = in[i];
+  const uint64_t cell = sort_value<true>(x.key, kb, s0);
+  int64_t pos = i;
+  int64_t j = i - 1;
+  for (; j >= 0 && i - j <= kCellMax; --j) {
+    const SortItem y = in[j];
+    if (sort_value<true>(y.key, kb, s0) != cell) break;
+    pos -= kv_less(x, y);
+  }
+  const int64_t back = i - 1 - j;
+  j = i + 1;
+  for (; j < n && j - i <= kCellMax; ++j) {
+    const SortItem y = in[j];
+    if (sort_value<true>(y.key, kb, s0) != cell) break;
+    pos += kv_less(y, x);
+  }
+  if (back + (j - i) > kCellMax) {
+    state[kAgain] = 1;
+    return;
+  }
+  pack_record(pa, state, pos, x.tile, x.aux);
+}
+
 // ---------------------------------------------------------------- workspace
-size_t rank_ws_bytes(size_t n_tiles, size_t k_cap) {
-  const size_t cap = k_cap ? k_cap : 1;
+// Items beyond the record cap that the fast path may sort: the keys that share
+// the K-th key's 24 leading bits (about n 2^-12 times the density of the gains'
+// logarithms there).
+static size_t cap_slack(size_t n_tiles) { return 4096 + n_tiles / 256; }
+
+size_t rank_ws_bytes(size_t n_tiles, size_t k_cap, size_t n_seg) {
+  const size_t cap = k_cap + cap_slack(n_tiles);
   const size_t max_blocks = (n_tiles + kItems - 1) / kItems + 1;
   const size_t rs_blocks = (cap + kRsItems - 1) / kRsItems;
   size_t b = 0;
   b += align_up(cap * sizeof(SortItem), 256) * 2;
   b += align_up((max_blocks + 1) * 8, 256) * 2;
   b += align_up((size_t)kStateWords * 8, 256);
-  b += align_up(rs_blocks * kRsBins * 4, 256) + align_up(kRsBins * 4, 256);
+  b += align_up(rs_blocks * kRsMaxBins * 4, 256) + align_up(kRsMaxBins * 4, 256);
+  b += align_up(n_seg * 16, 256);
   return b;
 }
 
-RankWs carve_rank(void* base, size_t n_tiles, size_t k_cap) {
-  const size_t cap = k_cap ? k_cap : 1;
+RankWs carve_rank(void* base, size_t n_tiles, size_t k_cap, size_t n_seg) {
+  const size_t cap = k_cap + cap_slack(n_tiles);
   const size_t max_blocks = (n_tiles + kItems - 1) / kItems + 1;
   char* p = static_cast<char*>(base);
   RankWs w;
@@ -758,25 +1061,77 @@ RankWs carve_rank(void* base, size_t n_tiles, size_t k_cap) {
   w.blk_b = reinterpret_cast<uint64_t*>(p); p += align_up((max_blocks + 1) * 8, 256);
   w.state = reinterpret_cast<uint64_t*>(p); p += align_up((size_t)kStateWords * 8, 256);
   w.rs_nblk = (cap + kRsItems - 1) / kRsItems;
-  w.rs_hist = reinterpret_cast<uint32_t*>(p); p += align_up(w.rs_nblk * kRsBins * 4, 256);
-  w.rs_tot = reinterpret_cast<uint32_t*>(p);
+  w.rs_hist = reinterpret_cast<uint32_t*>(p); p += align_up(w.rs_nblk * kRsMaxBins * 4, 256);
+  w.rs_tot = reinterpret_cast<uint32_t*>(p); p += align_up(kRsMaxBins * 4, 256);
+  w.kseg = reinterpret_cast<uint64_t*>(p);
   w.cap = cap;
   w.max_blocks = max_blocks;
+  (void)n_seg;
   return w;
 }
 
-hipError_t launch_rank_init(const RankWs& ws, hipStream_t st) {
-  hipLaunchKernelGGL(k_rank_init, dim3(1), dim3(256), 0, st, ws.state);
+hipError_t launch_rank_init(const RankWs* ws, const uint8_t* hdr, size_t n_hdr, uint8_t* stream_out, hipStream_t st) {
+  for (size_t o = 0; o == 0 || o < n_hdr; o += sizeof(HeaderChunk)) {
+    HeaderChunk hc;
+    const size_t k = n_hdr - o < sizeof hc ? n_hdr - o : sizeof hc;
+    memcpy(hc.b, hdr + o, k);
+    hipLaunchKernelGGL(k_rank_init, dim3(1), dim3(256), 0, st, ws && o == 0 ? ws->state : (uint64_t*)nullptr, hc, (int)k,
+                       stream_out + o);
+  }
   return hipGetLastError();
+}
+
+hipError_t launch_rank_totals(const RankWs& ws, uint64_t* dst, hipStream_t st) {
+  hipLaunchKernelGGL(k_rank_totals, dim3(1), dim3(64), 0, st, ws.state, dst);
+  return hipGetLastError();
+}
+
+bool rank_small(int64_t max_n, size_t n_seg) { return max_n <= kSmallMax && n_seg <= (size_t)kSmallSegs; }
+
+hipError_t launch_rank_small(const double* gain, const SmallTable& tb, int n_seg, int64_t max_n, const RankWs& ws,
+                             const HeaderChunk& hc, int n_hdr, const PackArgs& pa, uint64_t* totals, hipStream_t st) {
+  if (n_seg > 1) hipLaunchKernelGGL(k_small_count, dim3((unsigned)n_seg), dim3(256), 0, st, gain, tb, ws.kseg);
+  if (max_n <= 2048)
+    hipLaunchKernelGGL((k_small_rank<2048>), dim3((unsigned)n_seg), dim3(1024), 0, st, gain, tb, n_seg, ws.kseg,
+                       ws.state, hc, n_hdr, pa, totals);
+  else
+    hipLaunchKernelGGL((k_small_rank<kSmallMax>), dim3((unsigned)n_seg), dim3(1024), 0, st, gain, tb, n_seg, ws.kseg,
+                       ws.state, hc, n_hdr, pa, totals);
+  return hipGetLastError();
+}
+
+// Sort of the survivors in items_a (at most cap_items, the count in the state)
+// by chunks in LDS, then multiway merges; the final pass packs the records.
+static void sort_and_pack(const RankWs& ws, int64_t cap_items, int clear_hist, const PackArgs& pa, hipStream_t st) {
+  int passes = 0;
+  for (int logw = kLogChunk; ((int64_t)1 << logw) < cap_items;
+       logw += cap_items <= ((int64_t)4 << logw) ? 2 : kLogFan)
+    ++passes;
+  hipLaunchKernelGGL(k_sort_chunks, dim3((unsigned)((cap_items + kChunk - 1) / kChunk)), dim3(kChunkThreads), 0, st,
+                     ws.items_a, ws.state, cap_items, clear_hist, passes == 0 ? 1 : 0, pa);
+  SortItem* in = ws.items_a;
+  SortItem* out = ws.items_b;
+  int done = 0;
+  for (int logw = kLogChunk; ((int64_t)1 << logw) < cap_items;) {
+    const dim3 grid((unsigned)((cap_items + 255) / 256));
+    const int last = ++done == passes ? 1 : 0;
+    if (cap_items <= ((int64_t)4 << logw)) {  // at most four runs left: one base-8 pass
+      hipLaunchKernelGGL((k_merge_runs<3, 4>), grid, dim3(256), 0, st, in, ws.state, cap_items, logw, out, last, pa);
+      logw += 2;
+    } else {
+      hipLaunchKernelGGL((k_merge_runs<1, kFan>), grid, dim3(256), 0, st, in, ws.state, cap_items, logw, out, last, pa);
+      logw += kLogFan;
+    }
+    SortItem* t = in; in = out; out = t;
+  }
 }
 
 // One segment: count -> select -> compact -> sort -> pack, all on the device.
 // `cap` bounds K (the budget's record count, at most n); grids are sized by it
-// and kernels read the actual K from the state.
+// and kernels read the actual K from the state.  exact: the path that handles
+// any number of equal gains, else the fast one (see k_compact_fast).
 hipError_t launch_rank_segment(const double* gain, int64_t t0, int64_t n, int64_t cap, const RankWs& ws,
-                               const uint16_t* seed, const int8_t* code, const uint16_t* scale, int P, int b,
-                               int idx_bits, int seed_bits, int scale_bits, int L, uint64_t h,
-                               uint64_t stream_cap, uint8_t* stream_out, hipStream_t st) {
+                               const PackArgs& pa, bool exact, hipStream_t st) {
   const double* g = gain + t0;
   int64_t cb = (n + kThreads - 1) / kThreads;
   if (cb > 512) cb = 512;
@@ -790,60 +1145,69 @@ hipError_t launch_rank_segment(const double* gain, int64_t t0, int64_t n, int64_
   int64_t sb = (n + 4 * kThreads - 1) / (4 * kThreads);
   if (sb > 128) sb = 128;
   if (sb < 1) sb = 1;
-  for (int pass = 1; pass <= 5; ++pass)
+  const int n_pass = exact ? 5 : 1;
+  for (int pass = 1; pass <= n_pass; ++pass)
     hipLaunchKernelGGL(k_select_pass, dim3((unsigned)sb), dim3(kThreads), 0, st, g, n, ws.state,
                        (int64_t)(cap > 0 ? cap : 0), pass, shifts[pass - 1], widths[pass - 1], shifts[pass],
-                       widths[pass]);
+                       widths[pass], exact ? 0 : 1);
+  if (!exact) {
+    int64_t cap_items = cap + (int64_t)cap_slack((size_t)n);
+    if (cap_items > n) cap_items = n;
+    // small segments in shorter chunks, so that more blocks share them
+    const int rounds = n > ((int64_t)1 << 22) ? 16 : 4;
+    int64_t nb = (n + kThreads * rounds - 1) / (kThreads * rounds);
+    nb = nb < 1 ? 1 : nb > 1536 ? 1536 : nb;
+    if (rounds == 16)
+      hipLaunchKernelGGL((k_compact_fast<16>), dim3((unsigned)nb), dim3(kThreads), 0, st, g, pa.seed, pa.scale, t0, n,
+                         ws.state, (uint64_t)cap_items, ws.items_a);
+    else
+      hipLaunchKernelGGL((k_compact_fast<4>), dim3((unsigned)nb), dim3(kThreads), 0, st, g, pa.seed, pa.scale, t0, n,
+                         ws.state, (uint64_t)cap_items, ws.items_a);
+    if (cap <= 0 || n <= 0) return hipGetLastError();
+    if (cap_items <= kRadixMin) {
+      sort_and_pack(ws, cap_items, 1, pa, st);
+      return hipGetLastError();
+    }
+    const int nblk = (int)((cap_items + kRsItems - 1) / kRsItems);
+    SortItem* in = ws.items_a;
+    SortItem* out = ws.items_b;
+    for (int pass = 0; pass < 3; ++pass) {
+      hipLaunchKernelGGL((k_rs_hist<9, true>), dim3((unsigned)nblk), dim3(kRsThreads), 0, st, in, ws.state, cap_items,
+                         pass == 0 ? 1 : 0, 9 * pass, ws.rs_hist, nblk);
+      hipLaunchKernelGGL(k_rs_scan, dim3(512), dim3(1024), 0, st, ws.rs_hist, nblk, ws.rs_tot);
+      hipLaunchKernelGGL((k_rs_scatter<9, true>), dim3((unsigned)nblk), dim3(kRsThreads), 0, st, in, out, ws.state,
+                         cap_items, 9 * pass, ws.rs_hist, nblk, ws.rs_tot, 0, pa);
+      SortItem* tt = in; in = out; out = tt;
+    }
+    hipLaunchKernelGGL(k_pack_cells, dim3((unsigned)((cap_items + 255) / 256)), dim3(256), 0, st, in, ws.state,
+                       cap_items, pa);
+    return hipGetLastError();
+  }
   // the first compaction launch finishes the select and records the totals
   int64_t nbc = (n + kItems - 1) / kItems;
   if (nbc < 1) nbc = 1;
   hipLaunchKernelGGL(k_compact_count, dim3((unsigned)nbc), dim3(kThreads), 0, st, g, n, ws.state, ws.blk_a, ws.blk_b);
   hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(1024), 0, st, ws.blk_a, ws.blk_b, nbc, ws.state);
   if (cap <= 0 || n <= 0) return hipGetLastError();
-  hipLaunchKernelGGL(k_compact_write, dim3((unsigned)nbc), dim3(kThreads), 0, st, g, seed, scale, t0, n, ws.state,
+  hipLaunchKernelGGL(k_compact_write, dim3((unsigned)nbc), dim3(kThreads), 0, st, g, pa.seed, pa.scale, t0, n, ws.state,
                      ws.blk_a, ws.blk_b, ws.items_a);
-  // sort the survivors ascending on (~key, tile): LDS chunks, then multiway
-  // merges; the final pass packs the records instead of writing items
-  const PackArgs pa{seed, code, scale, P, b, idx_bits, seed_bits, scale_bits, L, h, stream_cap, stream_out};
+  // sort the survivors ascending on (~key, tile)
   if (cap > kRadixMin) {
-    const int nblk = (int)ws.rs_nblk;
+    const int nblk = (int)((cap + kRsItems - 1) / kRsItems);
     SortItem* in = ws.items_a;
     SortItem* out = ws.items_b;
-    for (int pass = 0; pass < 64 / kRsBits; ++pass) {
-      const int shift = pass * kRsBits;
-      const int last = pass == 64 / kRsBits - 1 ? 1 : 0;
-      hipLaunchKernelGGL(k_rs_hist, dim3((unsigned)nblk), dim3(kRsThreads), 0, st, in, ws.state, shift, ws.rs_hist,
-                         nblk);
-      hipLaunchKernelGGL(k_rs_scan, dim3(kRsBins), dim3(1024), 0, st, ws.rs_hist, nblk, ws.rs_tot);
-      hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)nblk), dim3(kRsThreads), 0, st, in, out, ws.state, shift,
-                         ws.rs_hist, nblk, ws.rs_tot, last, pa);
+    for (int pass = 0; pass < 8; ++pass) {
+      hipLaunchKernelGGL((k_rs_hist<8, false>), dim3((unsigned)nblk), dim3(kRsThreads), 0, st, in, ws.state, cap, 0,
+                         8 * pass, ws.rs_hist, nblk);
+      hipLaunchKernelGGL(k_rs_scan, dim3(256), dim3(1024), 0, st, ws.rs_hist, nblk, ws.rs_tot);
+      hipLaunchKernelGGL((k_rs_scatter<8, false>), dim3((unsigned)nblk), dim3(kRsThreads), 0, st, in, out, ws.state, cap,
+                         8 * pass, ws.rs_hist, nblk, ws.rs_tot, pass == 7 ? 1 : 0, pa);
       SortItem* tt = in; in = out; out = tt;
     }
     return hipGetLastError();
   }
-  int passes = 0;
-  for (int logw = kLogChunk; ((int64_t)1 << logw) < cap; logw += cap <= ((int64_t)4 << logw) ? 2 : kLogFan) ++passes;
-  hipLaunchKernelGGL(k_sort_chunks, dim3((unsigned)((cap + kChunk - 1) / kChunk)), dim3(kChunkThreads), 0, st,
-                     ws.items_a, ws.state, passes == 0 ? 1 : 0, pa);
-  SortItem* in = ws.items_a;
-  SortItem* out = ws.items_b;
-  int done = 0;
-  for (int logw = kLogChunk; ((int64_t)1 << logw) < cap;) {
-    const dim3 grid((unsigned)((cap + 255) / 256));
-    const int last = ++done == passes ? 1 : 0;
-    if (cap <= ((int64_t)4 << logw)) {  // at most four runs left: one base-8 pass
-      hipLaunchKernelGGL((k_merge_runs<3, 4>), grid, dim3(256), 0, st, in, ws.state, logw, out, last, pa);
-      logw += 2;
-    } else {
-      hipLaunchKernelGGL((k_merge_runs<1, kFan>), grid, dim3(256), 0, st, in, ws.state, logw, out, last, pa);
-      logw += kLogFan;
-    }
-    SortItem* t = in; in = out; out = t;
-  }
+  sort_and_pack(ws, cap, 0, pa, st);
   return hipGetLastError();
 }
-
-// Totals of one call: records, eligible tiles, no-space flag.
-const uint64_t* rank_totals(const RankWs& ws) { return ws.state + kTotK; }
 
 }  // namespace awsrc

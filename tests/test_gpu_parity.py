@@ -415,6 +415,78 @@ def test_rank_large_segment_with_ties():
         assert K == K_o and bytes(s.cpu().numpy().tobytes()) == want
 
 
+def _want_stream_records(rec, segs, caps):
+    """Records of a P = 8, b = 4, S = 256 stream (11 bytes: tile u32, seed u8,
+    eight 4-bit codes, scale u16) by a numpy ordering of each segment."""
+    gain, out = rec["gain"].cpu().numpy(), []
+    for (t0, n), cap in zip(segs, caps):
+        el = t0 + np.nonzero(gain[t0:t0 + n] > 0)[0]
+        out.append(el[np.lexsort((el, -gain[el]))][:cap])
+    t = np.concatenate(out)
+    raw = np.empty((t.size, 11), dtype=np.uint8)
+    raw[:, :4] = t.astype("<u4").view(np.uint8).reshape(-1, 4)
+    raw[:, 4] = rec["seed"].cpu().numpy()[t] & 0xFF
+    c = rec["codes"].cpu().numpy()[t].astype(np.uint8) & 0xF
+    raw[:, 5:9] = c[:, 0::2] | (c[:, 1::2] << 4)
+    raw[:, 9:] = rec["scale"].cpu().numpy()[t].astype("<u2").view(np.uint8).reshape(-1, 2)
+    return t.size, raw
+
+
+@pytest.mark.parametrize("shapes,per_module,bpw,kind", [
+    ([(1, 64)], False, 8.0, "plain"),                        # one tile
+    ([(2048, 64)], False, 0.3, "plain"),                     # the two sizes of the one-workgroup sort
+    ([(2049, 64)], False, 0.3, "odd"),
+    ([(8192, 64)], False, 30.0, "odd"),                      # every eligible record fits the budget
+    ([(8192, 64)], False, 0.3, "ties"),
+    ([(8193, 64)], False, 0.3, "odd"),                       # first size of the multi-launch path
+    ([(8193, 64)], False, 0.3, "same"),                      # one value: more equal gains than it holds spare
+    ([(3, 64), (5000, 64), (1, 128), (40, 640)], True, 0.2, "odd"),
+    ([(3, 64)] * 257, True, 2.0, "plain"),                   # more segments than the small table
+    ([(9000, 64), (3, 64), (20000, 64)], True, 0.2, "ties"),
+    ([(300, 64)] * 20, False, 0.2, "plain"),
+    ([(70000, 64)], False, 0.9, "plain"),                    # chunks of the sort, then merges
+    ([(1200000, 64)], False, 1.7, "plain"),                  # record cap above 2^20: cells of the radix sort
+    ([(1200000, 64)], False, 1.7, "odd"),
+    ([(1200000, 64)], False, 1.7, "narrow"),                 # cells that overflow
+])
+def test_rank_paths(shapes, per_module, bpw, kind):
+    """Every path of the ranking (one workgroup per small segment, the fast
+    selection with chunk and cell sorts, the exact path behind it) at the sizes
+    where they meet, byte-exact, with infinite, NaN, subnormal, negative and
+    equal gains."""
+    T = sum(r * c // 64 for r, c in shapes)
+    p = awsrc.make_params(64, 8, 4, 256)
+    rec = gen_records(T, 8, 4, 256, seed=9, device=DEV, frac_ties=0.6 if kind == "ties" else 0.0)
+    g = rec["gain"]
+    if kind == "odd":
+        for k, v in enumerate((float("inf"), float("nan"), 5e-324, 1e-310, -float("inf"), 0.0, -0.0, 1e300, 1e-300)):
+            g[k * 7 % T::max(1, T // 5)] = v
+    elif kind == "same":
+        g.fill_(0.25)
+    elif kind == "narrow":
+        g.copy_(1.0 + torch.arange(T, device=DEV, dtype=torch.float64).mul_(2654435761 % T).remainder_(T) * 2.0 ** -52)
+    segs, caps, off = [], [], 0
+    L, h = 11, 40 + 8 * len(shapes)
+    for r, c in shapes if per_module else [(T, 64)]:
+        n = r * c // 64
+        segs.append((off, n))
+        caps.append(int(bpw * n * 64 / 8) // L if per_module else (int(bpw * T * 64 / 8) - h) // L)
+        off += n
+    K_want, raw = _want_stream_records(rec, segs, caps)
+    mode = awsrc.AWSRC_MODE_PER_MODULE if per_module else awsrc.AWSRC_MODE_GLOBAL
+    s, K, ne = awsrc.awsrc_rank_prefix(p, shapes, mode, bpw, rec["seed"], rec["codes"], rec["scale"], g)
+    assert K == K_want and ne == int((g > 0).sum())
+    got = s.cpu().numpy()
+    hd = O.parse_header(got[:h].tobytes())
+    assert hd["T_total"] == T and got.size == h + K * L
+    assert np.array_equal(got[h:].reshape(K, L), raw)
+    if K > 1:  # one byte short: refused
+        with pytest.raises(awsrc.AwsrcError) as e:
+            awsrc.awsrc_rank_prefix(p, shapes, mode, bpw, rec["seed"], rec["codes"], rec["scale"], g,
+                                    stream_cap=h + K * L - 1)
+        assert e.value.status == awsrc.AWSRC_ENOSPC
+
+
 def test_rank_stack3b_scale_global_order():
     """Global ranking at the size of the 36-layer stack (252 modules, 43.35M
     tiles, 0.32 bpw: about 9.2M records): K from the budget, the records'
