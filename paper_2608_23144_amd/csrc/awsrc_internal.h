@@ -452,7 +452,7 @@ struct PackArgs {
 };
 
 constexpr int kStateWords = 32 + 3 * 4096;  // rank state: scalars, pick states, three select histograms
-constexpr int64_t kSmallMax = 8192;         // tiles of a small segment
+constexpr int64_t kSmallMax = 4096;         // tiles of a small segment
 constexpr int kSmallSegs = 256;             // segments of a call on the small path
 constexpr int kRankTotals = 4;              // records, eligible tiles, no-space flag, run-again flag
 

@@ -34,9 +34,9 @@ namespace awsrc {
 constexpr int kThreads = 256;
 constexpr int kRounds = 16;
 constexpr int kItems = kThreads * kRounds;  // items per block in the compaction
-constexpr int kChunk = 4096;                // items per LDS-sorted chunk
-constexpr int kChunkThreads = 1024;
-constexpr int kLogChunk = 12;
+constexpr int kChunk = 256;                 // items per LDS-sorted chunk
+constexpr int kChunkThreads = 128;
+constexpr int kLogChunk = 8;
 constexpr int kFan = 16;                    // runs per multiway merge
 constexpr int kLogFan = 4;
 constexpr int kSelBits = 12;                // radix-select digit width
@@ -524,16 +524,39 @@ __device__ __forceinline__ void put_bits(uint64_t (&w)[3], int& pos, uint64_t v,
   pos += nbits;
 }
 
+// The P codes of tile t as bytes (code p in byte p), in one load where they
+// fill an aligned word.
+struct Codes {
+  uint64_t w[2];
+};
+__device__ __forceinline__ Codes load_codes(const PackArgs& pa, uint32_t t) {
+  const int8_t* c = pa.code + (int64_t)t * pa.P;
+  Codes r = {{0, 0}};
+  if (pa.P == 8 && (reinterpret_cast<uintptr_t>(pa.code) & 7) == 0) {
+    r.w[0] = *reinterpret_cast<const uint64_t*>(c);
+  } else if (pa.P == 4 && (reinterpret_cast<uintptr_t>(pa.code) & 3) == 0) {
+    r.w[0] = *reinterpret_cast<const uint32_t*>(c);
+  } else {
+#pragma unroll
+    for (int p = 0; p < kMaxP; ++p)
+      if (p < pa.P) r.w[p >> 3] |= (uint64_t)(uint8_t)c[p] << (8 * (p & 7));
+  }
+  return r;
+}
+
 // Record of tile t (aux = its seed | scale << 16) into a slot of the stream.
 // A record at a 4-byte aligned place whose size is a multiple of 4 goes out
 // as whole words.
-__device__ __forceinline__ void write_record(const PackArgs& pa, uint64_t slot, uint32_t t, uint32_t aux) {
+__device__ __forceinline__ void write_record(const PackArgs& pa, uint64_t slot, uint32_t t, uint32_t aux,
+                                             const Codes& codes) {
   uint64_t w[3] = {0, 0, 0};
   int pos = 0;
   put_bits(w, pos, (uint64_t)t, pa.idx_bits);
   put_bits(w, pos, (uint64_t)(aux & 0xFFFFu), pa.seed_bits);
   const uint64_t cm = (1ull << pa.b) - 1ull;
-  for (int p = 0; p < pa.P; ++p) put_bits(w, pos, (uint64_t)(int64_t)pa.code[(int64_t)t * pa.P + p] & cm, pa.b);
+#pragma unroll
+  for (int p = 0; p < kMaxP; ++p)
+    if (p < pa.P) put_bits(w, pos, (codes.w[p >> 3] >> (8 * (p & 7))) & cm, pa.b);
   put_bits(w, pos, (uint64_t)(aux >> 16) & ((1ull << pa.scale_bits) - 1ull), pa.scale_bits);
   uint8_t* o = pa.out + pa.h + slot * (uint64_t)pa.L;
   if (((reinterpret_cast<uintptr_t>(o) | (uintptr_t)pa.L) & 3) == 0) {
@@ -547,19 +570,20 @@ __device__ __forceinline__ void write_record(const PackArgs& pa, uint64_t slot, 
 // Record i of the segment (tile t) goes to byte h + (first slot + i) * L of
 // the stream; a stream buffer too small for the running total raises the
 // no-space flag instead.
-__device__ void pack_record(const PackArgs& pa, uint64_t* state, int64_t i, uint32_t t, uint32_t aux) {
+__device__ __forceinline__ void pack_record(const PackArgs& pa, uint64_t* state, int64_t i, uint32_t t, uint32_t aux,
+                                            const Codes& codes) {
   const uint64_t K = state[kSegK], off = state[kSegOff];
   if ((uint64_t)i >= K) return;  // the fast path sorts a few more items than it keeps
   if (pa.h + (off + K) * (uint64_t)pa.L > pa.cap) {
     if (i == 0) state[kNoSpace] = 1;
     return;
   }
-  write_record(pa, off + (uint64_t)i, t, aux);
+  write_record(pa, off + (uint64_t)i, t, aux, codes);
 }
 
 // the same, with the seed and scale read from the encoder outputs
 __device__ __forceinline__ void pack_record(const PackArgs& pa, uint64_t* state, int64_t i, uint32_t t) {
-  pack_record(pa, state, i, t, (uint32_t)pa.seed[t] | ((uint32_t)pa.scale[t] << 16));
+  pack_record(pa, state, i, t, (uint32_t)pa.seed[t] | ((uint32_t)pa.scale[t] << 16), load_codes(pa, t));
 }
 
 // ---------------------------------------------------------------- sort of the survivors
@@ -680,9 +704,10 @@ __global__ __launch_bounds__(256) void k_small_count(const double* __restrict__ 
 }
 
 template <int M>
-__global__ __launch_bounds__(1024) void k_small_rank(const double* __restrict__ gain, SmallTable tb, int n_seg,
+__global__ __launch_bounds__(M / 2 < 1024 ? M / 2 : 1024) void k_small_rank(const double* __restrict__ gain, SmallTable tb, int n_seg,
                                                      const uint64_t* __restrict__ kseg, uint64_t* state, HeaderChunk hc,
                                                      int n_hdr, PackArgs pa, uint64_t* __restrict__ totals) {
+  constexpr int THREADS = M / 2 < 1024 ? M / 2 : 1024;
   __shared__ uint64_t sk[M];
   __shared__ uint32_t st[M];
   __shared__ uint64_t s_sum[2];
@@ -690,17 +715,17 @@ __global__ __launch_bounds__(1024) void k_small_rank(const double* __restrict__ 
   const SmallSeg sg = small_seg(tb, blockIdx.x);
   const bool last = (int)blockIdx.x == n_seg - 1;
   if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i < n_hdr; i += 1024) pa.out[i] = hc.b[i];
+    for (int i = threadIdx.x; i < n_hdr; i += THREADS) pa.out[i] = hc.b[i];
   if (threadIdx.x < 2) s_sum[threadIdx.x] = 0;
   if (threadIdx.x == 0) s_el = 0;
   __syncthreads();
   // records and eligible tiles of the earlier segments
-  for (int i = threadIdx.x; i < (int)blockIdx.x; i += 1024) {
+  for (int i = threadIdx.x; i < (int)blockIdx.x; i += THREADS) {
     atomicAdd((unsigned long long*)&s_sum[0], (unsigned long long)kseg[2 * i]);
     atomicAdd((unsigned long long*)&s_sum[1], (unsigned long long)kseg[2 * i + 1]);
   }
   uint32_t c = 0;
-  for (int i = threadIdx.x; i < M; i += 1024) {
+  for (int i = threadIdx.x; i < M; i += THREADS) {
     const uint64_t k = i < sg.n ? gain_key(gain[sg.t0 + i]) : 0ull;
     c += k != 0;
     sk[i] = ~k;  // ineligible tiles and padding sort last
@@ -709,14 +734,14 @@ __global__ __launch_bounds__(1024) void k_small_rank(const double* __restrict__ 
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off, 64);
   if ((threadIdx.x & 63) == 0 && c) atomicAdd(&s_el, c);
-  bitonic_lds<M, (M / 2 < 1024 ? M / 2 : 1024)>(sk, st);
+  bitonic_lds<M, THREADS>(sk, st);
   const uint64_t elig = s_el, off = s_sum[0];
   const uint64_t K = elig < (uint64_t)sg.cap ? elig : (uint64_t)sg.cap;
   const bool fits = pa.h + (off + K) * (uint64_t)pa.L <= pa.cap;
   if (fits)
-    for (int i = threadIdx.x; i < (int)K; i += 1024) {
+    for (int i = threadIdx.x; i < (int)K; i += THREADS) {
       const uint32_t t = (uint32_t)sg.t0 + st[i];
-      write_record(pa, off + (uint64_t)i, t, (uint32_t)pa.seed[t] | ((uint32_t)pa.scale[t] << 16));
+      write_record(pa, off + (uint64_t)i, t, (uint32_t)pa.seed[t] | ((uint32_t)pa.scale[t] << 16), load_codes(pa, t));
     }
   if (last && threadIdx.x == 0) {
     totals[0] = off + K;
@@ -990,7 +1015,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const SortItem* __res
       const SortItem x = s_items[j];
       const uint32_t d = digit(x.key);
       const uint32_t off = dbase[d] + ((uint32_t)j - lstart[d]);
-      if (pack) pack_record(pa, state, (int64_t)off, x.tile, x.aux);
+      if (pack) pack_record(pa, state, (int64_t)off, x.tile, x.aux, load_codes(pa, x.tile));
       else out[off] = x;
     }
   }
@@ -1000,35 +1025,64 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const SortItem* __res
 // finds its place among the items of its own cell (by key, then tile) and is
 // packed.  A cell of more than kCellMax items (gains that agree in more than
 // 20 mantissa bits, many times over) sets kAgain.
+// A block's keys (and kCellMax to either side) are compared in LDS, while the
+// gathers of its tiles' codes, the bulk of the memory time, are in flight.
 constexpr int kCellMax = 64;
+constexpr int kPcRounds = 4;
+constexpr int kPcItems = 256 * kPcRounds;
 __global__ __launch_bounds__(256) void k_pack_cells(const SortItem* __restrict__ in, uint64_t* state, int64_t cap_items,
                                                     PackArgs pa) {
+  __shared__ uint64_t sk[kPcItems + 2 * kCellMax];
+  __shared__ uint32_t st[kPcItems + 2 * kCellMax];
   const int64_t n = sort_count(state, cap_items);
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
+  const int64_t base = (int64_t)blockIdx.x * kPcItems;
+  if (base >= n) return;  // uniform per block
   const uint64_t kb = state[kBase];
   const int s0 = (int)state[kShift];
-  const SortItem x = in[i];
-  const uint64_t cell = sort_value<true>(x.key, kb, s0);
-  int64_t pos = i;
-  int64_t j = i - 1;
-  for (; j >= 0 && i - j <= kCellMax; --j) {
-    const SortItem y = in[j];
-    if (sort_value<true>(y.key, kb, s0) != cell) break;
-    pos -= kv_less(x, y);
+  SortItem x[kPcRounds];
+#pragma unroll
+  for (int r = 0; r < kPcRounds; ++r) {
+    const int64_t i = base + r * 256 + threadIdx.x;
+    x[r] = in[i < n ? i : n - 1];
   }
-  const int64_t back = i - 1 - j;
-  j = i + 1;
-  for (; j < n && j - i <= kCellMax; ++j) {
-    const SortItem y = in[j];
-    if (sort_value<true>(y.key, kb, s0) != cell) break;
-    pos += kv_less(y, x);
+  if (threadIdx.x < 2 * kCellMax) {  // the halo; places outside [0, n) are never compared
+    const int j = threadIdx.x < kCellMax ? (int)threadIdx.x : kPcItems + (int)threadIdx.x;
+    const int64_t i = base + j - kCellMax;
+    if (i >= 0 && i < n) { sk[j] = in[i].key; st[j] = in[i].tile; }
   }
-  if (back + (j - i) > kCellMax) {
-    state[kAgain] = 1;
-    return;
+  Codes c[kPcRounds];
+#pragma unroll
+  for (int r = 0; r < kPcRounds; ++r) c[r] = load_codes(pa, x[r].tile);
+#pragma unroll
+  for (int r = 0; r < kPcRounds; ++r) {
+    sk[kCellMax + r * 256 + threadIdx.x] = x[r].key;
+    st[kCellMax + r * 256 + threadIdx.x] = x[r].tile;
   }
-  pack_record(pa, state, pos, x.tile, x.aux);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kPcRounds; ++r) {
+    const int64_t i = base + r * 256 + threadIdx.x;
+    if (i >= n) break;
+    const int at = kCellMax + r * 256 + threadIdx.x;
+    const uint64_t cell = sort_value<true>(x[r].key, kb, s0);
+    const int lo = i < kCellMax ? (int)i : kCellMax;                 // items before and after this one in reach
+    const int hi = n - 1 - i < kCellMax ? (int)(n - 1 - i) : kCellMax;
+    int64_t pos = i;
+    int d = 1;
+    for (; d <= lo; ++d) {
+      const SortItem y{sk[at - d], st[at - d], 0u};
+      if (sort_value<true>(y.key, kb, s0) != cell) break;
+      pos -= kv_less(x[r], y);
+    }
+    int e = 1;
+    for (; e <= hi; ++e) {
+      const SortItem y{sk[at + e], st[at + e], 0u};
+      if (sort_value<true>(y.key, kb, s0) != cell) break;
+      pos += kv_less(y, x[r]);
+    }
+    if (d - 1 + e - 1 >= kCellMax) state[kAgain] = 1;
+    else pack_record(pa, state, pos, x[r].tile, x[r].aux, c[r]);
+  }
 }
 
 // ---------------------------------------------------------------- workspace
@@ -1091,7 +1145,10 @@ bool rank_small(int64_t max_n, size_t n_seg) { return max_n <= kSmallMax && n_se
 hipError_t launch_rank_small(const double* gain, const SmallTable& tb, int n_seg, int64_t max_n, const RankWs& ws,
                              const HeaderChunk& hc, int n_hdr, const PackArgs& pa, uint64_t* totals, hipStream_t st) {
   if (n_seg > 1) hipLaunchKernelGGL(k_small_count, dim3((unsigned)n_seg), dim3(256), 0, st, gain, tb, ws.kseg);
-  if (max_n <= 2048)
+  if (max_n <= 1024)
+    hipLaunchKernelGGL((k_small_rank<1024>), dim3((unsigned)n_seg), dim3(512), 0, st, gain, tb, n_seg, ws.kseg, ws.state,
+                       hc, n_hdr, pa, totals);
+  else if (max_n <= 2048)
     hipLaunchKernelGGL((k_small_rank<2048>), dim3((unsigned)n_seg), dim3(1024), 0, st, gain, tb, n_seg, ws.kseg,
                        ws.state, hc, n_hdr, pa, totals);
   else
@@ -1143,7 +1200,9 @@ hipError_t launch_rank_segment(const double* gain, int64_t t0, int64_t n, int64_
   // fewer blocks than the counting pass: every block repeats the pick (a read
   // of the 32 KB histogram), and the keys under the prefix thin out fast
   int64_t sb = (n + 4 * kThreads - 1) / (4 * kThreads);
-  if (sb > 128) sb = 128;
+  // (the fast path's one pass reads every gain: on many, twice the machine)
+  const int64_t sb_max = !exact && n > ((int64_t)1 << 22) ? 512 : 128;
+  if (sb > sb_max) sb = sb_max;
   if (sb < 1) sb = 1;
   const int n_pass = exact ? 5 : 1;
   for (int pass = 1; pass <= n_pass; ++pass)
@@ -1179,7 +1238,7 @@ hipError_t launch_rank_segment(const double* gain, int64_t t0, int64_t n, int64_
                          cap_items, 9 * pass, ws.rs_hist, nblk, ws.rs_tot, 0, pa);
       SortItem* tt = in; in = out; out = tt;
     }
-    hipLaunchKernelGGL(k_pack_cells, dim3((unsigned)((cap_items + 255) / 256)), dim3(256), 0, st, in, ws.state,
+    hipLaunchKernelGGL(k_pack_cells, dim3((unsigned)((cap_items + kPcItems - 1) / kPcItems)), dim3(256), 0, st, in, ws.state,
                        cap_items, pa);
     return hipGetLastError();
   }

@@ -434,12 +434,13 @@ def _want_stream_records(rec, segs, caps):
 
 @pytest.mark.parametrize("shapes,per_module,bpw,kind", [
     ([(1, 64)], False, 8.0, "plain"),                        # one tile
-    ([(2048, 64)], False, 0.3, "plain"),                     # the two sizes of the one-workgroup sort
-    ([(2049, 64)], False, 0.3, "odd"),
-    ([(8192, 64)], False, 30.0, "odd"),                      # every eligible record fits the budget
-    ([(8192, 64)], False, 0.3, "ties"),
-    ([(8193, 64)], False, 0.3, "odd"),                       # first size of the multi-launch path
-    ([(8193, 64)], False, 0.3, "same"),                      # one value: more equal gains than it holds spare
+    ([(1024, 64)], False, 0.3, "plain"),                     # the sizes of the one-workgroup sort
+    ([(1025, 64)], False, 0.3, "odd"),
+    ([(2049, 64)], False, 0.3, "plain"),
+    ([(4096, 64)], False, 30.0, "odd"),                      # every eligible record fits the budget
+    ([(4096, 64)], False, 0.3, "ties"),
+    ([(4097, 64)], False, 0.3, "odd"),                       # first size of the multi-launch path
+    ([(9000, 64)], False, 0.3, "same"),                      # one value: more equal gains than it holds spare
     ([(3, 64), (5000, 64), (1, 128), (40, 640)], True, 0.2, "odd"),
     ([(3, 64)] * 257, True, 2.0, "plain"),                   # more segments than the small table
     ([(9000, 64), (3, 64), (20000, 64)], True, 0.2, "ties"),
