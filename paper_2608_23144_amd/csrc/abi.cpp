@@ -80,13 +80,13 @@ constexpr int kHeaderFixed = 40;
 
 // A small piece of pinned host memory that kernels write results of a call to,
 // so that the host reads them after one stream synchronization (a copy into
-// pageable memory costs 11 us more).  64 slots of 1 KiB in one block, allocated
+// pageable memory costs 11 us more).  64 slots of 4 KiB in one block, allocated
 // on first use and kept until the process ends; a slot is taken for the length
 // of a call and given back, and a call that finds none free (more than 64 in
 // flight, or no pinned memory) reads through a copy instead.
 class HostSlot {
  public:
-  static constexpr size_t kBytes = 1024;
+  static constexpr size_t kBytes = 4096;
   HostSlot() {
     std::lock_guard<std::mutex> lock(mu());
     Block& b = block();
@@ -120,6 +120,23 @@ class HostSlot {
   HostSlot& operator=(const HostSlot&) = delete;
   // where a kernel writes the results: the slot, or `device` when there is none
   uint64_t* device_or(uint64_t* device) const { return dev_ ? static_cast<uint64_t*>(dev_) : device; }
+  // n host bytes (a multiple of 8) of device memory, waiting for the stream
+  hipError_t fetch(void* dst, const void* device, size_t n, hipStream_t s) const {
+    if (!dev_ || n > kBytes) {
+      const hipError_t e = hipMemcpyAsync(dst, device, n, hipMemcpyDeviceToHost, s);
+      return e != hipSuccess ? e : hipStreamSynchronize(s);
+    }
+    const hipError_t e = launch_stage_words(nullptr, 0, nullptr, static_cast<const uint64_t*>(device), (int)(n / 8),
+                                            static_cast<uint64_t*>(dev_), s);
+    return e != hipSuccess ? e : read(dst, n, device, s);
+  }
+  // a word of the slot that kernels may set, cleared; null when there is no slot
+  unsigned long long* flag() const {
+    if (dev_) *reinterpret_cast<volatile uint64_t*>(host_) = 0;
+    return static_cast<unsigned long long*>(dev_);
+  }
+  bool holds(size_t n) const { return dev_ && n <= kBytes; }
+  bool flag_set() const { return *reinterpret_cast<volatile uint64_t*>(host_) != 0; }
   // waits for the stream and fetches n bytes of results
   hipError_t read(void* dst, size_t n, const void* device, hipStream_t s) const {
     if (!dev_) {
@@ -245,7 +262,7 @@ awsrc_status encode_module(const awsrc_params* p, const void* W, int32_t w_dtype
   a.seed_out = seed_out; a.code_out = code_out; a.scale_out = scale_out; a.gain_out = gain_out;
   a.alpha_out = alpha_or_null;
   HIPCHK(launch_scored_init(a, s, add_scored));
-  HIPCHK(launch_gen_basis(p->basis_key, p->C, p->P, p->S, p->gen_version, a.basis, false, s));
+  HIPCHK(launch_gen_basis(p->basis_key, p->C, p->P, p->S, p->gen_version, a.basis, s));
   if (d_mode == AWSRC_D_PER_COL) HIPCHK(launch_col_factors(a, s));
   HIPCHK(launch_encode_screen(a, s));
   if (!a.fused_rescore) HIPCHK(launch_encode_finalize(a, s));
@@ -423,7 +440,7 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
     if (items > (int64_t)INT32_MAX) return fail(AWSRC_EINVAL, "too many work items");
     if (n_modules > 1) HIPCHK(launch_mod_table(tab.data(), n_modules, mods, s));
     HIPCHK(launch_scored_zero(a.scored, s));  // the pruned screen adds its count
-    HIPCHK(launch_gen_basis(p->basis_key, p->C, p->P, p->S, p->gen_version, a.basis, false, s));
+    HIPCHK(launch_gen_basis(p->basis_key, p->C, p->P, p->S, p->gen_version, a.basis, s));
     HIPCHK(launch_perm_screen(a, tab[0], mods, n_modules, items2, s));
     HIPCHK(launch_finalize_pe_modules(a, tab[0], mods, n_modules, items, s));
     return AWSRC_OK;
@@ -471,7 +488,7 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
   if (items > (int64_t)INT32_MAX) return fail(AWSRC_EINVAL, "too many work items");
   HIPCHK(launch_mod_table(tab.data(), n_modules, mods, s));
   HIPCHK(launch_scored_zero(a.scored, s));  // the pruned screen adds its count
-  HIPCHK(launch_gen_basis(p->basis_key, p->C, p->P, p->S, p->gen_version, a.basis, false, s));
+  HIPCHK(launch_gen_basis(p->basis_key, p->C, p->P, p->S, p->gen_version, a.basis, s));
   HIPCHK(launch_pe_screen(a, mods, n_modules, items, a.frag, colsh, s));
   HIPCHK(launch_finalize_pe_modules(a, tab[0], mods, n_modules, items, s));
   return AWSRC_OK;
@@ -845,8 +862,8 @@ extern "C" awsrc_status awsrc_decode_prepare(const uint8_t* stream_bytes, uint64
   // host copies of this call (header, module tables, error count) use
   // buffers that live until the stream is synchronized
   std::vector<uint8_t> hbuf(h_caller);
-  HIPCHK(hipMemcpyAsync(hbuf.data(), stream_bytes, h_caller, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
+  HostSlot slot;
+  HIPCHK(slot.fetch(hbuf.data(), stream_bytes, h_caller, s));
   const uint8_t* fx = hbuf.data();
   if (memcmp(fx, "AWSR", 4) != 0) return fail(AWSRC_ECORRUPT, "bad magic");
   if (get_le(fx + 4, 2) != 1) return fail(AWSRC_ECORRUPT, "unsupported stream version");
@@ -904,14 +921,21 @@ extern "C" awsrc_status awsrc_decode_prepare(const uint8_t* stream_bytes, uint64
   pl.K = K; pl.T_total = T_total; pl.h = h;
   pl.records = stream_bytes + h;
   pl.workspace = workspace;
-  const DecodeArgs a = decode_args(&pl);
+  DecodeArgs a = decode_args(&pl);
+  a.err_flag = slot.flag();
   memcpy(tabs.data() + 2 * (size_t)nmod + 1, W0_ptrs, nmod * sizeof(void*));
-  HIPCHK(hipMemcpyAsync(const_cast<uint64_t*>(a.mod_tile_off), tabs.data(), tabs.size() * 8, hipMemcpyHostToDevice, s));
-  HIPCHK(launch_gen_basis(key, C, P, (int)S, gen, a.basis, true, s));
+  // the module tables go by value when they fit, else in a copy of their own
+  const bool by_value = tabs.size() <= (size_t)kTableWords;
+  if (!by_value)
+    HIPCHK(hipMemcpyAsync(const_cast<uint64_t*>(a.mod_tile_off), tabs.data(), tabs.size() * 8, hipMemcpyHostToDevice, s));
+  HIPCHK(launch_decode_setup(key, gen, a, tabs.data(), by_value ? (int)tabs.size() : 0, s));
   HIPCHK(launch_decode_validate(a, s));
   unsigned long long nerr = 0;
-  HIPCHK(hipMemcpyAsync(&nerr, a.errors, 8, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
+  if (a.err_flag) HIPCHK(hipStreamSynchronize(s));
+  if (!a.err_flag || slot.flag_set()) {
+    HIPCHK(hipMemcpyAsync(&nerr, a.errors, 8, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+  }
   if (nerr) return fail(AWSRC_ECORRUPT, "%llu invalid or duplicate records", nerr);
   *plan = pl;
   return AWSRC_OK;
@@ -979,9 +1003,15 @@ awsrc_status reconstruct(const awsrc_decode_plan* plan, int32_t n_out, const int
   uint64_t* bbt = reinterpret_cast<uint64_t*>(ws + l.total - 256 - l.bbtab);
   hipStream_t s = (hipStream_t)stream;
   std::vector<uint64_t> mt(2 * (size_t)n + 1, 0);
-  HIPCHK(hipMemcpyAsync(bbt, tabs.data(), tabs.size() * 8, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(mt.data(), a.mod_tile_off, mt.size() * 8, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
+  HostSlot slot;
+  if (tabs.size() <= (size_t)kTableWords && slot.holds(mt.size() * 8)) {
+    HIPCHK(launch_stage_words(tabs.data(), (int)tabs.size(), bbt, a.mod_tile_off, (int)mt.size(),
+                              slot.device_or(nullptr), s));
+    HIPCHK(slot.read(mt.data(), mt.size() * 8, nullptr, s));
+  } else {
+    HIPCHK(hipMemcpyAsync(bbt, tabs.data(), tabs.size() * 8, hipMemcpyHostToDevice, s));
+    HIPCHK(slot.fetch(mt.data(), a.mod_tile_off, mt.size() * 8, s));
+  }
   for (uint32_t m = 0; m < n; ++m) {
     const int64_t c = (int64_t)mt[n + 1 + m];
     if (c % group) return fail(AWSRC_EINVAL, "module %u: cols %lld not a multiple of group %d", m, (long long)c, group);

@@ -264,9 +264,8 @@ __device__ __forceinline__ float screen_score_ldl(const float (&b)[PB], const FP
 // Each returns hipSuccess or the first HIP error.
 // Basis tables of GenBasis version gen_version (1: signs and columns; 2: also
 // the seeded coordinate permutation, B_s[j, p] = sigma_j H[pi(j), c_p]/sqrt(C)).
-// tsign (the decoder's transposed table) is built only on request.
-hipError_t launch_gen_basis(uint64_t key, int C, int P, int S, int gen_version, BasisTables t, bool tsign,
-                            hipStream_t st);
+// (The decoder's tsign comes from launch_decode_setup.)
+hipError_t launch_gen_basis(uint64_t key, int C, int P, int S, int gen_version, BasisTables t, hipStream_t st);
 
 // Scale double quantization of the backbone's group scales (blocks of 256).
 int64_t sdq_blocks(int64_t n_groups);
@@ -501,6 +500,7 @@ struct DecodeArgs {
   // read gives a tile's rank
   uint32_t* bitmap;
   unsigned long long* errors;    // [1]
+  unsigned long long* err_flag;  // host-visible word set when a record is bad, or null
   // [K][2] decoded records written by validation: {tile within module,
   // module, seed | scale << 16, sum of codes}, then the P codes as int8 (zero
   // padded to 16)
@@ -508,6 +508,20 @@ struct DecodeArgs {
   uint4* dec_t;                  // [K + 1][2] the same records in tile order (reconstruction)
   uint32_t* bsum;                // [ceil(words / 4096)] scan scratch
 };
+// Words passed to a kernel by value (tables small enough for it).
+constexpr int kTableWords = 448;
+struct TableChunk {
+  uint64_t w[kTableWords];
+};
+// Everything validation and decoding read besides the records, in one launch:
+// the transposed sign table, the module tables (n_tabs <= kTableWords host
+// words, 0: already copied), the cleared bitmap and error count.
+hipError_t launch_decode_setup(uint64_t key, int gen_version, const DecodeArgs& a, const uint64_t* tabs, int n_tabs,
+                               hipStream_t st);
+// n_tab <= kTableWords host words to device memory `to`, and n_out device
+// words from src to `out` (host-visible), in one launch.
+hipError_t launch_stage_words(const uint64_t* tab, int n_tab, uint64_t* to, const uint64_t* src, int n_out,
+                              uint64_t* out, hipStream_t st);
 hipError_t launch_decode_validate(const DecodeArgs& a, hipStream_t st);
 hipError_t launch_decode_apply(const DecodeArgs& a, hipStream_t st);
 

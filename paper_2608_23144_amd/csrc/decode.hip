@@ -13,9 +13,12 @@
 // reconstruct (dense bf16) - the decoded records put in tile order (prefix
 //            counts of the bitmap words give each record tile its rank), then
 //            one streaming pass over every weight.
+#include <string.h>
+
 #include <type_traits>
 
 #include "awsrc_internal.h"
+#include "basis_gen.h"
 
 namespace awsrc {
 
@@ -101,10 +104,68 @@ __device__ __forceinline__ Rec parse(const DecodeArgs& a, int64_t i) {
   return out;
 }
 
-__global__ void k_fill_u32(uint32_t* p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0u;
+// One launch sets a decode up: the transposed sign table (blocks below
+// seed_blocks, one wavefront per seed: every lane repeats the draws of
+// GenBasis and forms the sign bits of its coordinates), the module tables
+// (passed by value), the cleared error count and the cleared bitmap (the other
+// blocks).  As separate launches, a copy and two fills these cost some 25 us a
+// call at sizes where the decode itself takes as long.
+__global__ __launch_bounds__(256) void k_decode_setup(uint64_t key, int gen_version, DecodeArgs a, int seed_blocks,
+                                                      TableChunk tab, int n_tab, int64_t fill_words) {
+  __shared__ uint64_t s_key[4][kMaxC];
+  if (blockIdx.x == 0) {
+    uint64_t* t = const_cast<uint64_t*>(a.mod_tile_off);
+    for (int i = threadIdx.x; i < n_tab; i += 256) t[i] = tab.w[i];
+    if (threadIdx.x == 0) *a.errors = 0ull;
+  }
+  if ((int)blockIdx.x >= seed_blocks) {
+    u32x4_t* b = reinterpret_cast<u32x4_t*>(a.bitmap);  // 256-byte aligned and padded
+    const int64_t n = (fill_words + 3) / 4, step = (int64_t)(gridDim.x - seed_blocks) * 256;
+    for (int64_t i = (int64_t)(blockIdx.x - seed_blocks) * 256 + threadIdx.x; i < n; i += step)
+      b[i] = u32x4_t{0u, 0u, 0u, 0u};
+    return;
+  }
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int s = (int)blockIdx.x * 4 + wv;
+  const int C = a.C, P = a.P, nw = (C + 63) / 64;
+  const uint64_t base = (uint64_t)s << 32;
+  if (gen_version == 2) {
+    for (int j = lane; j < C; j += 64) s_key[wv][j] = splitmix64(key, base + (uint64_t)(nw + P + j));
+    __syncthreads();  // (every seed block takes this branch)
+  }
+  if (s >= a.S) return;
+  int c[kMaxP];
+  uint64_t used[2] = {0ull, 0ull};
+#pragma unroll
+  for (int p = 0; p < kMaxP; ++p) c[p] = p < P ? draw_column(key, base, nw, C, p, used) : 0;
+  for (int h = 0; h < nw; ++h) {
+    const int j = lane + 64 * h;
+    if (j >= C) break;
+    int at = j;
+    if (gen_version == 2) {  // the rank of (word, j)
+      at = 0;
+      const uint64_t kj = s_key[wv][j];
+      for (int i = 0; i < C; ++i) {
+        const uint64_t ki = s_key[wv][i];
+        at += (ki < kj) || (ki == kj && i < j);
+      }
+    }
+    const uint32_t sg = (uint32_t)(splitmix64(key, base + (uint64_t)h) >> (j & 63)) & 1u;
+    uint32_t t = 0;
+#pragma unroll
+    for (int p = 0; p < kMaxP; ++p)
+      if (p < P) t |= (sg ^ (uint32_t)(__popc((unsigned)(at & c[p])) & 1)) << p;
+    a.basis.tsign[(size_t)s * kMaxC + j] = (uint16_t)t;
+  }
+}
+
+// Tables passed by value into device memory, and a piece of device memory out
+// to where the host reads it.
+__global__ __launch_bounds__(256) void k_stage_words(TableChunk tab, int n_tab, uint64_t* __restrict__ to,
+                                                     const uint64_t* __restrict__ src, int n_out,
+                                                     uint64_t* __restrict__ out) {
+  for (int i = threadIdx.x; i < n_tab; i += 256) to[i] = tab.w[i];
+  for (int i = threadIdx.x; i < n_out; i += 256) out[i] = src[i];
 }
 
 // field checks of one record (everything but a repeated tile)
@@ -137,7 +198,10 @@ __global__ __launch_bounds__(256) void k_decode_validate(DecodeArgs a) {
     const uint32_t old = atomicOr(&a.bitmap[2 * (r.idx >> 5)], bit);
     bad = (old & bit) != 0;
   }
-  if (bad) atomicAdd(a.errors, 1ull);
+  if (bad) {
+    atomicAdd(a.errors, 1ull);
+    if (a.err_flag) __hip_atomic_store(a.err_flag, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
   // decoded form for the apply pass (only used once the whole stream is valid)
   int lo = 0, hi = a.n_modules - 1;
   while (lo < hi) {
@@ -216,11 +280,19 @@ __global__ __launch_bounds__(1024) void k_scan_top(DecodeArgs a, int64_t nb) {
   }
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_words(DecodeArgs a, int64_t nw) {
+// scanned: k_scan_top has run; else each block adds up the sums before its own
+__global__ __launch_bounds__(kScanThreads) void k_scan_words(DecodeArgs a, int64_t nw, int scanned) {
   __shared__ uint32_t s_wave[kScanThreads / 64];
   const int64_t w0 = (int64_t)blockIdx.x * kScanBlockWords + (int64_t)threadIdx.x * kScanWords;
-  uint32_t tot;
-  uint32_t run = a.bsum[blockIdx.x] +
+  uint32_t tot, before = 0;
+  if (scanned) {
+    before = a.bsum[blockIdx.x];
+  } else {
+    uint32_t c = 0;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += kScanThreads) c += a.bsum[i];
+    block_exclusive_scan<kScanThreads>(c, s_wave, &before);
+  }
+  uint32_t run = before +
                  block_exclusive_scan<kScanThreads>(thread_word_count(a.bitmap, nw, w0), s_wave, &tot);
 #pragma unroll
   for (int k = 0; k < kScanWords; ++k) {
@@ -737,8 +809,11 @@ hipError_t launch_reconstruct_bf16(const DecodeArgs& a, const BackboneTabs& bb, 
     const int64_t nwords = (int64_t)((a.T_total + 31) / 32);
     const int64_t nb = (nwords + kScanBlockWords - 1) / kScanBlockWords;
     hipLaunchKernelGGL(k_scan_sums, dim3((unsigned)nb), dim3(kScanThreads), 0, st, a, nwords);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, st, a, nb);
-    hipLaunchKernelGGL(k_scan_words, dim3((unsigned)nb), dim3(kScanThreads), 0, st, a, nwords);
+    // up to 1024 sums every block of the next launch adds them up itself (at
+    // most four loads a thread); a launch of its own costs 4 us
+    const int scanned = nb > 1024 ? 1 : 0;
+    if (scanned) hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, st, a, nb);
+    hipLaunchKernelGGL(k_scan_words, dim3((unsigned)nb), dim3(kScanThreads), 0, st, a, nwords, scanned);
     hipLaunchKernelGGL(k_decode_tile_order, dim3((unsigned)((a.K + 255) / 256)), dim3(256), 0, st, a);
     HIP_RETURN_IF(hipGetLastError());
   }
@@ -758,13 +833,29 @@ hipError_t launch_reconstruct_bf16(const DecodeArgs& a, const BackboneTabs& bb, 
   return hipSuccess;
 }
 
-hipError_t launch_decode_validate(const DecodeArgs& a, hipStream_t st) {
-  const int64_t nwords = (int64_t)((a.T_total + 31) / 32);
-  int64_t fb = (nwords + 255) / 256;
-  if (fb > 4096) fb = 4096;
+hipError_t launch_decode_setup(uint64_t key, int gen_version, const DecodeArgs& a, const uint64_t* tabs, int n_tabs,
+                               hipStream_t st) {
+  const int64_t words = 2 * (int64_t)((a.T_total + 31) / 32);
+  int64_t fb = (words + 4095) / 4096;
+  if (fb > 1024) fb = 1024;
   if (fb < 1) fb = 1;
-  hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)fb), dim3(256), 0, st, a.bitmap, 2 * nwords);
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(a.errors), (int64_t)2);
+  const int sb = (a.S + 3) / 4;
+  TableChunk tab;
+  if (n_tabs) memcpy(tab.w, tabs, (size_t)n_tabs * 8);
+  hipLaunchKernelGGL(k_decode_setup, dim3((unsigned)(sb + fb)), dim3(256), 0, st, key, gen_version, a, sb, tab, n_tabs,
+                     words);
+  return hipGetLastError();
+}
+
+hipError_t launch_stage_words(const uint64_t* tab, int n_tab, uint64_t* to, const uint64_t* src, int n_out,
+                              uint64_t* out, hipStream_t st) {
+  TableChunk tc;
+  if (n_tab) memcpy(tc.w, tab, (size_t)n_tab * 8);
+  hipLaunchKernelGGL(k_stage_words, dim3(1), dim3(256), 0, st, tc, n_tab, to, src, n_out, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_decode_validate(const DecodeArgs& a, hipStream_t st) {
   if (a.K > 0)
     hipLaunchKernelGGL(k_decode_validate, dim3((unsigned)((a.K + 255) / 256)), dim3(256), 0, st, a);
   return hipGetLastError();
