@@ -221,7 +221,9 @@ size_t module_ws_bytes(const awsrc_params* p, int64_t rows, int64_t cols, int32_
   const int nsplit = screen_nsplit(p->C, p->P, p->S, rows, cols, d_mode, p->gen_version);
   const size_t b_tg = align_up((size_t)T * nsplit * kTop * 4, 256);
   const size_t b_ts = align_up((size_t)T * nsplit * kTop * 4, 256);
-  return 256 + b_basis + b_fac + b_wd + b_frag + b_tg + b_ts + 256;
+  const size_t b_white =
+      white_supported(p->C, p->P, p->S, d_mode, p->gen_version, rows, cols) ? align_up(white_bytes(p->C, p->S, cols), 256) : 0;
+  return 256 + b_basis + b_fac + b_wd + b_frag + b_tg + b_ts + b_white + 256;
 }
 
 awsrc_status encode_module(const awsrc_params* p, const void* W, int32_t w_dtype, const float* W0, int64_t rows,
@@ -257,6 +259,9 @@ awsrc_status encode_module(const awsrc_params* p, const void* W, int32_t w_dtype
   a.top_gain = reinterpret_cast<float*>(ws);
   ws += b_tg;
   a.top_seed = reinterpret_cast<uint32_t*>(ws);
+  ws += b_tg;  // (as many bytes)
+  a.white =
+      white_supported(p->C, p->P, p->S, d_mode, p->gen_version, rows, cols) ? static_cast<void*>(ws) : nullptr;
   a.nsplit = nsplit;
   a.fused_rescore = screen_fuses_rescore(p->C, p->P, d_mode, p->gen_version, nsplit) ? 1 : 0;
   a.seed_out = seed_out; a.code_out = code_out; a.scale_out = scale_out; a.gain_out = gain_out;

@@ -294,6 +294,7 @@ struct EncodeArgs {
   double* wd64;        // per-column fp64 Walsh-Hadamard transform of d per block [nb][C]
   unsigned long long* scored;  // count of candidates scored in full (the pruned screen adds to it)
   void* frag;          // +-1 basis fragments of the matrix-core screen
+  void* white;         // whitened basis of a group of column blocks (encode_white.hip), or null
   float* top_gain;     // [T][nsplit][kTop] screened gains per seed range, descending
                        // (the batched per-element encoder: [item][kTop][32], see launch_pe_lists_tile_order)
   uint32_t* top_seed;  // same layout: seed | kEdge flag
@@ -398,6 +399,10 @@ bool perm_batched_supported(int C, int P, int d_mode, int gen_version);
 constexpr int kPermRows = 64;  // rows per workgroup (offsets in ModEntry::item2_off)
 hipError_t launch_perm_screen(const EncodeArgs& a, const ModEntry& one, const ModEntry* mods, int n_mods,
                               int64_t items2, hipStream_t st);
+// The screen with a whitened basis (encode_white.hip) and its table's size.
+bool white_supported(int C, int P, int S, int d_mode, int gen_version, int64_t rows, int64_t cols);
+size_t white_bytes(int C, int S, int64_t cols);
+hipError_t launch_white_screen(const EncodeArgs& a, void* ws, hipStream_t st);
 hipError_t launch_encode_screen_mfma(const EncodeArgs& a, void* frag, hipStream_t st);
 hipError_t launch_col_factors(const EncodeArgs& a, hipStream_t st);
 hipError_t launch_encode_screen(const EncodeArgs& a, hipStream_t st);

@@ -777,6 +777,7 @@ static hipError_t run_finalize(const EncodeArgs& a, hipStream_t st) {
 #define PBSEL(C_, P_) factor_pb(C_, P_)
 hipError_t launch_col_factors(const EncodeArgs& a, hipStream_t st) { AWSRC_DISPATCH(run_factors, a, st); }
 hipError_t launch_encode_screen(const EncodeArgs& a, hipStream_t st) {
+  if (a.white) return launch_white_screen(a, a.white, st);
   if (screen_mfma_supported(a.C, a.P, a.d_mode, a.gen_version)) return launch_encode_screen_mfma(a, a.frag, st);
   AWSRC_DISPATCH(run_screen, a, st);
 }

@@ -134,6 +134,44 @@ def test_encode_small_shapes(C, P, b, S, rows, cols, d_mode):
     assert nd <= max(1, T // 50)
 
 
+@pytest.mark.parametrize("P,b,S,rows,cols,fmt,name", [
+    (8, 3, 1024, 1025, 4096, 0, "block3b"),   # one row past a group, two seed ranges
+    (8, 4, 1024, 1100, 8448, 0, "linear256"), # 66 column blocks of 2 MB: two groups of blocks
+    (5, 4, 257, 1087, 15616, 1, "block3b")])  # odd S, padded P, power-of-two scale
+def test_encode_whitened_c128(P, b, S, rows, cols, fmt, name):
+    """The C = 128 per-column screen with a whitened basis (from 256 seeds,
+    1024 rows and 2^25 candidates on): group and pair remainders against the
+    oracle on a sample with the last rows and blocks, and tiles of zero
+    residual, which keep seed 0 and gain 0."""
+    wl = workload(name, C=128, P=P, b=b, S=S, d_mode="col")
+    m = Module("t", rows, cols, 0, 5, 5)
+    inp, bb, enc = _gpu_module(wl, m, fmt=fmt)
+    T, nb = rows * cols // 128, cols // 128
+    idx = np.unique(np.r_[np.arange(0, T, T // 300), np.arange(T - 40, T), np.arange(nb - 1, T, 64 * nb)])
+    nd = _check_encode_sample(wl, m, inp, bb[3], enc, idx, fmt=fmt)
+    assert nd <= max(1, idx.size // 50)
+    W = bb[3].clone()  # residual zero everywhere but in the last column
+    W[:, -1] += 0.01
+    z = awsrc.awsrc_encode_tiles(_params(wl, fmt), W, bb[3], inp["d"])
+    seed = _u16(z["seed"]).reshape(rows, -1)
+    gain = z["gain"].cpu().numpy().reshape(rows, -1)
+    assert np.all(seed[:, :-1] == 0) and np.all(gain[:, :-1] == 0) and np.all(gain[:, -1] >= 0)
+
+
+def test_encode_whitened_matches_rows():
+    """The same rows through the whitened screen (1024 of them in one call)
+    and through the smaller calls' screen give the same records."""
+    wl = workload("block3b", C=128, P=8, b=3, S=1024, d_mode="col")
+    m = Module("t", 1024, 4096, 0, 6, 6)
+    inp, bb, enc = _gpu_module(wl, m)
+    nb = m.cols // 128
+    for r0 in (0, 512):
+        part = awsrc.awsrc_encode_tiles(_params(wl), inp["W"][r0:r0 + 512].contiguous(),
+                                        bb[3][r0:r0 + 512].contiguous(), inp["d"])
+        for k in ("seed", "codes", "scale", "gain"):
+            assert torch.equal(part[k], enc[k][r0 * nb:(r0 + 512) * nb]), k
+
+
 @pytest.mark.parametrize("P,S,rows,cols,d_mode", [(8, 48, 70, 256, "col"), (3, 30, 64, 128, "col"),
                                                    (5, 62, 129, 256, "col"), (8, 40, 67, 256, "elem"),
                                                    (4, 256, 64, 128, "elem")])
