@@ -209,7 +209,9 @@ namespace {
 
 // Workspace of one module on the per-module kernels (every path but the
 // batched per-element one): size only, or carve it and launch.
-size_t module_ws_bytes(const awsrc_params* p, int64_t rows, int64_t cols, int32_t d_mode) {
+// `white` returns the part at its end that only the whitened screen uses: a
+// workspace without it is enough, and takes the other screen of that shape.
+size_t module_ws_bytes(const awsrc_params* p, int64_t rows, int64_t cols, int32_t d_mode, size_t* white) {
   const int64_t nb = cols / p->C;
   const int64_t T = rows * nb;
   const int PB = factor_pb(p->C, p->P);
@@ -223,13 +225,14 @@ size_t module_ws_bytes(const awsrc_params* p, int64_t rows, int64_t cols, int32_
   const size_t b_ts = align_up((size_t)T * nsplit * kTop * 4, 256);
   const size_t b_white =
       white_supported(p->C, p->P, p->S, d_mode, p->gen_version, rows, cols) ? align_up(white_bytes(p->C, p->S, cols), 256) : 0;
+  *white = b_white;
   return 256 + b_basis + b_fac + b_wd + b_frag + b_tg + b_ts + b_white + 256;
 }
 
 awsrc_status encode_module(const awsrc_params* p, const void* W, int32_t w_dtype, const float* W0, int64_t rows,
                            int64_t cols, const float* d, int32_t d_mode, uint16_t* seed_out, int8_t* code_out,
-                           uint16_t* scale_out, double* gain_out, float* alpha_or_null, char* ws, bool add_scored,
-                           hipStream_t s) {
+                           uint16_t* scale_out, double* gain_out, float* alpha_or_null, char* ws, bool white,
+                           bool add_scored, hipStream_t s) {
   const int64_t nb = cols / p->C;
   const int64_t T = rows * nb;
   const int PB = factor_pb(p->C, p->P);
@@ -260,8 +263,7 @@ awsrc_status encode_module(const awsrc_params* p, const void* W, int32_t w_dtype
   ws += b_tg;
   a.top_seed = reinterpret_cast<uint32_t*>(ws);
   ws += b_tg;  // (as many bytes)
-  a.white =
-      white_supported(p->C, p->P, p->S, d_mode, p->gen_version, rows, cols) ? static_cast<void*>(ws) : nullptr;
+  a.white = white ? static_cast<void*>(ws) : nullptr;
   a.nsplit = nsplit;
   a.fused_rescore = screen_fuses_rescore(p->C, p->P, d_mode, p->gen_version, nsplit) ? 1 : 0;
   a.seed_out = seed_out; a.code_out = code_out; a.scale_out = scale_out; a.gain_out = gain_out;
@@ -371,7 +373,7 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
   if (T_total > (int64_t)UINT32_MAX) return fail(AWSRC_EINVAL, "more than 2^32 tiles");
   const bool c16 = c16_supported(p->C, p->P);
   const bool batched = pe_batched_supported(p->C, p->P, d_mode, p->gen_version);
-  size_t need = 0;
+  size_t need = 0, least = 0;  // asked for, and enough
   const bool perm = perm_batched_supported(p->C, p->P, d_mode, p->gen_version);
   if (c16) {
     need = c16_layout(p, n_modules, T_total).total;
@@ -381,12 +383,15 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
     need = pe_layout(p, n_modules, pe_items(p, n_modules, rows, cols)).total;
   } else {
     for (int m = 0; m < n_modules; ++m) {
-      const size_t b = module_ws_bytes(p, rows[m], cols[m], d_mode);
+      size_t white = 0;
+      const size_t b = module_ws_bytes(p, rows[m], cols[m], d_mode, &white);
       need = b > need ? b : need;
+      least = b - white > least ? b - white : least;
     }
   }
+  if (!least) least = need;
   if (!workspace) { *ws_bytes = need; return AWSRC_OK; }
-  if (*ws_bytes < need) return fail(AWSRC_ENOSPC, "workspace %zu < %zu bytes", *ws_bytes, need);
+  if (*ws_bytes < least) return fail(AWSRC_ENOSPC, "workspace %zu < %zu bytes", *ws_bytes, least);
   if (T_total == 0) return AWSRC_OK;
   if (!W || !W0 || !d || !seed_out || !code_out || !scale_out || !gain_out) return fail(AWSRC_EINVAL, "NULL buffer");
   for (int m = 0; m < n_modules; ++m) {
@@ -456,9 +461,11 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
     for (int m = 0; m < n_modules; ++m) {
       const int64_t T = rows[m] * (cols[m] / p->C);
       if (T == 0) continue;
+      size_t white = 0;
+      const bool fits = module_ws_bytes(p, rows[m], cols[m], d_mode, &white) <= *ws_bytes;
       st = encode_module(p, W[m], w_dtype, W0[m], rows[m], cols[m], d[m], d_mode, seed_out + t0,
                          code_out + t0 * p->P, scale_out + t0, gain_out + t0,
-                         alpha_or_null ? alpha_or_null + t0 * p->P : nullptr, ws, !first, s);
+                         alpha_or_null ? alpha_or_null + t0 * p->P : nullptr, ws, white && fits, !first, s);
       if (st) return st;
       first = false;
       t0 += T;
@@ -628,6 +635,8 @@ extern "C" awsrc_status awsrc_encode_tiles_noalloc(const awsrc_params* p, const 
   awsrc_status st = awsrc_encode_tiles(p, W, w_dtype, W0, rows, cols, d, d_mode, seed_out, code_out, scale_out,
                                        gain_out, alpha_or_null, nullptr, &need, stream);
   if (st) return st;
+  if (white_supported(p->C, p->P, p->S, d_mode, p->gen_version, rows, cols))
+    need -= align_up(white_bytes(p->C, p->S, cols), 256);  // not needed (module_ws_bytes)
   if (need > kNoallocScratchBytes)
     return fail(AWSRC_ENOSPC, "module needs %zu bytes of scratch, more than the %zu-byte static array", need,
                 kNoallocScratchBytes);

@@ -160,10 +160,18 @@ def test_encode_whitened_c128(P, b, S, rows, cols, fmt, name):
 
 def test_encode_whitened_matches_rows():
     """The same rows through the whitened screen (1024 of them in one call)
-    and through the smaller calls' screen give the same records."""
+    and through the smaller calls' screen give the same records, and so does
+    the whole module through the entry point with a fixed scratch, which has
+    no room for the whitened basis (135 MB; that call took the module before)."""
     wl = workload("block3b", C=128, P=8, b=3, S=1024, d_mode="col")
-    m = Module("t", 1024, 4096, 0, 6, 6)
+    m = Module("t", 1024, 8448, 0, 6, 6)
     inp, bb, enc = _gpu_module(wl, m)
+    assert awsrc.encode_workspace_bytes(_params(wl), inp["W"], awsrc.AWSRC_D_PER_COL) > 64 << 20
+    fixed = awsrc.awsrc_encode_tiles_noalloc(_params(wl), inp["W"], bb[3], inp["d"],
+                                             out={k: torch.empty_like(enc[k])
+                                                  for k in ("seed", "codes", "scale", "gain", "alpha")})
+    for k in ("seed", "codes", "scale", "gain"):
+        assert torch.equal(fixed[k], enc[k]), k
     nb = m.cols // 128
     for r0 in (0, 512):
         part = awsrc.awsrc_encode_tiles(_params(wl), inp["W"][r0:r0 + 512].contiguous(),
