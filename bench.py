@@ -71,7 +71,7 @@ MEASURED_TRAFFIC = {
         "bytes": 26142208960},
     # one step of the 32B layer (profiles/counters_layer32b.md)
     ("encode", "layer32b"): {
-        "files": ["awsrc_internal.h", "basis.hip", "encode.hip", "encode_mfma.hip", "encode_pe.hip",
+        "files": ["awsrc_internal.h", "basis.hip", "encode.hip", "encode_mfma.hip", "encode_white.hip", "encode_pe.hip",
                   "rescore_pe.hip", "rescore64.h"],
         "sha256": "f5cd199c3a5245c6611d36b08ee9fe96bce500bab8f26b718433d744bcd47246",
         "bytes": 8115737536},
@@ -233,6 +233,15 @@ def encode_split_bound(C: int, P: int, per_element: bool, gen_version: int, scor
     bnd = bound_ops_per_candidate(P, per_element)
     valu = bnd + scored_frac * (full - bnd) if scored_frac < 1.0 else full
     return {"mfma_flops_per_candidate": 6.0 * P * C, "valu_ops_per_candidate": valu}
+
+
+def whitened_split_bound(C: int, P: int, scored_frac: float) -> dict:
+    """The same for the whitened screen: 2 P C fp16 flops per candidate, whose
+    P results are squared, summed and compared (P + 1 ops); the fraction scored
+    in full is projected from fp32 (P (C - 1)) and solved."""
+    full = ops_per_candidate(C, P, False, 1) - min(P * C, C * int(math.log2(C)))
+    return {"mfma_flops_per_candidate": 2.0 * P * C,
+            "valu_ops_per_candidate": P + 1 + scored_frac * (P * (C - 1) + full)}
 
 
 def sdq_timing(awsrc, torch, wl, run, stream, reps: int = 20) -> dict:
@@ -424,7 +433,10 @@ def encode_roofline(awsrc, run: Run, stage_ms: dict, gen_version: int) -> dict:
     scored = awsrc.awsrc_encode_scored(run.enc_out)
     f_scored = scored / cand
     if mfma_screen(wl.C, wl.P, per_elem, gen_version):
-        sb = encode_split_bound(wl.C, wl.P, per_elem, gen_version, f_scored)
+        white = (wl.C == 128 and not per_elem and gen_version == 1 and wl.S >= 256
+                 and all(m.rows >= 1024 and m.rows * (m.cols // wl.C) * wl.S >= 1 << 25 for m in wl.modules))
+        sb = (whitened_split_bound(wl.C, wl.P, f_scored) if white
+              else encode_split_bound(wl.C, wl.P, per_elem, gen_version, f_scored))
         t_mfma = cand * sb["mfma_flops_per_candidate"] / (PEAK_MFMA_BF16_TFLOPS * 1e12)
         t_valu = cand * sb["valu_ops_per_candidate"] / (PEAK_VALU_TOPS * 1e12)
         if t_mfma >= t_valu:
