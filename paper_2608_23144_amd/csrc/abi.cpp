@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -300,18 +301,50 @@ PeLayout pe_layout(const awsrc_params* p, int n_modules, int64_t items) {
 }
 
 // Workspace of the C = 16 encoder: count | row tables | sign patterns |
-// module table (several modules) or the screen's lists (one module).
+// module table (several modules) or the screen's lists (one module) | factor
+// table of a group of modules (per-column weights).
 struct C16Layout {
-  size_t frag, masks, mods, list, total;
+  size_t frag, masks, mods, list, fac, total;
 };
-C16Layout c16_layout(const awsrc_params* p, int n_modules, int64_t T_total) {
+C16Layout c16_layout(const awsrc_params* p, int n_modules, int64_t T_total, size_t fac_bytes) {
   C16Layout l;
   l.frag = align_up(c16_frag_bytes(p->S), 256);
   l.masks = align_up(c16_info_bytes(p->S), 256);
   l.mods = n_modules > 1 ? align_up((size_t)n_modules * sizeof(ModEntry), 256) : 0;
   l.list = n_modules > 1 ? 0 : align_up((size_t)T_total * kTop * 4, 256);
-  l.total = 256 + l.frag + l.masks + l.mods + 2 * l.list + 256;
+  l.fac = align_up(fac_bytes, 256);
+  l.total = 256 + l.frag + l.masks + l.mods + 2 * l.list + l.fac + 256;
   return l;
+}
+
+// Modules of the C = 16 encoder that share a launch: all of them, or with
+// per-column weights as many as keep the factor table (64 bytes per column
+// block and seed) within the largest module's or 64 MiB, so that the table of
+// a call over many modules does not grow with their number.
+struct C16Group {
+  int first, n;
+  int64_t blocks;
+};
+constexpr size_t kC16FacBytes = (size_t)64 << 20;
+std::vector<C16Group> c16_groups(const awsrc_params* p, int n_modules, const int64_t* rows, const int64_t* cols,
+                                 int32_t d_mode, size_t* fac_bytes) {
+  std::vector<C16Group> g;
+  *fac_bytes = 0;
+  if (d_mode == AWSRC_D_PER_ELEM) {
+    g.push_back({0, n_modules, 0});
+    return g;
+  }
+  auto blocks = [&](int m) -> int64_t { return rows[m] ? cols[m] / p->C : 0; };
+  size_t most = kC16FacBytes;
+  for (int m = 0; m < n_modules; ++m) most = std::max(most, c16_fac_bytes(p->S, blocks(m)));
+  for (int m = 0; m < n_modules; ++m) {
+    const int64_t b = blocks(m);
+    if (g.empty() || c16_fac_bytes(p->S, g.back().blocks + b) > most) g.push_back({m, 0, 0});
+    ++g.back().n;
+    g.back().blocks += b;
+    *fac_bytes = std::max(*fac_bytes, c16_fac_bytes(p->S, g.back().blocks));
+  }
+  return g;
 }
 
 // Workspace of the version-2 per-element encoder (C = 64): count | basis | the
@@ -376,7 +409,9 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
   size_t need = 0, least = 0;  // asked for, and enough
   const bool perm = perm_batched_supported(p->C, p->P, d_mode, p->gen_version);
   if (c16) {
-    need = c16_layout(p, n_modules, T_total).total;
+    size_t fac_bytes = 0;
+    (void)c16_groups(p, n_modules, rows, cols, d_mode, &fac_bytes);
+    need = c16_layout(p, n_modules, T_total, fac_bytes).total;
   } else if (perm) {
     need = perm_layout(p, n_modules, T_total).total;
   } else if (batched) {
@@ -404,7 +439,9 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
   char* ws = reinterpret_cast<char*>(align_up(reinterpret_cast<uintptr_t>(workspace), 256));
   hipStream_t s = (hipStream_t)stream;
   if (c16) {
-    const C16Layout l = c16_layout(p, n_modules, T_total);
+    size_t fac_bytes = 0;
+    const std::vector<C16Group> groups = c16_groups(p, n_modules, rows, cols, d_mode, &fac_bytes);
+    const C16Layout l = c16_layout(p, n_modules, T_total, fac_bytes);
     EncodeArgs a{};
     a.w_dtype = w_dtype; a.d_mode = d_mode;
     a.C = p->C; a.P = p->P; a.b = p->b; a.S = p->S;
@@ -419,14 +456,30 @@ awsrc_status encode_modules(const awsrc_params* p, int32_t n_modules, const void
       a.top_gain = reinterpret_cast<float*>(masks + l.masks);
       a.top_seed = reinterpret_cast<uint32_t*>(masks + l.masks + l.list);
     }
+    a.colfac = reinterpret_cast<float*>(masks + l.masks + l.mods + 2 * l.list);
     a.seed_out = seed_out; a.code_out = code_out; a.scale_out = scale_out; a.gain_out = gain_out;
     a.alpha_out = alpha_or_null;
     std::vector<ModEntry> tab;
-    const int64_t items = module_entries(p, n_modules, W, W0, d, rows, cols, 0, tab);
+    if (module_entries(p, n_modules, W, W0, d, rows, cols, 0, tab) > (int64_t)INT32_MAX)
+      return fail(AWSRC_EINVAL, "too many work items");
+    // work items and column blocks are counted within a group
+    for (const C16Group& g : groups) {
+      int64_t item = 0, blk = 0;
+      for (int m = g.first; m < g.first + g.n; ++m) {
+        tab[m].item_off = item;
+        tab[m].item2_off = blk;
+        item += c16_items(rows[m] * (cols[m] / p->C));
+        blk += rows[m] ? cols[m] / p->C : 0;
+      }
+      if ((blk * p->S + 255) / 256 > (int64_t)INT32_MAX) return fail(AWSRC_EINVAL, "too many work items");
+    }
     if (n_modules > 1) HIPCHK(launch_mod_table(tab.data(), n_modules, mods, s));
-    if (items > (int64_t)INT32_MAX) return fail(AWSRC_EINVAL, "too many work items");
-    HIPCHK(launch_encode_c16(a, p->basis_key, tab[0], mods, n_modules, items,
-                             (unsigned long long)T_total * (unsigned long long)p->S, frag, masks, s));
+    HIPCHK(launch_c16_tables(a, p->basis_key, (unsigned long long)T_total * (unsigned long long)p->S, frag, masks, s));
+    for (const C16Group& g : groups) {
+      const ModEntry& last = tab[g.first + g.n - 1];
+      const int64_t items = last.item_off + c16_items(last.rows * (last.cols / p->C));
+      if (items) HIPCHK(launch_encode_c16(a, tab[g.first], mods + g.first, g.n, items, g.blocks, frag, masks, s));
+    }
     return AWSRC_OK;
   }
   if (perm) {
@@ -552,7 +605,7 @@ extern "C" awsrc_status awsrc_encode_screen_lists(const awsrc_params* p, int32_t
   }
   if (n_modules != 1) return fail(AWSRC_EINVAL, "lists of several modules on the per-module path are not kept");
   if (c16_supported(p->C, p->P)) {
-    const C16Layout l = c16_layout(p, 1, T_total);
+    const C16Layout l = c16_layout(p, 1, T_total, 0);
     *nsplit = 1;
     if (!gain_out && !seed_out) return AWSRC_OK;
     if (!gain_out || !seed_out) return fail(AWSRC_EINVAL, "NULL output");

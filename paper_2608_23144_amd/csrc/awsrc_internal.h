@@ -318,7 +318,8 @@ struct ModEntry {
   int64_t rows, cols;
   int64_t tile_off;
   int64_t item_off;
-  int64_t item2_off;  // the same in another unit of rows (the version-2 screen's)
+  int64_t item2_off;  // the same in another unit of rows (the version-2 screen's), or
+                      // the first of its column blocks (the C = 16 factor table's)
 };
 static_assert(sizeof(ModEntry) == 64, "module table entries are 64 bytes");
 
@@ -376,12 +377,17 @@ hipError_t launch_pe_lists_tile_order(const float* tg, const uint32_t* ts, const
 // tables of its own (no BasisTables).  Modules are linear runs of tiles, 64
 // per work item; `one` is the module itself when n_mods == 1 (no table).
 // a.top_gain / a.top_seed: where to keep the screen's lists, or null.
+// blocks: column blocks of these modules; a.colfac: their factor table, 64
+// bytes a (block, seed) (per-column weights).
 bool c16_supported(int C, int P);
 int64_t c16_items(int64_t tiles);
 size_t c16_frag_bytes(int S);
 size_t c16_info_bytes(int S);
-hipError_t launch_encode_c16(const EncodeArgs& a, uint64_t key, const ModEntry& one, const ModEntry* mods, int n_mods,
-                             int64_t items, unsigned long long candidates, void* frag, void* info, hipStream_t st);
+size_t c16_fac_bytes(int S, int64_t blocks);
+hipError_t launch_c16_tables(const EncodeArgs& a, uint64_t key, unsigned long long candidates, void* frag, void* info,
+                             hipStream_t st);
+hipError_t launch_encode_c16(const EncodeArgs& a, const ModEntry& one, const ModEntry* mods, int n_mods, int64_t items,
+                             int64_t blocks, const void* frag, const void* info, hipStream_t st);
 
 bool encode_supported(int C, int P);
 // the matrix-core screens: C = 64 (P <= 8), C = 128 (P <= 8, per-column

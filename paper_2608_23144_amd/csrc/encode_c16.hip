@@ -18,21 +18,29 @@
 //     are the same in both halves of K, so a row table of 32 lanes serves.
 //   * The 16 rows of a product are 4 seeds x 4 entries, ordered so that lane
 //     (tile n, g) receives the four entries of seed 4 R + g: one product for
-//     b_0..b_3, two for the six Gram entries and the mean of d (from products
-//     of two sign columns, which serve either generator version).  A lane then
-//     owns a whole candidate without any exchange.
+//     b_0..b_3, and with per-element weights two for the six Gram entries and
+//     the mean of d (from products of two sign columns, which serve either
+//     generator version).  A lane then owns a whole candidate without any
+//     exchange.
+//   * With per-column weights the Gram side belongs to the column block and the
+//     seed: k_c16_factors builds its factor from fp64 sums, as the other
+//     per-column screens have it, 64 bytes a (block, seed) that the lanes read
+//     from the caches.  (Factored per candidate in fp32, one channel 1e5 / 1e6
+//     times the others cost 1331 / 4958 of 15,360 tiles their best seed; from
+//     the table 1092 / 4095, in the general screen 1025 / 4080.)
 //   * Every candidate is scored in full (with 16 seeds, four per lane, there
 //     is little to prune).  One whose rounding is on a knife edge (about 1e-3
 //     of them) is scored again in the general screen's arithmetic: with
-//     power-of-two scales a flipped rounding moves the score by percents.  Each
-//     lane keeps its two best, the four lanes of a
-//     tile merge, and the re-score runs in the same wavefront with one lane
-//     per tile, from the residual and weights kept in LDS.
+//     power-of-two scales a flipped rounding moves the score by percents.  So
+//     is one whose Gram matrix is close to singular (kIll).  Each lane keeps
+//     its two best, the four lanes of a tile merge, and the re-score runs in
+//     the same wavefront with one lane per tile, from the residual and weights
+//     kept in LDS.
 //
 // On the gate, up and down projections of a 3B layer (67.6 M weights, bf16,
 // per-element weights, S = 16): 3884 us with the general vector screen and
-// re-score, 491 us here, 90 of them in the knife-edge scores (a copy of the
-// tensors takes 160).
+// re-score, 500 us here, 90 of them in the knife-edge scores (a copy of the
+// tensors takes 160).  11008 x 2048 with per-column weights: 985 -> 200 us.
 #include <math.h>
 
 #include "awsrc_internal.h"
@@ -49,6 +57,17 @@ constexpr int kC = 16;
 constexpr int kPB = 4;
 constexpr int kNT = 64;       // tiles per wavefront
 constexpr int kRow = 20;      // floats per LDS row of a tile (16-byte aligned rows)
+// A candidate with a pivot e_p below kIll e_0 (e_0 is the mean of d) is scored
+// in the general screen's arithmetic: where a few channels carry nearly all of
+// d the Gram matrix is close to singular, the pivots are what is left of sums
+// that cancel, and the score is decided by the order of those sums.  One
+// channel of each tile 1e5 / 1e6 times the others, per element, tiles (of
+// 15,360) whose best seed in 64 bits is lost: general screen 1142 / 4586,
+// the products here 1342 / 5081, with this rule 1144 / 4586.  At 100 times 1e-4
+// of the candidates are below it, at 1000 times 1%, without outliers none.  The
+// test costs 1% (the MLP projections below: 494 -> 500 us); an 11008 x 2048 module
+// with one channel in 1000 at 1e5 takes 277 us instead of 208.
+constexpr float kIll = 0x1p-10f;
 constexpr int kBlocks = 3;    // row tables per four seeds: b, and two of Gram entries
 
 __device__ __forceinline__ void wave_sync() {
@@ -110,6 +129,11 @@ struct SeedInfo {
 };
 static_assert(sizeof(SeedInfo) == 32, "table entry");
 
+// A factor table entry (per-column weights): L, 1/e and e of col_factor64, padded to whole 64 bytes.
+constexpr int kFac = 16;
+constexpr int kFacLen = kPB * (kPB - 1) / 2 + 2 * kPB;
+static_assert(kFacLen <= kFac, "factor entry");
+
 // Entry k of the length-16 transform of x, in the operation order of the
 // in-place butterflies (so the same value bit for bit).
 __device__ __forceinline__ float wht16_entry(const float (&x)[kC], uint32_t k) {
@@ -126,12 +150,12 @@ __device__ __forceinline__ float wht16_entry(const float (&x)[kC], uint32_t k) {
 }
 
 // The score of one candidate in the general vector screen's arithmetic
-// (projections summed in coordinate order, Gram entries from the transform of
-// the tile's weights or, per column, the fp64 factor): for candidates on a
-// knife edge, see screen_valu.h.  r, d: the tile's LDS rows.
-template <bool POW2>
+// (projections summed in coordinate order; per element, Gram entries from the
+// transform of the tile's weights; per column, the factor table f): for
+// candidates on a knife edge, see screen_valu.h.  r, d: the tile's LDS rows.
+template <bool POW2, bool PE>
 __device__ __forceinline__ float general_score(const EncodeArgs& a, const SeedInfo& si, const float* r, const float* d,
-                                               float qmax, float inv_qmax, bool* edge) {
+                                               const float (&f)[kFacLen], float qmax, float inv_qmax, bool* edge) {
   constexpr int PB = kPB;
   const int P = a.P;
   const uint32_t m[PB] = {si.mask[0] & 0xFFFFu, si.mask[0] >> 16, si.mask[1] & 0xFFFFu, si.mask[1] >> 16};
@@ -144,10 +168,12 @@ __device__ __forceinline__ float general_score(const EncodeArgs& a, const SeedIn
   }
 #pragma unroll
   for (int p = 0; p < PB; ++p) bv[p] = p < P ? bv[p] * 0.25f : 0.0f;
-  uint32_t c[PB];
+  if constexpr (!PE) {
+    return screen_score_ldl<PB, POW2, 0>(bv, f, qmax, inv_qmax, edge);
+  } else {
+    uint32_t c[PB];
 #pragma unroll
-  for (int p = 0; p < PB; ++p) c[p] = (si.col >> (8 * p)) & 15u;
-  if (a.d_mode == AWSRC_D_PER_ELEM) {
+    for (int p = 0; p < PB; ++p) c[p] = (si.col >> (8 * p)) & 15u;
     float x[kC], G[PB][PB];
 #pragma unroll
     for (int i = 0; i < kC; ++i) x[i] = d[(uint32_t)(si.inv >> (4 * i)) & 15u];
@@ -161,30 +187,6 @@ __device__ __forceinline__ float general_score(const EncodeArgs& a, const SeedIn
     }
     return chol_score32<PB>(bv, G, eps, qmax, inv_qmax, POW2, edge);
   }
-  double sum = 0.0, G[PB][PB];
-#pragma unroll
-  for (int p = 0; p < PB; ++p)
-#pragma unroll
-    for (int q = 0; q < p; ++q) G[p][q] = 0.0;
-#pragma unroll
-  for (int j = 0; j < kC; ++j) {
-    const double x = (double)d[j];
-    sum += x;
-#pragma unroll
-    for (int p = 0; p < PB; ++p)
-#pragma unroll
-      for (int q = 0; q < p; ++q) G[p][q] += flip(x, m[p] ^ m[q], j);
-  }
-  const double eps = a.lambda * (sum / kC);
-#pragma unroll
-  for (int p = 0; p < PB; ++p) {
-#pragma unroll
-    for (int q = 0; q < p; ++q) G[p][q] = p < P ? G[p][q] / kC : 0.0;
-    G[p][p] = p < P ? sum / kC + eps : 1.0;
-  }
-  float f[PB * (PB - 1) / 2 + 2 * PB];
-  col_factor64<PB>(G, f);
-  return screen_score_ldl<PB, POW2, 0>(bv, f, qmax, inv_qmax, edge);
 }
 
 }  // namespace
@@ -264,7 +266,55 @@ __global__ __launch_bounds__(64) void k_c16_tables(uint64_t key, int P, int S, i
   }
 }
 
-template <bool POW2, bool FULLP>
+// Per-column weights: the factor of G + eps I of every (column block, seed),
+// from fp64 sums (col_factor64), one thread each; blocks of the modules
+// follow each other (ModEntry::item2_off).
+__global__ __launch_bounds__(256) void k_c16_factors(EncodeArgs a, ModEntry one, const ModEntry* __restrict__ mods,
+                                                     int n_mods, const SeedInfo* __restrict__ info, int64_t blocks) {
+  constexpr int PB = kPB;
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= blocks * a.S) return;
+  const int64_t blk = i / a.S;
+  const int s = (int)(i % a.S);
+  ModEntry md = one;
+  if (n_mods > 1) md = mods[find_module<&ModEntry::item2_off>(mods, n_mods, blk)];
+  const float* dp = md.d + (blk - md.item2_off) * kC;
+  const SeedInfo si = info[s];
+  const uint32_t m[PB] = {si.mask[0] & 0xFFFFu, si.mask[0] >> 16, si.mask[1] & 0xFFFFu, si.mask[1] >> 16};
+  double sum = 0.0, G[PB][PB];
+#pragma unroll
+  for (int p = 0; p < PB; ++p)
+#pragma unroll
+    for (int q = 0; q < p; ++q) G[p][q] = 0.0;
+#pragma unroll
+  for (int j = 0; j < kC; j += 4) {
+    const gf32x4 v = gload4f(dp + j);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const double x = (double)v[k];
+      sum += x;
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+#pragma unroll
+        for (int q = 0; q < p; ++q) G[p][q] += flip(x, m[p] ^ m[q], j + k);
+    }
+  }
+  const double eps = a.lambda * (sum / kC);
+#pragma unroll
+  for (int p = 0; p < PB; ++p) {
+#pragma unroll
+    for (int q = 0; q < p; ++q) G[p][q] = p < a.P ? G[p][q] / kC : 0.0;
+    G[p][p] = p < a.P ? sum / kC + eps : 1.0;
+  }
+  float f[kFac] = {};
+  col_factor64<PB>(G, f);
+#pragma unroll
+  for (int k = 0; k < kFac; k += 4)
+    *reinterpret_cast<f32x4*>(a.colfac + i * kFac + k) = f32x4{f[k], f[k + 1], f[k + 2], f[k + 3]};
+}
+
+// PE: per-element weights; else the Gram side comes from the factor table.
+template <bool POW2, bool FULLP, bool PE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_encode_c16(EncodeArgs a, ModEntry one, const ModEntry* __restrict__ mods,
                                                    int n_mods, const u32x4* __restrict__ frag,
                                                    const SeedInfo* __restrict__ info) {
@@ -279,7 +329,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
   const uint32_t nb = (uint32_t)(md.cols / kC);
   const int64_t T = md.rows * (int64_t)nb;
   const int64_t t0 = (item - md.item_off) * kNT;
-  const bool pe = a.d_mode == AWSRC_D_PER_ELEM;
 
   // lane (n, g): eight coordinates (from 8 (g & 1)) of tiles 16 (g >> 1) + n
   // and 32 + 16 (g >> 1) + n; tiles past the end repeat the last one
@@ -290,7 +339,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
     const int64_t t = tt < T ? tt : T - 1;
     o[2 * i] = t * kC + 8 * (g & 1);
     o[2 * i + 1] = o[2 * i] + 4;
-    od[2 * i] = pe ? o[2 * i] : (int64_t)((uint32_t)t % nb) * kC + 8 * (g & 1);
+    od[2 * i] = PE ? o[2 * i] : (int64_t)((uint32_t)t % nb) * kC + 8 * (g & 1);
     od[2 * i + 1] = od[2 * i] + 4;
   }
   gf32x4 dv[4];
@@ -324,54 +373,82 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
     wave_sync();
     // operands of the two groups of 16 tiles: [hi | mid] and [lo | 0]
     u32x4 U0[2], U1[2], D0[2], D1[2];
-    split3(u, U0[0], U0[1], U1[0]);
-    split3(dd, D0[0], D0[1], D1[0]);
-    U1[1] = u32x4{0, 0, 0, 0};
-    D1[1] = u32x4{0, 0, 0, 0};
+    auto operands = [](const float (&x8)[8], u32x4 (&X0)[2], u32x4 (&X1)[2]) {
+      split3(x8, X0[0], X0[1], X1[0]);
+      X1[1] = u32x4{0, 0, 0, 0};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      uint32_t x = U0[0][e], y = U0[1][e];
-      swap32(x, y);
-      U0[0][e] = x; U0[1][e] = y;
-      x = U1[0][e]; y = U1[1][e];
-      swap32(x, y);
-      U1[0][e] = x; U1[1][e] = y;
-      x = D0[0][e]; y = D0[1][e];
-      swap32(x, y);
-      D0[0][e] = x; D0[1][e] = y;
-      x = D1[0][e]; y = D1[1][e];
-      swap32(x, y);
-      D1[0][e] = x; D1[1][e] = y;
-    }
-    Top2 top[2];
-    u32x4 A0 = fl[0], A1 = fl[32], A2 = fl[64];
-    for (int R = 0; R < nR; ++R) {
-      f32x4 bq[2], ga[2], gb[2];
-      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+      for (int e = 0; e < 4; ++e) {
+        uint32_t x = X0[0][e], y = X0[1][e];
+        swap32(x, y);
+        X0[0][e] = x; X0[1][e] = y;
+        x = X1[0][e]; y = X1[1][e];
+        swap32(x, y);
+        X1[0][e] = x; X1[1][e] = y;
+      }
+    };
+    operands(u, U0, U1);
+    if constexpr (PE) operands(dd, D0, D1);
+    // per-column weights: this lane's tiles' rows of the factor table
+    const float* fr[2];
+    if constexpr (!PE) {
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
-        ga[k] = mfma(A1, D1[k], mfma(A1, D0[k], z));
-        gb[k] = mfma(A2, D1[k], mfma(A2, D0[k], z));
+        const int64_t tt = t0 + 32 * i + 16 * k + n;
+        const uint32_t t = (uint32_t)(tt < T ? tt : T - 1);
+        fr[k] = a.colfac + (md.item2_off + (int64_t)(t % nb)) * a.S * kFac;
+      }
+    }
+    Top2 top[2];
+    u32x4 A0 = fl[0], A1, A2;
+    if constexpr (PE) { A1 = fl[32]; A2 = fl[64]; }
+    for (int R = 0; R < nR; ++R) {
+      const int s = 4 * R + g;
+      f32x4 bq[2], ga[2], gb[2], fv[2][kFac / 4];
+      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+      if constexpr (!PE) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int c = 0; c < kFac / 4; ++c)
+            fv[k][c] = *reinterpret_cast<const f32x4*>(fr[k] + (s < a.S ? s : a.S - 1) * kFac + 4 * c);
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        if constexpr (PE) {
+          ga[k] = mfma(A1, D1[k], mfma(A1, D0[k], z));
+          gb[k] = mfma(A2, D1[k], mfma(A2, D0[k], z));
+        }
         bq[k] = mfma(A0, U1[k], mfma(A0, U0[k], z));
       }
       const u32x4* fn = fl + (size_t)(R + 1 < nR ? R + 1 : R) * (kBlocks * 32);
-      A0 = fn[0]; A1 = fn[32]; A2 = fn[64];
-      const int s = 4 * R + g;
+      A0 = fn[0];
+      if constexpr (PE) { A1 = fn[32]; A2 = fn[64]; }
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         // G + eps I = L diag(e) L^T (the layout of the per-column table)
-        const float gq[LS] = {ga[k][0], ga[k][1], ga[k][2], ga[k][3], gb[k][0], gb[k][1]};
-        const float d0 = gb[k][2], diag = fmaf(lam, d0, d0);
-        float f[LS + 2 * kPB];
-        screen_factor<kPB, FULLP>(gq, diag, P, f);
+        float f[kFacLen];
+        if constexpr (PE) {
+          const float gq[LS] = {ga[k][0], ga[k][1], ga[k][2], ga[k][3], gb[k][0], gb[k][1]};
+          const float d0 = gb[k][2], diag = fmaf(lam, d0, d0);
+          screen_factor<kPB, FULLP>(gq, diag, P, f);
+        } else {
+#pragma unroll
+          for (int c = 0; c < kFacLen; ++c) f[c] = fv[k][c >> 2][c & 3];
+        }
         const float b[kPB] = {bq[k][0], bq[k][1], bq[k][2], bq[k][3]};
         bool edge;
         float gain = screen_score_ldl<kPB, POW2, 0>(b, f, qmax, inv_qmax, &edge);
-        edge = edge && s < a.S;
-        if (__ballot(edge) != 0) {
-          if (edge) {
+        constexpr int E0 = LS + kPB;  // the pivots (1 in padded columns)
+        float least = f[E0];
+#pragma unroll
+        for (int p = 1; p < kPB; ++p) least = FULLP || p < P ? fminf(least, f[E0 + p]) : least;
+        const bool ill = least < kIll * f[E0];
+        const bool general = (int)(edge | ill) & (int)(s < a.S);
+        edge = false;  // as the general score finds it
+        if (__ballot(general) != 0) {
+          if (general) {
             const int at = (32 * i + 16 * k + n) * kRow;
-            gain = general_score<POW2>(a, info[s], rsh + at, dsh + at, qmax, inv_qmax, &edge);
+            gain = general_score<POW2, PE>(a, info[s], rsh + at, dsh + at, f, qmax, inv_qmax, &edge);
           }
         }
         top[k].add(s < a.S ? gain : -INFINITY, (uint32_t)s | (edge ? kEdge : 0u));
@@ -495,20 +572,38 @@ bool c16_supported(int C, int P) { return C == kC && P <= kPB; }
 int64_t c16_items(int64_t tiles) { return (tiles + kNT - 1) / kNT; }
 size_t c16_frag_bytes(int S) { return (size_t)((S + 3) / 4) * kBlocks * 32 * 16; }
 size_t c16_info_bytes(int S) { return (size_t)S * sizeof(SeedInfo); }
+size_t c16_fac_bytes(int S, int64_t blocks) { return (size_t)blocks * S * kFac * 4; }
 
-hipError_t launch_encode_c16(const EncodeArgs& a, uint64_t key, const ModEntry& one, const ModEntry* mods, int n_mods,
-                             int64_t items, unsigned long long candidates, void* frag, void* info, hipStream_t st) {
-  u32x4* fr = static_cast<u32x4*>(frag);
-  SeedInfo* mk = static_cast<SeedInfo*>(info);
-  hipLaunchKernelGGL(k_c16_tables, dim3((unsigned)((a.S + 3) / 4)), dim3(64), 0, st, key, a.P, a.S, a.gen_version, fr, mk,
-                     a.scored, candidates);
+hipError_t launch_c16_tables(const EncodeArgs& a, uint64_t key, unsigned long long candidates, void* frag, void* info,
+                             hipStream_t st) {
+  hipLaunchKernelGGL(k_c16_tables, dim3((unsigned)((a.S + 3) / 4)), dim3(64), 0, st, key, a.P, a.S, a.gen_version,
+                     static_cast<u32x4*>(frag), static_cast<SeedInfo*>(info), a.scored, candidates);
+  return hipGetLastError();
+}
+
+template <bool POW2, bool FULLP>
+static void run_c16(const EncodeArgs& a, const ModEntry& one, const ModEntry* mods, int n_mods, int64_t items,
+                    const u32x4* fr, const SeedInfo* mk, hipStream_t st) {
   const dim3 grid((unsigned)items), blk(64);
+  if (a.d_mode == AWSRC_D_PER_ELEM)
+    hipLaunchKernelGGL((k_encode_c16<POW2, FULLP, true>), grid, blk, 0, st, a, one, mods, n_mods, fr, mk);
+  else
+    hipLaunchKernelGGL((k_encode_c16<POW2, FULLP, false>), grid, blk, 0, st, a, one, mods, n_mods, fr, mk);
+}
+
+hipError_t launch_encode_c16(const EncodeArgs& a, const ModEntry& one, const ModEntry* mods, int n_mods, int64_t items,
+                             int64_t blocks, const void* frag, const void* info, hipStream_t st) {
+  const u32x4* fr = static_cast<const u32x4*>(frag);
+  const SeedInfo* mk = static_cast<const SeedInfo*>(info);
+  if (a.d_mode != AWSRC_D_PER_ELEM)
+    hipLaunchKernelGGL(k_c16_factors, dim3((unsigned)((blocks * a.S + 255) / 256)), dim3(256), 0, st, a, one, mods, n_mods,
+                       mk, blocks);
   if (a.scale_fmt == AWSRC_SCALE_POW2) {
-    if (a.P == kPB) hipLaunchKernelGGL((k_encode_c16<true, true>), grid, blk, 0, st, a, one, mods, n_mods, fr, mk);
-    else hipLaunchKernelGGL((k_encode_c16<true, false>), grid, blk, 0, st, a, one, mods, n_mods, fr, mk);
+    if (a.P == kPB) run_c16<true, true>(a, one, mods, n_mods, items, fr, mk, st);
+    else run_c16<true, false>(a, one, mods, n_mods, items, fr, mk, st);
   } else {
-    if (a.P == kPB) hipLaunchKernelGGL((k_encode_c16<false, true>), grid, blk, 0, st, a, one, mods, n_mods, fr, mk);
-    else hipLaunchKernelGGL((k_encode_c16<false, false>), grid, blk, 0, st, a, one, mods, n_mods, fr, mk);
+    if (a.P == kPB) run_c16<false, true>(a, one, mods, n_mods, items, fr, mk, st);
+    else run_c16<false, false>(a, one, mods, n_mods, items, fr, mk, st);
   }
   return hipGetLastError();
 }

@@ -275,6 +275,126 @@ def test_encode_c16(P, b, S, d_mode, gen, fmt, name):
         off += T
 
 
+def _f32_chain_scores(R, D, op, d_mode):
+    """Screen scores [T, S] of the stated fp32 chain, every operation rounded to
+    fp32 (multiply-adds once): projections summed in coordinate order, the factor
+    L diag(e) L^T from 64-bit sums stored in fp32 (per column) or from Gram
+    entries summed pairwise in fp32 (per element), fit, codes, score."""
+    f, T, C, P = np.float32, R.shape[0], R.shape[1], op.P
+    u = (D.astype(f) * R.astype(f)).astype(f)
+    out = np.empty((T, op.S))
+    for s in range(op.S):
+        B = np.sign(O.basis_matrix(op.basis_key, s, C, P, op.gen_version))
+
+        def r32(x):
+            return x.astype(f).astype(np.float64)
+
+        def dots(x, pairwise):  # sums of +-x over the coordinates, in fp32
+            if pairwise:
+                while x.shape[1] > 1:
+                    x = (x[:, 0::2] + x[:, 1::2]).astype(f)
+                return x[:, 0].astype(np.float64)
+            acc = np.zeros(T, f)
+            for j in range(C):
+                acc = (acc + x[:, j]).astype(f)
+            return acc.astype(np.float64)
+
+        rnd = (lambda x: x) if d_mode == "col" else r32
+        G = {(p, q): (D.astype(np.float64) @ (B[:, p] * B[:, q]) if d_mode == "col"
+                      else dots(D.astype(f) * (B[:, p] * B[:, q]).astype(f), True)) / C
+             for p in range(P) for q in range(p + 1)}
+        eps = rnd(op.ridge_lambda * G[0, 0])
+        L, e = {}, []
+        for p in range(P):
+            for q in range(p):
+                t = G[p, q]
+                for k in range(q):
+                    t = rnd(t - L[p, k] * rnd(L[q, k] * e[k]))
+                L[p, q] = rnd(t / e[q])
+            t = rnd(G[p, p] + eps)
+            for k in range(p):
+                t = rnd(t - L[p, k] * rnd(L[p, k] * e[k]))
+            e.append(np.maximum(t, 1e-30))
+        L, inv, e = {k: r32(v) for k, v in L.items()}, [r32(1 / v) for v in e], [r32(v) for v in e]
+        w, al = [], [None] * P
+        for p in range(P):
+            t = r32(dots(u * B[:, p].astype(f), False) / np.sqrt(C))
+            for k in range(p):
+                t = r32(t - L[p, k] * w[k])
+            w.append(t)
+        for p in reversed(range(P)):
+            t = r32(w[p] * inv[p])
+            for k in range(p + 1, P):
+                t = r32(t - L[k, p] * al[k])
+            al[p] = t
+        q, _, sc = O.quantize(np.stack(al, 1), op.b, op.scale_fmt)
+        t1, quad = np.zeros(T), np.zeros(T)
+        for k in range(P):
+            y = q[:, k].astype(np.float64)
+            for i in range(k + 1, P):
+                y = r32(y + L[i, k] * q[:, i])
+            t1, quad = r32(t1 + y * w[k]), r32(quad + r32(e[k] * y) * y)
+        out[:, s] = r32(sc * r32(2 * t1 - r32(sc * quad)))
+    return out
+
+
+@pytest.mark.parametrize("ratio", [1e4, 1e5, 1e6])
+@pytest.mark.parametrize("d_mode,gen,fmt", [("col", 1, 0), ("col", 2, 0), ("col", 1, 1), ("elem", 1, 0), ("elem", 2, 1)])
+def test_encode_c16_outlier_channels(d_mode, gen, fmt, ratio):
+    """C = 16, P = 4 where one channel of every tile dominates d: the Gram matrix
+    is nearly singular and any fp32 screen loses some tiles' best seed.  It may
+    lose no more of them than the fp32 chain above does on the same tiles (plus
+    three standard deviations of that count: which ones are lost depends on the
+    order of the sums)."""
+    wl = workload("block3b", C=16, P=4, b=4, S=16, d_mode=d_mode)
+    rows, cols = 256, 512
+    inp = gen_module_inputs(wl, Module("t", rows, cols, 0, 7, 7), DEV)
+    at = torch.arange(0, cols, 16, device=DEV) + torch.arange(cols // 16, device=DEV) * 5 % 16
+    d = inp["d"].clone()
+    d[..., at] *= ratio
+    W0 = awsrc.awsrc_backbone_rtn(inp["W"])[3]
+    enc = awsrc.awsrc_encode_tiles(_params(wl, fmt, gen), inp["W"], W0, d)
+    op = _oparams(wl, fmt, gen)
+    R = O.tiles(O.residual(inp["W32"].cpu().numpy(), W0.cpu().numpy()), 16)
+    D = O.tile_weights(d.cpu().numpy(), rows, cols, 16)
+    gains = O.encode_tiles(R, D, op, keep_all=True)["all_gains"]
+    best, E, T = gains.max(1), (D.astype(np.float64) * R.astype(np.float64) ** 2).sum(1), np.arange(R.shape[0])
+
+    def lost(seed):
+        return int((best - gains[T, seed] > 1e-6 * np.abs(best) + 1e-13 * E).sum())
+
+    s32 = _f32_chain_scores(R, D, op, d_mode)
+    two = np.argsort(-s32, axis=1, kind="stable")[:, :2]
+    a, b = s32[T, two[:, 0]], s32[T, two[:, 1]]
+    second = (b >= a - (1e-4 * np.abs(a) + 1e-7 * E)) & (gains[T, two[:, 1]] > gains[T, two[:, 0]])
+    chain, got = lost(np.where(second, two[:, 1], two[:, 0])), lost(_u16(enc["seed"]).astype(np.int64))
+    assert got <= chain + 3 * np.sqrt(chain) + 3, (got, chain)
+
+
+def test_encode_c16_factor_groups():
+    """Per-column weights over more column blocks and seeds than one factor table
+    holds (64 MiB, two of these modules): the modules of a call run in groups,
+    an empty one among them, with the results of one call per module."""
+    p = awsrc.make_params(16, 4, 4, 65536)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    shapes = [(9, 128), (0, 128), (1, 128), (33, 128), (2, 256)]
+    Ws = [0.02 * torch.randn(r, c, generator=g, device=DEV) for r, c in shapes]
+    W0s = [awsrc.awsrc_backbone_rtn(W)[3] if W.shape[0] else torch.empty_like(W) for W in Ws]
+    ds = [torch.exp(torch.randn(c, generator=g, device=DEV)) for _, c in shapes]
+    n = awsrc.encode_modules_workspace_bytes(p, shapes, awsrc.AWSRC_DTYPE_F32, awsrc.AWSRC_D_PER_COL)
+    assert n < 160 << 20
+    ws = torch.full((n,), 0xFF, dtype=torch.uint8, device=DEV)
+    got = awsrc.awsrc_encode_modules(p, Ws, W0s, ds, want_alpha=True, workspace=ws)
+    off = 0
+    for (r, c), W, W0, d in zip(shapes, Ws, W0s, ds):
+        T = r * c // 16
+        if T:
+            ref = awsrc.awsrc_encode_tiles(p, W, W0, d, want_alpha=True)
+            for k in ("seed", "codes", "scale", "gain", "alpha"):
+                assert torch.equal(got[k][off:off + T], ref[k]), (r, c, k)
+        off += T
+
+
 @pytest.mark.parametrize("P,b,S,fmt,name", [(8, 4, 40, 0, "block3b"), (8, 4, 2, 1, "linear256"), (5, 3, 7, 0, "block3b"),
                                             (1, 4, 9, 0, "linear256"), (4, 5, 64, 1, "block3b")])
 def test_encode_perm_modules(P, b, S, fmt, name):
