@@ -225,7 +225,7 @@ size_t module_ws_bytes(const awsrc_params* p, int64_t rows, int64_t cols, int32_
   const size_t b_tg = align_up((size_t)T * nsplit * kTop * 4, 256);
   const size_t b_ts = align_up((size_t)T * nsplit * kTop * 4, 256);
   const size_t b_white =
-      white_supported(p->C, p->P, p->S, d_mode, p->gen_version, rows, cols) ? align_up(white_bytes(p->C, p->S, cols), 256) : 0;
+      white_supported(p->C, p->P, p->S, d_mode, p->gen_version, rows, cols) ? align_up(white_bytes(p->S, cols), 256) : 0;
   *white = b_white;
   return 256 + b_basis + b_fac + b_wd + b_frag + b_tg + b_ts + b_white + 256;
 }
@@ -689,7 +689,7 @@ extern "C" awsrc_status awsrc_encode_tiles_noalloc(const awsrc_params* p, const 
                                        gain_out, alpha_or_null, nullptr, &need, stream);
   if (st) return st;
   if (white_supported(p->C, p->P, p->S, d_mode, p->gen_version, rows, cols))
-    need -= align_up(white_bytes(p->C, p->S, cols), 256);  // not needed (module_ws_bytes)
+    need -= align_up(white_bytes(p->S, cols), 256);  // not needed (module_ws_bytes)
   if (need > kNoallocScratchBytes)
     return fail(AWSRC_ENOSPC, "module needs %zu bytes of scratch, more than the %zu-byte static array", need,
                 kNoallocScratchBytes);

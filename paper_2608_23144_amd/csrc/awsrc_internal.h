@@ -407,7 +407,7 @@ hipError_t launch_perm_screen(const EncodeArgs& a, const ModEntry& one, const Mo
                               int64_t items2, hipStream_t st);
 // The screen with a whitened basis (encode_white.hip) and its table's size.
 bool white_supported(int C, int P, int S, int d_mode, int gen_version, int64_t rows, int64_t cols);
-size_t white_bytes(int C, int S, int64_t cols);
+size_t white_bytes(int S, int64_t cols);
 hipError_t launch_white_screen(const EncodeArgs& a, void* ws, hipStream_t st);
 hipError_t launch_encode_screen_mfma(const EncodeArgs& a, void* frag, hipStream_t st);
 hipError_t launch_col_factors(const EncodeArgs& a, hipStream_t st);

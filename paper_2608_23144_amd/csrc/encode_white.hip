@@ -51,8 +51,10 @@ namespace {
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
 
-constexpr int kWhitePB = 8;
+constexpr int kC = 128;
+constexpr int kPB = 8;
 constexpr int kWhiteTiles = 64;  // tiles per workgroup
+constexpr float kRootC = 0.08838834764831845f;  // 1/sqrt(C)
 
 // Bound on the error of |M~ v~| (M and v rounded to fp16) relative to |v|:
 // |M - M~|_F <= 2^-11 sqrt(8), |M|_2 <= 1 and |v - v~| <= 2^-11 |v| give
@@ -79,9 +81,8 @@ __device__ __forceinline__ void wave_sync() {
 // 32 ks + 8 (lane / 16) + e; rows of absent seeds and columns are zero.  One
 // thread per (seed, ks, lane / 16).  A negative or non-finite weight makes its
 // entries NaN, and a candidate whose bound is NaN is scored.
-template <int C>
 __global__ __launch_bounds__(256) void k_whiten(EncodeArgs a, int stride, int blk0, u32x4* __restrict__ white) {
-  constexpr int PB = kWhitePB, NKS = C / 32, LS = PB * (PB - 1) / 2;
+  constexpr int C = kC, PB = kPB, NKS = C / 32, LS = PB * (PB - 1) / 2;
   constexpr int TPS = NKS * 4;  // threads per seed
   const int n_pairs = (a.S + 1) / 2;
   const int i = blockIdx.x * 256 + threadIdx.x;
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(256) void k_whiten(EncodeArgs a, int stride, int bl
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int e = 2 * e2 + h;
-      const float sd = __builtin_amdgcn_sqrtf(dp[e]) * (C == 64 ? 0.125f : 0.08838834764831845f);
+      const float sd = __builtin_amdgcn_sqrtf(dp[e]) * kRootC;
       float w[PB];
 #pragma unroll
       for (int p = 0; p < PB; ++p) {
@@ -135,10 +136,10 @@ __global__ __launch_bounds__(256) void k_whiten(EncodeArgs a, int stride, int bl
 }
 
 // two wavefronts per SIMD: at most 256 VGPRs, and the LDS allows four workgroups per CU
-template <int C, bool POW2>
+template <bool POW2>
 __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32x4* __restrict__ white, int stride,
                                                          int blk0) {
-  constexpr int PB = kWhitePB, NKS = C / 32, NT = kWhiteTiles;
+  constexpr int C = kC, PB = kPB, NKS = C / 32, NT = kWhiteTiles;
   constexpr int LS = PB * (PB - 1) / 2, NF = LS + 2 * PB;
   constexpr int QC = 256;  // queue slots of a wavefront: at most 63 entries wait before a step of 128 candidates
   __shared__ __attribute__((aligned(16))) float lu[C * NT];  // u, [coordinate][tile]
@@ -227,7 +228,6 @@ __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32
   const bool my_valid = row0 + lane < a.rows;
   const float qmax = (float)((1 << (a.b - 1)) - 1);
   const float inv_qmax = 1.0f / qmax;
-  constexpr float isq = C == 64 ? 0.125f : 0.08838834764831845f;  // 1/sqrt(C)
   float tg0 = -INFINITY, tg1 = -INFINITY;
   uint32_t ts0 = 0, ts1 = 0;  // seed words: seed | kEdge flag
   s_best[wv][lane] = (uint64_t)__float_as_uint(-INFINITY);
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
-      for (int p = 0; p < PB; ++p) bs[p] = p < P ? b[p] * isq : 0.0f;
+      for (int p = 0; p < PB; ++p) bs[p] = p < P ? b[p] * kRootC : 0.0f;
       score();
     }
     // A candidate on a knife edge (a few in a thousand) is scored again from
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32
 #pragma unroll
         for (int p = 0; p < PB; ++p) {
           const float v = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(c[p & 3]), 16 * (p >> 2)));
-          bs[p] = lane == l ? v * isq : bs[p];
+          bs[p] = lane == l ? v * kRootC : bs[p];
         }
       }
       if ((edges >> lane) & 1) score();
@@ -507,40 +507,38 @@ constexpr size_t kWhiteBytes = (size_t)128 << 20;
 // S = 512 229 -> 250; 512 x 11008 S = 1024 373 -> 407; 512 x 27648 S = 1024
 // 809 -> 993.  So: 256 seeds, 1024 rows and 2^25 candidates.
 bool white_supported(int C, int P, int S, int d_mode, int gen_version, int64_t rows, int64_t cols) {
-  return C == 128 && P <= kWhitePB && d_mode == AWSRC_D_PER_COL && gen_version == 1 && S >= 256 && rows >= 1024 &&
+  return C == kC && P <= kPB && d_mode == AWSRC_D_PER_COL && gen_version == 1 && S >= 256 && rows >= 1024 &&
          rows * (cols / C) * S >= ((int64_t)1 << 25);
 }
 
-static size_t white_block_bytes(int C, int S) { return (size_t)((S + 1) / 2) * (C / 32) * 64 * 16; }
+static size_t white_block_bytes(int S) { return (size_t)((S + 1) / 2) * (kC / 32) * 64 * 16; }
 
-static int64_t white_blocks(int C, int S, int64_t nb) {
-  int64_t n = (int64_t)(kWhiteBytes / white_block_bytes(C, S));
+static int64_t white_blocks(int S, int64_t nb) {
+  int64_t n = (int64_t)(kWhiteBytes / white_block_bytes(S));
   if (n < 1) n = 1;
   return n < nb ? n : nb;
 }
 
-size_t white_bytes(int C, int S, int64_t cols) {
-  return (size_t)white_blocks(C, S, cols / C) * white_block_bytes(C, S);
-}
+size_t white_bytes(int S, int64_t cols) { return (size_t)white_blocks(S, cols / kC) * white_block_bytes(S); }
 
-template <int C, bool POW2>
+template <bool POW2>
 static hipError_t run_white(const EncodeArgs& a, void* ws, hipStream_t st) {
-  const int64_t nb = a.cols / C, step = white_blocks(C, a.S, nb);
+  const int64_t nb = a.cols / kC, step = white_blocks(a.S, nb);
   u32x4* white = static_cast<u32x4*>(ws);
   const int64_t nrg = (a.rows + kWhiteTiles - 1) / kWhiteTiles;
-  const int threads = 2 * ((a.S + 1) / 2) * (C / 32) * 4;
+  const int threads = 2 * ((a.S + 1) / 2) * (kC / 32) * 4;
   for (int64_t b0 = 0; b0 < nb; b0 += step) {
     const int64_t n = nb - b0 < step ? nb - b0 : step;
-    hipLaunchKernelGGL((k_whiten<C>), dim3((unsigned)((threads + 255) / 256), (unsigned)n), dim3(256), 0, st, a,
-                       colfac_stride(kWhitePB), (int)b0, white);
-    hipLaunchKernelGGL((k_screen_white<C, POW2>), dim3((unsigned)(n * nrg * a.nsplit)), dim3(128), 0, st, a, white,
-                       colfac_stride(kWhitePB), (int)b0);
+    hipLaunchKernelGGL(k_whiten, dim3((unsigned)((threads + 255) / 256), (unsigned)n), dim3(256), 0, st, a,
+                       colfac_stride(kPB), (int)b0, white);
+    hipLaunchKernelGGL((k_screen_white<POW2>), dim3((unsigned)(n * nrg * a.nsplit)), dim3(128), 0, st, a, white,
+                       colfac_stride(kPB), (int)b0);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_white_screen(const EncodeArgs& a, void* ws, hipStream_t st) {
-  return a.scale_fmt == AWSRC_SCALE_POW2 ? run_white<128, true>(a, ws, st) : run_white<128, false>(a, ws, st);
+  return a.scale_fmt == AWSRC_SCALE_POW2 ? run_white<true>(a, ws, st) : run_white<false>(a, ws, st);
 }
 
 }  // namespace awsrc
