@@ -715,7 +715,8 @@ static hipError_t run_screen(const EncodeArgs& a, hipStream_t st) {
   const int nb = (int)(a.cols / C);
   const int64_t waves = nb * ((a.rows + 63) / 64);
   if (a.d_mode == AWSRC_D_PER_ELEM && a.gen_version != 1) {
-    if constexpr (C != 64 || PB > 8)  // C = 64, P <= 8: encode_perm.hip
+    if constexpr (C == 64 && PB <= 8) return hipErrorNotSupported;  // encode_perm.hip's shapes: no lists are written here
+    else
       hipLaunchKernelGGL((k_screen_valu<C, PB, true, true>), dim3((unsigned)waves), dim3(64), 0, st, a,
                          colfac_stride(PB));
   } else if (a.d_mode == AWSRC_D_PER_ELEM)
