@@ -56,13 +56,20 @@ constexpr int kPB = 8;
 constexpr int kWhiteTiles = 64;  // tiles per workgroup
 constexpr float kRootC = 0.08838834764831845f;  // 1/sqrt(C)
 
-// Bound on the error of |M~ v~| (M and v rounded to fp16) relative to |v|:
+// Bound on the error of |M~ v~| (M and v rounded to fp16) relative to |v|, for
+// the M of the factor as stored in fp32, the one that the scores use:
 // |M - M~|_F <= 2^-11 sqrt(8), |M|_2 <= 1 and |v - v~| <= 2^-11 |v| give
-// 2^-11 (sqrt(8) + 1) = 1.87e-3; the rest covers the fp32 sums (2e-5) and the
-// entries of M below fp16's normal range (1e-6).
+// 2^-11 (sqrt(8) + 1) = 1.87e-3; the rest covers the fp32 sums of a product
+// (2e-5), the entries of M below fp16's normal range (1e-6) and the forward
+// substitution.  Each of that one's at most seven steps a row rounds vectors no
+// longer than sqrt(G_pp), and a pivot e_p brings them to the scale of M: in fp32
+// 7 sqrt(8) 2^-24 sqrt(G_pp / e_p), 4e-5 at a ratio of kWhiteIll (measured: 4e-6
+// there, 1.6e-4 at 2^20, always 1.5e-7 times the root).  Above it, where a few
+// channels carry most of a block's weight, the substitution runs in fp64.
 constexpr float kWhiteSlack = 2.0e-3f;
+constexpr float kWhiteIll = 1024.0f;
 
-// The power of two that brings a vector of squared norm e to [2^10, 2^11).
+// The power of two that brings a vector of squared norm e to [2^9.5, 2^10.5).
 __device__ __forceinline__ float vscale(float e) {
   const int x = (int)((__float_as_uint(e) >> 23) & 0xFFu);
   return __uint_as_float((uint32_t)(127 + ((147 - x) >> 1)) << 23);
@@ -76,11 +83,41 @@ __device__ __forceinline__ void wave_sync() {
 
 }  // namespace
 
+// Rows of M at eight coordinates with weights d8: fragments o[p], by forward
+// substitution in T.  neg[p]: their signs in column p; f: L packed by rows, then
+// diag(e)^-1/2.
+template <typename T>
+__device__ __forceinline__ void whiten8(const float (&d8)[8], const uint32_t (&neg)[kPB], int P,
+                                        const float (&f)[kPB * (kPB - 1) / 2 + kPB], u32x4 (&o)[kPB]) {
+  constexpr int PB = kPB, LS = PB * (PB - 1) / 2;
+#pragma unroll
+  for (int e2 = 0; e2 < 4; ++e2) {
+    uint32_t hb[2][PB];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int e = 2 * e2 + h;
+      const T sd = __builtin_amdgcn_sqrtf(d8[e]) * kRootC;
+      T w[PB];
+#pragma unroll
+      for (int p = 0; p < PB; ++p) {
+        T t = p < P ? (((neg[p] >> e) & 1u) ? -sd : sd) : (T)0;
+#pragma unroll
+        for (int k = 0; k < p; ++k) t = __builtin_elementwise_fma(-(T)f[ltri(p, k)], w[k], t);
+        w[p] = t;
+        hb[h][p] = (uint32_t)__half_as_ushort(__float2half_rn((float)(t * (T)f[LS + p])));
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < PB; ++p) o[p][e2] = hb[0][p] | (hb[1][p] << 16);
+  }
+}
+
 // M of column blocks blk0 .. as fragments white[block][pair][ks][lane]: eight
 // fp16 of row m = lane % 16 (seed 2 pair + m / 8, column m % 8) at coordinates
 // 32 ks + 8 (lane / 16) + e; rows of absent seeds and columns are zero.  One
-// thread per (seed, ks, lane / 16).  A negative or non-finite weight makes its
-// entries NaN, and a candidate whose bound is NaN is scored.
+// thread per (seed, ks, lane / 16).  A negative weight makes its entries NaN,
+// and a candidate whose bound is NaN is scored; a block without any weight
+// (1/e infinite) has M = 0.
 __global__ __launch_bounds__(256) void k_whiten(EncodeArgs a, int stride, int blk0, u32x4* __restrict__ white) {
   constexpr int C = kC, PB = kPB, NKS = C / 32, LS = PB * (PB - 1) / 2;
   constexpr int TPS = NKS * 4;  // threads per seed
@@ -102,40 +139,31 @@ __global__ __launch_bounds__(256) void k_whiten(EncodeArgs a, int stride, int bl
     const f32x4 v = *reinterpret_cast<const f32x4*>(fs + 4 * k);
     f[4 * k] = v[0]; f[4 * k + 1] = v[1]; f[4 * k + 2] = v[2]; f[4 * k + 3] = v[3];
   }
+  float most = f[LS];  // the largest 1 / e
 #pragma unroll
-  for (int p = 0; p < PB; ++p) f[LS + p] = __builtin_amdgcn_sqrtf(f[LS + p]);
+  for (int p = 1; p < PB; ++p) most = p < a.P ? fmaxf(most, f[LS + p]) : most;
+  const bool ill = most > kWhiteIll * f[LS];
+#pragma unroll
+  for (int p = 0; p < PB; ++p) f[LS + p] = f[LS + p] < INFINITY ? __builtin_amdgcn_sqrtf(f[LS + p]) : 0.0f;
   const int j0 = 32 * ks + 8 * g;
   uint32_t neg[PB];
 #pragma unroll
   for (int p = 0; p < PB; ++p)
     neg[p] = p < a.P ? (uint32_t)(a.basis.mask[((size_t)s * a.P + p) * 2 + (j0 >> 6)] >> (j0 & 63)) & 0xFFu : 0u;
   const float* dp = a.d + (int64_t)blk * C + j0;
+  float d8[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) d8[e] = dp[e];
   u32x4 o[PB];
-#pragma unroll
-  for (int e2 = 0; e2 < 4; ++e2) {
-    uint32_t hb[2][PB];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int e = 2 * e2 + h;
-      const float sd = __builtin_amdgcn_sqrtf(dp[e]) * kRootC;
-      float w[PB];
-#pragma unroll
-      for (int p = 0; p < PB; ++p) {
-        float t = p < a.P ? (((neg[p] >> e) & 1u) ? -sd : sd) : 0.0f;
-#pragma unroll
-        for (int k = 0; k < p; ++k) t = fmaf(-f[ltri(p, k)], w[k], t);
-        w[p] = t;
-        hb[h][p] = (uint32_t)__half_as_ushort(__float2half_rn(t * f[LS + p]));
-      }
-    }
-#pragma unroll
-    for (int p = 0; p < PB; ++p) o[p][e2] = hb[0][p] | (hb[1][p] << 16);
-  }
+  if (ill) whiten8<double>(d8, neg, a.P, f, o);
+  else whiten8<float>(d8, neg, a.P, f, o);
 #pragma unroll
   for (int p = 0; p < PB; ++p) out[p] = o[p];
 }
 
 // two wavefronts per SIMD: at most 256 VGPRs, and the LDS allows four workgroups per CU
+// (one 64-bit value waits in scratch memory from before the loop over the seeds
+// until after it)
 template <bool POW2>
 __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32x4* __restrict__ white, int stride,
                                                          int blk0) {
@@ -170,10 +198,11 @@ __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32
   const int n = lane & 15, g = lane >> 4;
 
   // v fragments (coordinates 32 ks + 8 g .. + 7 of tiles 16 nb + n), scaled
-  // per tile by a power of two so that |v| lies in [2^10, 2^11), and u to LDS
+  // per tile by a power of two so that |v| lies in [2^9.5, 2^10.5), and u to LDS
   // (each wavefront stores half of the tiles)
   u32x4 vf[4][NKS];
   float en[4];
+  uint32_t finite = 0;  // bit nb: tile 16 nb + n has no infinite or NaN u
 #pragma unroll
   for (int nb = 0; nb < 4; ++nb) {
     const int64_t row = row0 + 16 * nb + n;
@@ -188,7 +217,7 @@ __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32
     }
     float rv[2 * NKS][4];
     load_residual4<2 * NKS>(a.W, a.w_dtype, a.W0, o, rv);
-    float e = 0.0f;
+    float e = 0.0f, z = 0.0f;
 #pragma unroll
     for (int q = 0; q < 2 * NKS; ++q)
 #pragma unroll
@@ -197,10 +226,14 @@ __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32
         const float u = valid ? dv[q][k] * r : 0.0f;
         rv[q][k] = r;
         e = fmaf(u, r, e);
+        z = fmaf(u, 0.0f, z);
         if (wv == (nb >> 1)) lu[(32 * (q >> 1) + 8 * g + 4 * (q & 1) + k) * NT + 16 * nb + n] = u;
       }
     e += __shfl_xor(e, 16, 64);
     e += __shfl_xor(e, 32, 64);
+    z += __shfl_xor(z, 16, 64);
+    z += __shfl_xor(z, 32, 64);
+    finite |= (uint32_t)(z == 0.0f) << nb;
     en[nb] = e;
     const float sc = vscale(e);
 #pragma unroll
@@ -226,6 +259,8 @@ __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32
   const float vsc = vscale(energy);
   const float slack_v = kWhiteSlack * sqrtf(energy);
   const bool my_valid = row0 + lane < a.rows;
+  // no score of a tile with an infinite or NaN u is a number: it keeps the empty list
+  const bool my_screened = my_valid && ((finite >> g) & 1u);
   const float qmax = (float)((1 << (a.b - 1)) - 1);
   const float inv_qmax = 1.0f / qmax;
   float tg0 = -INFINITY, tg1 = -INFINITY;
@@ -238,7 +273,8 @@ __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32
   const int sh = g >> 1, nb0 = 2 * (g & 1);
   const uint32_t tile0 = 16 * nb0 + n;
   // rows past the end are never kept
-  float thr2[2] = {row0 + tile0 < a.rows ? -1.0f : INFINITY, row0 + tile0 + 16 < a.rows ? -1.0f : INFINITY};
+  float thr2[2] = {row0 + tile0 < a.rows && ((finite >> nb0) & 1u) ? -1.0f : INFINITY,
+                   row0 + tile0 + 16 < a.rows && ((finite >> nb0) & 2u) ? -1.0f : INFINITY};
   int qhead = 0, qtail = 0;  // wavefront-uniform queue counters
   unsigned long long nscored = 0;
   const int P = a.P;
@@ -389,8 +425,9 @@ __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32
     const float best = fmaxf(tg0, og);
     const bool bedge = (tg0 >= og ? (ts0 & kEdge) : (uint32_t)(ob >> 32)) != 0;
     const float thr = slack_thr(best - 1.01f * rescore_window(best, energy, bedge));
-    const float x = thr >= 0.0f ? sqrtf(thr) - slack_v : -1.0f;
-    s_thr[wv][lane] = !my_valid ? INFINITY : x >= 0.0f ? (x * vsc) * (x * vsc) : -1.0f;
+    // (a tile without energy has nothing to gain, also where d = 0 makes its scores NaN)
+    const float x = energy == 0.0f ? 0.0f : thr >= 0.0f ? sqrtf(thr) - slack_v : -1.0f;
+    s_thr[wv][lane] = !my_screened ? INFINITY : x >= 0.0f ? (x * vsc) * (x * vsc) : -1.0f;
     wave_sync();
     thr2[0] = s_thr[wv][tile0];
     thr2[1] = s_thr[wv][tile0 + 16];

@@ -180,6 +180,44 @@ def test_encode_whitened_matches_rows():
             assert torch.equal(part[k], enc[k][r0 * nb:(r0 + 512) * nb]), k
 
 
+def test_encode_whitened_outlier_and_dead_blocks():
+    """The whitened screen against the former one (the fixed-scratch entry point)
+    where d is far from uniform: channels 1e4 and 1e3 times the others (pivots
+    small enough for the fp64 substitution), a block that is zero, one that is
+    half zero, and tiles of infinite or NaN weights.  The records are the same,
+    but for the outlier blocks, whose fp32 scores are uncertain in either screen
+    (their gains are the same in sum to 1e-4); dead blocks and tiles are not
+    scored over and over."""
+    wl = workload("block3b", C=128, P=8, b=3, S=1024, d_mode="col")
+    m = Module("t", 1024, 8448, 0, 8, 8)
+    inp = gen_module_inputs(wl, m, DEV)
+    W0 = awsrc.awsrc_backbone_rtn(inp["W"])[3]
+    W, d, p = inp["W"].clone(), inp["d"].clone(), _params(wl)
+    d[128 + 17] *= 1e4
+    d[[256 + 3, 256 + 64, 256 + 101]] *= 1e3
+    outlier = awsrc.awsrc_encode_scored(awsrc.awsrc_encode_tiles(p, W, W0, d))
+    d[384:512] = 0
+    d[512:576] = 0
+    for r in (0, 63, 64, 500, 1023):
+        W[r, 5::128] = (float("nan"), float("inf"), -float("inf"))[r % 3]
+    got = awsrc.awsrc_encode_tiles(p, W, W0, d)
+    scored = awsrc.awsrc_encode_scored(got)
+    assert scored <= outlier + 1e-3 * 1024 * 66 * 1024, (scored, outlier)
+    ref = awsrc.awsrc_encode_tiles_noalloc(p, W, W0, d, out={k: torch.empty_like(got[k])
+                                                            for k in ("seed", "codes", "scale", "gain")})
+    g, f = (e["gain"].view(1024, 66) for e in (got, ref))
+    same = torch.ones(66, dtype=torch.bool)
+    same[1:3] = False
+    for k in ("seed", "codes", "scale"):
+        a, b = (e[k].view(1024, 66, -1)[:, same.to(DEV)] for e in (got, ref))
+        assert torch.equal(a, b), k
+    assert torch.equal(g[:, same.to(DEV)].nan_to_num(nan=-1), f[:, same.to(DEV)].nan_to_num(nan=-1))
+    ok = torch.isfinite(f).all(1)
+    assert int(ok.sum()) == 1024 - 5
+    for blk in (1, 2):
+        assert float(g[ok, blk].sum()) >= float(f[ok, blk].sum()) * (1 - 1e-4)
+
+
 @pytest.mark.parametrize("P,S,rows,cols,d_mode", [(8, 48, 70, 256, "col"), (3, 30, 64, 128, "col"),
                                                    (5, 62, 129, 256, "col"), (8, 40, 67, 256, "elem"),
                                                    (4, 256, 64, 128, "elem")])
