@@ -112,6 +112,31 @@ __host__ __device__ __forceinline__ float rescore_window(float g, float e, bool 
 // than to every candidate's bound.
 __device__ __forceinline__ float slack_thr(float thr) { return thr - fabsf(thr) * 0x1p-9f; }
 
+// Whether the whitened screen (encode_white.hip) takes a column block of C = 128
+// weights d; the other blocks run screen_halves (screen_halves.h).  Where a few
+// channels carry the block, every seed fits them and the bounds of a tile lie
+// close together: a large part of the candidates is scored, in rounds that cost
+// the whitened screen three times as much, up to 5 ms for one workgroup.
+// Measured over 2048 x 5120, S = 1024 (that screen | the whitened one, us): even
+// weights 698 | 439; one channel with a share of 0.7 667 | 505, 0.9 720 | 818,
+// 0.95 757 | 1659, 0.99 1177 | 5220; four with 0.9 673 | 638, 0.95 735 | 1009;
+// eight with 0.95 669 | 610, 0.99 774 | 1276; log-normal of sigma 2.5 683 | 645,
+// 3 749 | 1771.  In all of these the two meet where (sum sqrt(d))^2 is about 22
+// times sum d (128 for even weights, 24 and more in most blocks of sigma 2.5).
+// NaN, infinite, negative and all-zero weights are left to the other screen too.
+constexpr float kWhiteSpread = 22.0f;
+__device__ __forceinline__ bool white_takes(const float* d128) {
+  const int lane = threadIdx.x & 63;
+  const float2 v = reinterpret_cast<const float2*>(d128)[lane];
+  float s = v.x + v.y, q = sqrtf(v.x) + sqrtf(v.y);
+#pragma unroll
+  for (int k = 32; k >= 1; k >>= 1) {
+    s += __shfl_xor(s, k, 64);
+    q += __shfl_xor(q, k, 64);
+  }
+  return q * q > kWhiteSpread * s;  // the same in every lane
+}
+
 __device__ __forceinline__ bool code_edge(float x, float qmax) {
   const float ax = fabsf(x);
   return ax < qmax && 0.5f - fabsf(x - rintf(x)) < 1e-4f + 2e-5f * ax;

@@ -18,7 +18,9 @@
 // lists are those of scoring every candidate, in the best and in the second
 // wherever the second lies inside the re-score's window.  (How many candidates
 // are scored depends a little on the two wavefronts' timing, what is kept does
-// not.)
+// not.)  Column blocks in which a few channels carry most of the weight, and
+// those whose weights are not positive numbers, run the other C = 128 screen
+// in this kernel (white_takes).
 //
 // One workgroup = two wavefronts = 64 consecutive rows of one column block.
 // Both wavefronts hold v of all 64 tiles (64 VGPRs) and take alternate seed
@@ -43,6 +45,7 @@
 #include "awsrc_internal.h"
 #include "mfma_bf16.h"
 #include "rescore64.h"
+#include "screen_halves.h"
 
 namespace awsrc {
 
@@ -115,9 +118,7 @@ __device__ __forceinline__ void whiten8(const float (&d8)[8], const uint32_t (&n
 // M of column blocks blk0 .. as fragments white[block][pair][ks][lane]: eight
 // fp16 of row m = lane % 16 (seed 2 pair + m / 8, column m % 8) at coordinates
 // 32 ks + 8 (lane / 16) + e; rows of absent seeds and columns are zero.  One
-// thread per (seed, ks, lane / 16).  A negative weight makes its entries NaN,
-// and a candidate whose bound is NaN is scored; a block without any weight
-// (1/e infinite) has M = 0.
+// thread per (seed, ks, lane / 16).
 __global__ __launch_bounds__(256) void k_whiten(EncodeArgs a, int stride, int blk0, u32x4* __restrict__ white) {
   constexpr int C = kC, PB = kPB, NKS = C / 32, LS = PB * (PB - 1) / 2;
   constexpr int TPS = NKS * 4;  // threads per seed
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(256) void k_whiten(EncodeArgs a, int stride, int bl
   for (int p = 1; p < PB; ++p) most = p < a.P ? fmaxf(most, f[LS + p]) : most;
   const bool ill = most > kWhiteIll * f[LS];
 #pragma unroll
-  for (int p = 0; p < PB; ++p) f[LS + p] = f[LS + p] < INFINITY ? __builtin_amdgcn_sqrtf(f[LS + p]) : 0.0f;
+  for (int p = 0; p < PB; ++p) f[LS + p] = __builtin_amdgcn_sqrtf(f[LS + p]);
   const int j0 = 32 * ks + 8 * g;
   uint32_t neg[PB];
 #pragma unroll
@@ -171,6 +172,7 @@ __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32
   constexpr int LS = PB * (PB - 1) / 2, NF = LS + 2 * PB;
   constexpr int QC = 256;  // queue slots of a wavefront: at most 63 entries wait before a step of 128 candidates
   __shared__ __attribute__((aligned(16))) float lu[C * NT];  // u, [coordinate][tile]
+  static_assert(2 * kHalvesLds <= C * NT && kHalvesLds % 4 == 0, "room for both wavefronts of the other screen");
   __shared__ uint32_t queue[2][QC];                          // seed | tile << 16
   __shared__ float res_g[2][64];
   __shared__ uint32_t res_s[2][64];
@@ -196,6 +198,12 @@ __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32
   const int pair0 = split * pp;
   const int pair1 = pair0 + pp < n_pairs ? pair0 + pp : n_pairs;
   const int n = lane & 15, g = lane >> 4;
+  if (!white_takes(a.d + (int64_t)blk * C)) {  // both wavefronts alike
+    if (row0 + 32 * wv < a.rows)
+      screen_halves<C, POW2>(a, static_cast<const u32x4*>(a.frag), stride, blk, row0 + 32 * wv, split,
+                             lu + wv * kHalvesLds);
+    return;
+  }
 
   // v fragments (coordinates 32 ks + 8 g .. + 7 of tiles 16 nb + n), scaled
   // per tile by a power of two so that |v| lies in [2^9.5, 2^10.5), and u to LDS
@@ -425,8 +433,7 @@ __global__ __launch_bounds__(128, 2) void k_screen_white(EncodeArgs a, const u32
     const float best = fmaxf(tg0, og);
     const bool bedge = (tg0 >= og ? (ts0 & kEdge) : (uint32_t)(ob >> 32)) != 0;
     const float thr = slack_thr(best - 1.01f * rescore_window(best, energy, bedge));
-    // (a tile without energy has nothing to gain, also where d = 0 makes its scores NaN)
-    const float x = energy == 0.0f ? 0.0f : thr >= 0.0f ? sqrtf(thr) - slack_v : -1.0f;
+    const float x = thr >= 0.0f ? sqrtf(thr) - slack_v : -1.0f;
     s_thr[wv][lane] = !my_screened ? INFINITY : x >= 0.0f ? (x * vsc) * (x * vsc) : -1.0f;
     wave_sync();
     thr2[0] = s_thr[wv][tile0];
@@ -575,6 +582,8 @@ static hipError_t run_white(const EncodeArgs& a, void* ws, hipStream_t st) {
 }
 
 hipError_t launch_white_screen(const EncodeArgs& a, void* ws, hipStream_t st) {
+  const hipError_t e = launch_mfma_frags(a.basis, kC, a.P, a.S, a.frag, st);  // for the blocks that white_takes leaves
+  if (e != hipSuccess) return e;
   return a.scale_fmt == AWSRC_SCALE_POW2 ? run_white<true>(a, ws, st) : run_white<false>(a, ws, st);
 }
 
