@@ -39,7 +39,7 @@
 //
 // On the gate, up and down projections of a 3B layer (67.6 M weights, bf16,
 // per-element weights, S = 16): 3884 us with the general vector screen and
-// re-score, 500 us here, 90 of them in the knife-edge scores (a copy of the
+// re-score, 503 us here, 90 of them in the knife-edge scores (a copy of the
 // tensors takes 160).  11008 x 2048 with per-column weights: 985 -> 200 us.
 #include <math.h>
 
@@ -65,7 +65,7 @@ constexpr int kRow = 20;      // floats per LDS row of a tile (16-byte aligned r
 // 15,360) whose best seed in 64 bits is lost: general screen 1142 / 4586,
 // the products here 1342 / 5081, with this rule 1144 / 4586.  At 100 times 1e-4
 // of the candidates are below it, at 1000 times 1%, without outliers none.  The
-// test costs 1% (the MLP projections below: 494 -> 500 us); an 11008 x 2048 module
+// test costs 1.5% (the MLP projections below: 495 -> 503 us); an 11008 x 2048 module
 // with one channel in 1000 at 1e5 takes 277 us instead of 208.
 constexpr float kIll = 0x1p-10f;
 constexpr int kBlocks = 3;    // row tables per four seeds: b, and two of Gram entries
@@ -533,7 +533,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
     uint16_t bits2;
     const int s2 = list_seed(ts1);
     const double g2 = score64(s2, q2, al2, &bits2);
-    if (need && (g2 > best || (g2 == best && s2 < best_s))) {
+    if (need && !(g2 < best) && (g2 != best || s2 < best_s)) {
       best = g2;
       best_s = s2;
       bits = bits2;
@@ -543,24 +543,26 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
   }
   if (t >= T) return;
   const int64_t to = md.tile_off + t;
-  a.seed_out[to] = (uint16_t)best_s;
-  a.scale_out[to] = bits;
-  a.gain_out[to] = best;
+  // a gain that is not a number (infinite or NaN inputs): the empty record of the general re-score
+  const bool none = !(best > -INFINITY);
+  a.seed_out[to] = none ? 0xFFFFu : (uint16_t)best_s;
+  a.scale_out[to] = none ? 0u : bits;
+  a.gain_out[to] = none ? -INFINITY : best;
   int8_t* cp = a.code_out + to * P;
   if (FULLP && (reinterpret_cast<uintptr_t>(cp) & 3) == 0) {
     uint32_t w = 0;
 #pragma unroll
     for (int p = 0; p < kPB; ++p) w |= (uint32_t)(uint8_t)q[p] << (8 * p);
-    *reinterpret_cast<uint32_t*>(cp) = w;
+    *reinterpret_cast<uint32_t*>(cp) = none ? 0u : w;
   } else {
 #pragma unroll
     for (int p = 0; p < kPB; ++p)
-      if (p < P) cp[p] = (int8_t)q[p];
+      if (p < P) cp[p] = none ? 0 : (int8_t)q[p];
   }
   if (a.alpha_out) {
 #pragma unroll
     for (int p = 0; p < kPB; ++p)
-      if (p < P) a.alpha_out[to * P + p] = (float)al[p];
+      if (p < P) a.alpha_out[to * P + p] = none ? 0.0f : (float)al[p];
   }
   if (a.top_gain) {
     *reinterpret_cast<float2*>(a.top_gain + t * kTop) = make_float2(tg0, tg1);

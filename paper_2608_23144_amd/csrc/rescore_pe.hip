@@ -83,6 +83,20 @@ __device__ __forceinline__ void write_better(const EncodeArgs& a, const ModEntry
   }
 }
 
+// The record of a tile whose gain is not a number (infinite or NaN inputs): the
+// empty one of the general re-score.
+template <int PB>
+__device__ __forceinline__ void no_record(int& seed, uint16_t& bits, double& gain, int (&q)[PB], double (&al)[PB]) {
+  seed = 0x7FFFFFFF;  // 65535 as stored
+  bits = 0;
+  gain = -INFINITY;
+#pragma unroll
+  for (int p = 0; p < PB; ++p) {
+    q[p] = 0;
+    al[p] = 0.0;
+  }
+}
+
 // Stages the 32 x 64 residual and weight blocks in LDS (rows of kRowD floats;
 // 16 lanes per row segment, 4 rows per pass: each instruction reads whole
 // cache lines); rows past the end repeat the last row.
@@ -401,8 +415,10 @@ __global__ __launch_bounds__(64, 2) void k_finalize_perm_modules(EncodeArgs a, M
   int q[PB];
   double al[PB];
   uint16_t bits;
-  const double gk = solve_score_ldl<PB>(a, bv, L, e, inv, eps, qmax, q, al, &bits);
-  write_better<PB>(a, md, h, valid, need, s0, s1, mine2 ? s1 : s0, row, blk, nb, gk, q, al, bits);
+  double gk = solve_score_ldl<PB>(a, bv, L, e, inv, eps, qmax, q, al, &bits);
+  int s_me = mine2 ? s1 : s0;
+  if (!(gk > -INFINITY)) no_record<PB>(s_me, bits, gk, q, al);
+  write_better<PB>(a, md, h, valid, need, s0, s1, s_me, row, blk, nb, gk, q, al, bits);
 }
 
 hipError_t launch_finalize_pe_modules(const EncodeArgs& a, const ModEntry& one, const ModEntry* mods, int n_mods,

@@ -232,6 +232,31 @@ def test_encode_whitened_leaves_concentrated_blocks():
     assert awsrc.awsrc_encode_scored(whole) <= 1.3 * parts
 
 
+@pytest.mark.parametrize("C,P,S,d_mode,gen", [(16, 4, 16, "elem", 1), (16, 3, 18, "elem", 2), (16, 4, 16, "col", 1),
+                                              (64, 8, 64, "elem", 2), (64, 3, 64, "elem", 2)])
+def test_encode_non_finite_weights(C, P, S, d_mode, gen):
+    """Tiles with an infinite or NaN weight get the empty record (no codes, gain
+    -inf, never ranked) in the C = 16 and the version-2 encoders, as in the general
+    one; the tiles beside them, in the same matrix products, are not touched."""
+    wl = workload("linear256", C=C, P=P, b=4, S=S, d_mode=d_mode)
+    rows, cols = 70, 256
+    inp = gen_module_inputs(wl, Module("t", rows, cols, 0, 5, 5), DEV)
+    W0 = awsrc.awsrc_backbone_rtn(inp["W"])[3]
+    p = _params(wl, 0, gen)
+    ref = awsrc.awsrc_encode_tiles(p, inp["W"], W0, inp["d"], want_alpha=True)
+    W, bad = inp["W"].clone(), torch.zeros(rows, cols // C, dtype=torch.bool, device=DEV)
+    for r, c, v in ((0, 3, "nan"), (3, C + 1, "inf"), (5, 2 * C + 4, "-inf"), (rows - 1, cols - 1, "nan")):
+        W[r, c] = float(v)
+        bad[r, c // C] = True
+    bad = bad.reshape(-1)
+    got = awsrc.awsrc_encode_tiles(p, W, W0, inp["d"], want_alpha=True)
+    for k in ("seed", "codes", "scale", "gain", "alpha"):
+        assert torch.equal(got[k][~bad], ref[k][~bad]), k
+    assert bool((got["seed"][bad] == -1).all()) and bool((got["gain"][bad] == -float("inf")).all())
+    for k in ("codes", "scale", "alpha"):
+        assert not bool(got[k][bad].any()), k
+
+
 @pytest.mark.parametrize("P,S,rows,cols,d_mode", [(8, 48, 70, 256, "col"), (3, 30, 64, 128, "col"),
                                                    (5, 62, 129, 256, "col"), (8, 40, 67, 256, "elem"),
                                                    (4, 256, 64, 128, "elem")])
