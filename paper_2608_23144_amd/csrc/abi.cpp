@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "awsrc_internal.h"
+#include "host_slot.h"
 
 using namespace awsrc;
 
@@ -78,89 +79,6 @@ uint64_t get_le(const uint8_t* p, int n) {
 }
 
 constexpr int kHeaderFixed = 40;
-
-// A small piece of pinned host memory that kernels write results of a call to,
-// so that the host reads them after one stream synchronization (a copy into
-// pageable memory costs 11 us more).  64 slots of 4 KiB in one block, allocated
-// on first use and kept until the process ends; a slot is taken for the length
-// of a call and given back, and a call that finds none free (more than 64 in
-// flight, or no pinned memory) reads through a copy instead.
-class HostSlot {
- public:
-  static constexpr size_t kBytes = 4096;
-  HostSlot() {
-    std::lock_guard<std::mutex> lock(mu());
-    Block& b = block();
-    if (!b.tried) {
-      b.tried = true;
-      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // another thread may be capturing
-      const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-      void* h = nullptr;
-      if (hipHostMalloc(&h, 64 * kBytes, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) {
-        b.host = static_cast<char*>(h);
-      } else {
-        (void)hipGetLastError();
-      }
-      if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
-    }
-    if (b.host && ~b.used) {
-      at_ = __builtin_ctzll(~b.used);
-      b.used |= 1ull << at_;
-      host_ = b.host + (size_t)at_ * kBytes;
-      void* d = nullptr;
-      if (hipHostGetDevicePointer(&d, host_, 0) == hipSuccess) dev_ = d;
-      else (void)hipGetLastError();
-    }
-  }
-  ~HostSlot() {
-    if (at_ < 0) return;
-    std::lock_guard<std::mutex> lock(mu());
-    block().used &= ~(1ull << at_);
-  }
-  HostSlot(const HostSlot&) = delete;
-  HostSlot& operator=(const HostSlot&) = delete;
-  // where a kernel writes the results: the slot, or `device` when there is none
-  uint64_t* device_or(uint64_t* device) const { return dev_ ? static_cast<uint64_t*>(dev_) : device; }
-  // n host bytes (a multiple of 8) of device memory, waiting for the stream
-  hipError_t fetch(void* dst, const void* device, size_t n, hipStream_t s) const {
-    if (!dev_ || n > kBytes) {
-      const hipError_t e = hipMemcpyAsync(dst, device, n, hipMemcpyDeviceToHost, s);
-      return e != hipSuccess ? e : hipStreamSynchronize(s);
-    }
-    const hipError_t e = launch_stage_words(nullptr, 0, nullptr, static_cast<const uint64_t*>(device), (int)(n / 8),
-                                            static_cast<uint64_t*>(dev_), s);
-    return e != hipSuccess ? e : read(dst, n, device, s);
-  }
-  // a word of the slot that kernels may set, cleared; null when there is no slot
-  unsigned long long* flag() const {
-    if (dev_) *reinterpret_cast<volatile uint64_t*>(host_) = 0;
-    return static_cast<unsigned long long*>(dev_);
-  }
-  bool holds(size_t n) const { return dev_ && n <= kBytes; }
-  bool flag_set() const { return *reinterpret_cast<volatile uint64_t*>(host_) != 0; }
-  // waits for the stream and fetches n bytes of results
-  hipError_t read(void* dst, size_t n, const void* device, hipStream_t s) const {
-    if (!dev_) {
-      const hipError_t e = hipMemcpyAsync(dst, device, n, hipMemcpyDeviceToHost, s);
-      if (e != hipSuccess) return e;
-    }
-    const hipError_t e = hipStreamSynchronize(s);
-    if (e == hipSuccess && dev_) memcpy(dst, host_, n);
-    return e;
-  }
-
- private:
-  struct Block {
-    char* host = nullptr;
-    uint64_t used = 0;
-    bool tried = false;
-  };
-  static std::mutex& mu() { static std::mutex m; return m; }
-  static Block& block() { static Block b; return b; }
-  int at_ = -1;
-  char* host_ = nullptr;
-  void* dev_ = nullptr;
-};
 
 }  // namespace
 
@@ -836,7 +754,7 @@ extern "C" awsrc_status awsrc_rank_prefix(const awsrc_params* p, int32_t n_modul
     if (whole) memcpy(hc.b, hdr.data(), hdr.size());
     else HIPCHK(launch_rank_init(nullptr, hdr.data(), hdr.size(), stream_out, s));
     HIPCHK(launch_rank_small(gain, tb, (int)seg_n.size(), (int64_t)max_n, rw, hc, whole ? (int)hdr.size() : 0, pa,
-                             slot.device_or(rw.state), s));
+                             slot.device_or(rw.state, s), s));
     HIPCHK(slot.read(tot, sizeof tot, rw.state, s));
   } else {
     for (bool exact : {false, true}) {
@@ -844,7 +762,7 @@ extern "C" awsrc_status awsrc_rank_prefix(const awsrc_params* p, int32_t n_modul
       for (size_t i = 0; i < seg_n.size(); ++i)
         HIPCHK(launch_rank_segment(gain, seg_t0[i], seg_n[i], seg_cap[i] < seg_n[i] ? seg_cap[i] : seg_n[i], rw, pa,
                                    exact, s));
-      HIPCHK(launch_rank_totals(rw, slot.device_or(rw.blk_a), s));
+      HIPCHK(launch_rank_totals(rw, slot.device_or(rw.blk_a, s), s));
       HIPCHK(slot.read(tot, sizeof tot, rw.blk_a, s));
       if (!tot[3]) break;  // else more equal gains than the fast path takes
     }
@@ -989,7 +907,7 @@ extern "C" awsrc_status awsrc_decode_prepare(const uint8_t* stream_bytes, uint64
   pl.records = stream_bytes + h;
   pl.workspace = workspace;
   DecodeArgs a = decode_args(&pl);
-  a.err_flag = slot.flag();
+  a.err_flag = slot.flag(s);
   memcpy(tabs.data() + 2 * (size_t)nmod + 1, W0_ptrs, nmod * sizeof(void*));
   // the module tables go by value when they fit, else in a copy of their own
   const bool by_value = tabs.size() <= (size_t)kTableWords;
@@ -998,7 +916,7 @@ extern "C" awsrc_status awsrc_decode_prepare(const uint8_t* stream_bytes, uint64
   HIPCHK(launch_decode_setup(key, gen, a, tabs.data(), by_value ? (int)tabs.size() : 0, s));
   HIPCHK(launch_decode_validate(a, s));
   unsigned long long nerr = 0;
-  if (a.err_flag) HIPCHK(hipStreamSynchronize(s));
+  if (a.err_flag) HIPCHK(slot.wait(s));
   if (!a.err_flag || slot.flag_set()) {
     HIPCHK(hipMemcpyAsync(&nerr, a.errors, 8, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
@@ -1073,7 +991,7 @@ awsrc_status reconstruct(const awsrc_decode_plan* plan, int32_t n_out, const int
   HostSlot slot;
   if (tabs.size() <= (size_t)kTableWords && slot.holds(mt.size() * 8)) {
     HIPCHK(launch_stage_words(tabs.data(), (int)tabs.size(), bbt, a.mod_tile_off, (int)mt.size(),
-                              slot.device_or(nullptr), s));
+                              slot.device_or(nullptr, s), s));
     HIPCHK(slot.read(mt.data(), mt.size() * 8, nullptr, s));
   } else {
     HIPCHK(hipMemcpyAsync(bbt, tabs.data(), tabs.size() * 8, hipMemcpyHostToDevice, s));

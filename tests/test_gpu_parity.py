@@ -906,6 +906,63 @@ def test_decode_prepare_reuses_workspace():
         assert np.all(np.abs(dev.cpu().numpy() - want) <= 2.0 ** -22 * (np.abs(w0f) + np.abs(want - w0f)) + 1e-30)
 
 
+def test_calls_of_many_threads():
+    """72 threads, each on a stream of its own, rank, decode and reconstruct while
+    every stream waits for one event, so that more calls are in flight than there
+    are pinned result slots (64): each gets its own results, as one after another."""
+    import threading
+
+    n, wl = 72, workload("linear256")
+    mods, gs = [], torch.Generator(device=DEV).manual_seed(11)
+    for i in range(n):
+        rows = 33 + 3 * i
+        T = rows * 4
+        rec = gen_records(T, wl.P, wl.b, wl.S, seed=100 + i, device=DEV)
+        W0 = torch.randn(rows, 256, generator=gs, device=DEV)
+        bb = awsrc.awsrc_backbone_rtn(W0)
+        mods.append((rows, rec, W0, bb[:3]))
+    p = _params(wl)
+
+    def work(i, stream):
+        rows, rec, W0, bb = mods[i]
+        s, K, ne = awsrc.awsrc_rank_prefix(p, [(rows, 256)], awsrc.AWSRC_MODE_GLOBAL, 1.5, rec["seed"], rec["codes"],
+                                           rec["scale"], rec["gain"], stream=stream)
+        out = W0.clone()
+        awsrc.awsrc_decode_add(s, [out], stream=stream)
+        dense = torch.empty(rows, 256, dtype=torch.bfloat16, device=DEV)
+        plan, ws = awsrc.awsrc_decode_prepare(s, [dense], stream=stream)
+        awsrc.awsrc_reconstruct_bf16(plan, [bb], stream=stream)
+        return K, ne, s, out, dense, ws
+
+    want = [work(i, None) for i in range(n)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(n)]
+    torch.cuda._sleep(20_000_000)
+    ev = torch.cuda.Event()
+    ev.record()
+    got, errors = [None] * n, []
+
+    def run(i):
+        try:
+            with torch.cuda.stream(streams[i]):
+                streams[i].wait_event(ev)
+                got[i] = work(i, streams[i])
+                streams[i].synchronize()
+        except Exception as e:  # noqa: BLE001 - reported below, from the main thread
+            errors.append((i, repr(e)))
+
+    threads = [threading.Thread(target=run, args=(i,)) for i in range(n)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors[:3]
+    for a, b in zip(got, want):
+        assert a[:2] == b[:2]
+        for k in (2, 3, 4):
+            assert torch.equal(a[k], b[k])
+
+
 def _corrupt_cases(stream, hd):
     h, L = hd["h"], hd["L_rec"]
     bad = {}
