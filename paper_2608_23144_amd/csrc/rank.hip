@@ -705,7 +705,7 @@ __global__ __launch_bounds__(256) void k_small_count(const double* __restrict__ 
 
 template <int M>
 __global__ __launch_bounds__(M / 2 < 1024 ? M / 2 : 1024) void k_small_rank(const double* __restrict__ gain, SmallTable tb, int n_seg,
-                                                     const uint64_t* __restrict__ kseg, uint64_t* state, HeaderChunk hc,
+                                                     const uint64_t* __restrict__ kseg, HeaderChunk hc,
                                                      int n_hdr, PackArgs pa, uint64_t* __restrict__ totals) {
   constexpr int THREADS = M / 2 < 1024 ? M / 2 : 1024;
   __shared__ uint64_t sk[M];
@@ -1146,14 +1146,14 @@ hipError_t launch_rank_small(const double* gain, const SmallTable& tb, int n_seg
                              const HeaderChunk& hc, int n_hdr, const PackArgs& pa, uint64_t* totals, hipStream_t st) {
   if (n_seg > 1) hipLaunchKernelGGL(k_small_count, dim3((unsigned)n_seg), dim3(256), 0, st, gain, tb, ws.kseg);
   if (max_n <= 1024)
-    hipLaunchKernelGGL((k_small_rank<1024>), dim3((unsigned)n_seg), dim3(512), 0, st, gain, tb, n_seg, ws.kseg, ws.state,
+    hipLaunchKernelGGL((k_small_rank<1024>), dim3((unsigned)n_seg), dim3(512), 0, st, gain, tb, n_seg, ws.kseg,
                        hc, n_hdr, pa, totals);
   else if (max_n <= 2048)
     hipLaunchKernelGGL((k_small_rank<2048>), dim3((unsigned)n_seg), dim3(1024), 0, st, gain, tb, n_seg, ws.kseg,
-                       ws.state, hc, n_hdr, pa, totals);
+                       hc, n_hdr, pa, totals);
   else
     hipLaunchKernelGGL((k_small_rank<kSmallMax>), dim3((unsigned)n_seg), dim3(1024), 0, st, gain, tb, n_seg, ws.kseg,
-                       ws.state, hc, n_hdr, pa, totals);
+                       hc, n_hdr, pa, totals);
   return hipGetLastError();
 }
 
