@@ -757,14 +757,17 @@ extern "C" awsrc_status awsrc_rank_prefix(const awsrc_params* p, int32_t n_modul
                              slot.device_or(rw.state, s), s));
     HIPCHK(slot.read(tot, sizeof tot, rw.state, s));
   } else {
-    for (bool exact : {false, true}) {
-      HIPCHK(launch_rank_init(&rw, hdr.data(), hdr.size(), stream_out, s));
+    RankPath path = kRankFast;
+    for (;;) {
+      if (path != kRankResume) HIPCHK(launch_rank_init(&rw, hdr.data(), hdr.size(), stream_out, s));
       for (size_t i = 0; i < seg_n.size(); ++i)
         HIPCHK(launch_rank_segment(gain, seg_t0[i], seg_n[i], seg_cap[i] < seg_n[i] ? seg_cap[i] : seg_n[i], rw, pa,
-                                   exact, s));
+                                   path, s));
       HIPCHK(launch_rank_totals(rw, slot.device_or(rw.blk_a, s), s));
       HIPCHK(slot.read(tot, sizeof tot, rw.blk_a, s));
-      if (!tot[3]) break;  // else more equal gains than the fast path takes
+      if (!tot[3] || path != kRankFast) break;
+      // more equal gains than the fast path takes
+      path = tot[3] == 1 && seg_n.size() == 1 ? kRankResume : kRankExact;
     }
   }
   const int64_t K_total = (int64_t)tot[0];

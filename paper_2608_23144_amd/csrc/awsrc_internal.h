@@ -506,8 +506,13 @@ hipError_t launch_rank_init(const RankWs* ws, const uint8_t* hdr, size_t n_hdr, 
 // Top-K of one tile segment (K = min(cap, eligible), found on the device),
 // ordered by (gain desc, tile asc), packed at the segment's first free record
 // slot of the stream; no host synchronization.
+enum RankPath {
+  kRankFast,    // may give up (kRankTotals' run-again word: 1 before the sort, 2 after)
+  kRankExact,   // any number of equal gains
+  kRankResume,  // the exact path after a fast attempt that gave up before the sort, the call's only segment
+};
 hipError_t launch_rank_segment(const double* gain, int64_t t0, int64_t n, int64_t cap, const RankWs& ws,
-                               const PackArgs& pa, bool exact, hipStream_t st);
+                               const PackArgs& pa, RankPath path, hipStream_t st);
 // Writes the kRankTotals totals of the segments so far to dst.
 hipError_t launch_rank_totals(const RankWs& ws, uint64_t* dst, hipStream_t st);
 // Every segment of a call at once, header and totals included, when none has

@@ -25,6 +25,12 @@
 // That is the exact path, which takes any number of equal gains.  The fast
 // path, tried first, stops the select after two digits and sorts a few more
 // keys than it keeps; small segments are ranked whole by one workgroup each.
+// The fast path gives up where too many gains are equal.  Mostly it finds that
+// before it sorts (a look at 4096 gains, the size of the K-th key's bin), and the
+// exact path goes on from there: gains rounded to bf16, 43 M of them, 2.55 ms
+// (with the whole fast path in front 4.1; the exact path alone,
+// as it was before there was a fast one, 2.7).  One value many thousand times
+// among distinct ones can still cost both paths, 3.1 ms there.
 #include <string.h>
 
 #include "awsrc_internal.h"
@@ -49,13 +55,17 @@ enum : int {
   kSegK = 4, kSegOff = 5,                       // records of the segment, its first record slot
   kElig = 6, kArrive = 7,                       // per-launch accumulators, reset after use
   kTotK = 8, kTotElig = 9, kNoSpace = 10,       // totals over the segments of one call
-  kAgain = 11,                                  // the fast path could not finish: run the exact path
+  kAgain = 11,                                  // the fast path could not finish (kAgain* below)
   kCnt = 12,                                    // survivors of the segment (fast path)
   kBase = 13, kShift = 14,                      // fast path: smallest ~key of the segment, cell width
+  kBig = 15,                                    // fast path: cells left to k_sort_cells
   kSel = 16,                                    // [2][4] pick state of alternate passes
+  kOver = 24,                                   // the survivors do not fit the fast path's items
   kHist = 32                                    // [3][kSelBins] histograms of rotating passes
 };
 static_assert(kHist + 3 * kSelBins == kStateWords, "rank state size");
+// kAgain: before anything was sorted (the select's first pass still stands), or after
+constexpr uint64_t kAgainEarly = 1, kAgainLate = 2;
 
 // Positive doubles order like their bit patterns; the top (sign) bit is set on
 // eligible keys so that every eligible key exceeds every ineligible (zero) key.
@@ -100,7 +110,18 @@ __global__ void k_rank_init(uint64_t* state, HeaderChunk hc, int n, uint8_t* __r
 // The totals of a call (records, eligible tiles, no-space and run-again
 // flags) for the host.
 __global__ void k_rank_totals(const uint64_t* state, uint64_t* dst) {
-  if (threadIdx.x < kRankTotals) dst[threadIdx.x] = state[kTotK + threadIdx.x];
+  if (threadIdx.x < kRankTotals) {
+    uint64_t v = state[kTotK + threadIdx.x];
+    if (threadIdx.x == kAgain - kTotK && state[kOver]) v = v > kAgainEarly ? v : kAgainEarly;
+    dst[threadIdx.x] = v;
+  }
+}
+
+// After a fast attempt that ended early, on the one segment of a call: the exact
+// path goes on from the first select pass (its pick, the second histogram and the
+// eligible count stand).
+__global__ void k_rank_resume(uint64_t* state) {
+  if ((threadIdx.x >= kTotK && threadIdx.x <= kAgain) || threadIdx.x == kOver) state[threadIdx.x] = 0;
 }
 
 // ---------------------------------------------------------------- radix select
@@ -151,6 +172,7 @@ __global__ __launch_bounds__(kThreads) void k_count_hist(const double* __restric
 
 struct SelState {
   uint64_t prefix, mask, rem, done;
+  uint64_t bin;  // keys in the bin just picked (pick_bin)
 };
 
 // One block of kThreads: the bin of histogram `hist` (digit at `shift`,
@@ -158,7 +180,7 @@ struct SelState {
 // bins counted from the top.  Every thread returns the same state.
 __device__ SelState pick_bin(const uint64_t* hist, SelState in, int shift, int width) {
   __shared__ uint64_t s_wave[kThreads / 64];
-  __shared__ uint64_t found[3];
+  __shared__ uint64_t found[4];
   constexpr int kMaxBpt = kSelBins / kThreads;
   const int nbins = 1 << width;
   const int bpt = nbins >= kThreads ? nbins / kThreads : 1;
@@ -172,7 +194,7 @@ __device__ SelState pick_bin(const uint64_t* hist, SelState in, int shift, int w
     v[i] = (i < bpt && r < nbins) ? hist[nbins - 1 - r] : 0ull;
     local += v[i];
   }
-  if (t < 3) found[t] = 0;
+  if (t < 4) found[t] = 0;
   // inclusive scan: within the wavefront by shuffles, then across the four
   uint64_t x = local;
 #pragma unroll
@@ -197,6 +219,7 @@ __device__ SelState pick_bin(const uint64_t* hist, SelState in, int shift, int w
         found[0] = (uint64_t)(nbins - 1 - (t * bpt + i));
         found[1] = in.rem - cum;
         found[2] = (c == in.rem - cum) ? 1ull : 0ull;
+        found[3] = c;
         hit = true;
       }
       cum += c;
@@ -208,8 +231,47 @@ __device__ SelState pick_bin(const uint64_t* hist, SelState in, int shift, int w
   out.mask = in.mask | (((1ull << width) - 1ull) << shift);
   out.rem = found[1];
   out.done = found[2];
+  out.bin = found[3];
   __syncthreads();
   return out;
+}
+
+// The fast path's look ahead at how many gains are equal: 4096 gains spread over
+// the segment, those at or above the K-th key's first digit (some 950 where a
+// quarter is kept, kTieSlots - 512 at most) entered in a hash table of kTieSlots
+// keys; returns how many were in it already.  With gains rounded to bf16 or
+// fp16, or of a thousand values, these are hundreds; groups of equal gains that
+// k_sort_cells takes (up to kCellSort, 2% of the records in groups of 2000)
+// give one or two.
+constexpr int kTieSlots = kSelBins / 2;  // 2^11
+constexpr int kTieProbe = 8;
+__device__ int tie_probe(const double* __restrict__ gain, int64_t n, const SelState& sel, unsigned long long* table) {
+  __shared__ int s_in, s_dup;
+  for (int b = threadIdx.x; b < kTieSlots; b += kThreads) table[b] = 0ull;
+  if (threadIdx.x == 0) s_in = s_dup = 0;
+  __syncthreads();
+  constexpr int kRows = 4096 / kThreads;
+  const uint32_t step = (uint32_t)(n / 4096);  // (n <= 2^32)
+  double gv[kRows];
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) {
+    const uint32_t j = r * kThreads + threadIdx.x;
+    gv[r] = gain[(int64_t)j * step + __umulhi(j * 0x9E3779B1u, step)];
+  }
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) {
+    const uint64_t k = gain_key(gv[r]);
+    if (k != 0 && (k & sel.mask) >= sel.prefix && atomicAdd(&s_in, 1) < kTieSlots - 512) {
+      // at most kTieSlots - 512 keys: an empty slot always ends the search
+      for (uint32_t at = ((uint32_t)(k >> 32) * 0x85EBCA6Bu ^ (uint32_t)k * 0x9E3779B1u) >> 21;; at = (at + 1) & (kTieSlots - 1)) {
+        const unsigned long long old = atomicCAS(&table[at], 0ull, (unsigned long long)k);
+        if (old == k) atomicAdd(&s_dup, 1);
+        if (old == 0ull || old == k) break;
+      }
+    }
+  }
+  __syncthreads();
+  return s_dup;
 }
 
 // Pass `pass` (1..5) of a segment: pick from the previous pass's histogram
@@ -217,8 +279,8 @@ __device__ SelState pick_bin(const uint64_t* hist, SelState in, int shift, int w
 // under the new prefix.  Pass 1 forms K = min(cap, eligible) itself.
 __global__ __launch_bounds__(kThreads) void k_select_pass(const double* __restrict__ gain, int64_t n,
                                                           uint64_t* state, int64_t cap, int pass, int prev_shift,
-                                                          int prev_width, int shift, int width, int fast) {
-  __shared__ uint32_t h[kSelBins];
+                                                          int prev_width, int shift, int width, int fast, int probe) {
+  __shared__ __attribute__((aligned(8))) uint32_t h[kSelBins];
   SelState cur;
   if (fast && blockIdx.x == 0) {
     // the fast path's segment bookkeeping (no other block reads these words)
@@ -234,17 +296,18 @@ __global__ __launch_bounds__(kThreads) void k_select_pass(const double* __restri
       state[kTotK] += ne < (uint64_t)cap ? ne : (uint64_t)cap;
       state[kTotElig] += ne;
       state[kCnt] = 0;
+      state[kBig] = 0;
       state[kBase] = ~(((uint64_t)top << (64 - kSelBits)) | ((1ull << (64 - kSelBits)) - 1ull));
     }
   }
   if (pass == 1) {
     const uint64_t ne = state[kElig];
     const uint64_t K = ne < (uint64_t)cap ? ne : (uint64_t)cap;
-    cur = SelState{0ull, 0ull, K, K == 0 ? 1ull : 0ull};
+    cur = SelState{0ull, 0ull, K, K == 0 ? 1ull : 0ull, 0ull};
     if (blockIdx.x == 0 && threadIdx.x == 0) state[kSegK] = K;
   } else {
     const uint64_t* sp = state + kSel + 4 * ((pass - 1) & 1);
-    cur = SelState{sp[0], sp[1], sp[2], sp[3]};
+    cur = SelState{sp[0], sp[1], sp[2], sp[3], 0ull};
   }
   // the histogram two passes back has been read by the previous launch
   uint64_t* hclr = state + kHist + kSelBins * ((pass + 1) % 3);
@@ -263,13 +326,18 @@ __global__ __launch_bounds__(kThreads) void k_select_pass(const double* __restri
       state[kShift] = (uint64_t)(64 - kSelBits + lg - kCellBits);
     }
   }
+  if (probe && blockIdx.x == gridDim.x - 1) {  // one block for this, the others for the pass
+    if (tie_probe(gain, n, nw, reinterpret_cast<unsigned long long*>(h)) >= kTieProbe && threadIdx.x == 0)
+      state[kAgain] = kAgainEarly;
+    return;
+  }
   if (nw.done) return;  // uniform
   for (int b = threadIdx.x; b < kSelBins; b += kThreads) h[b] = 0;
   __syncthreads();
   const uint64_t dm = (1ull << width) - 1ull;
   // eight independent loads per thread in flight (the grid is small: each
   // block ends with up to 4096 global atomics)
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
+  const int64_t stride = (int64_t)(gridDim.x - probe) * kThreads;
   int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   for (; i + 7 * stride < n; i += 8 * stride) {
     double gv[8];
@@ -295,7 +363,7 @@ __global__ __launch_bounds__(kThreads) void k_select_pass(const double* __restri
 // first compaction launch computes it.
 __device__ SelState final_select(const uint64_t* state) {
   const uint64_t* sp = state + kSel + 4 * (5 & 1);
-  SelState cur = SelState{sp[0], sp[1], sp[2], sp[3]};
+  SelState cur = SelState{sp[0], sp[1], sp[2], sp[3], 0ull};
   if (!cur.done) cur = pick_bin(state + kHist + kSelBins * (5 % 3), cur, 0, 4);
   return cur;
 }
@@ -442,7 +510,8 @@ __global__ __launch_bounds__(kThreads) void k_compact_write(const double* __rest
 // scan (43 M gains: 5 x 60, 71 and 31 of 2,089 us; here one of 60).  The
 // order of the survivors is free (slots are reserved by block), since the
 // sort breaks ties by tile.  More survivors than the items hold (many equal
-// gains) sets kAgain and the call runs the exact path instead.
+// gains) sets kAgain and the call runs the exact path instead, from the pass of
+// the select that is done.
 template <int ROUNDS>
 __global__ __launch_bounds__(kThreads) void k_compact_fast(const double* __restrict__ gain,
                                                            const uint16_t* __restrict__ seed,
@@ -453,8 +522,15 @@ __global__ __launch_bounds__(kThreads) void k_compact_fast(const double* __restr
   __shared__ uint64_t s_base;
   const uint64_t K = state[kSegK];
   const uint64_t* sp = state + kSel + 4;  // the pick of pass 1
-  SelState fin = SelState{sp[0], sp[1], sp[2], sp[3]};
-  if (!fin.done) fin = pick_bin(state + kHist + kSelBins, fin, 64 - 2 * kSelBits, kSelBits);
+  SelState fin = SelState{sp[0], sp[1], sp[2], sp[3], 0ull};
+  if (state[kAgain]) return;  // (not set in this launch)
+  if (!fin.done) {
+    fin = pick_bin(state + kHist + kSelBins, fin, 64 - 2 * kSelBits, kSelBits);
+    if (K - fin.rem + fin.bin > cap_items) {  // uniform
+      if (blockIdx.x == 0 && threadIdx.x == 0) state[kOver] = 1;
+      return;
+    }
+  }
   if (blockIdx.x == 0) {  // the first histogram has been read: clear it and the count for the next segment
     for (int b = threadIdx.x; b < kSelBins; b += kThreads) state[kHist + b] = 0;
     if (threadIdx.x == 0) state[kElig] = 0;
@@ -500,8 +576,6 @@ __global__ __launch_bounds__(kThreads) void k_compact_fast(const double* __restr
         it.tile = (uint32_t)(t0 + i);
         it.aux = (uint32_t)seed[t0 + i] | ((uint32_t)scale[t0 + i] << 16);
         items_out[slot] = it;
-      } else if (take) {
-        state[kAgain] = 1;
       }
       at += (uint64_t)__popcll(bal);
     }
@@ -639,9 +713,9 @@ __global__ __launch_bounds__(kChunkThreads) void k_sort_chunks(SortItem* __restr
                                                                PackArgs pa) {
   __shared__ uint64_t sk[kChunk];
   __shared__ uint32_t st[kChunk];
-  if (clear_hist && blockIdx.x == 0)
-    for (int b = threadIdx.x; b < kSelBins; b += kChunkThreads) state[kHist + kSelBins + b] = 0;
   const int64_t n = sort_count(state, cap_items);
+  if (clear_hist && blockIdx.x == 0 && n > 0)  // (an attempt given up needs it again)
+    for (int b = threadIdx.x; b < kSelBins; b += kChunkThreads) state[kHist + kSelBins + b] = 0;
   const int64_t base = (int64_t)blockIdx.x * kChunk;
   if (base >= n) return;  // uniform per block
 #pragma unroll
@@ -844,10 +918,10 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const SortItem* __restri
   constexpr int BINS = 1 << BITS;
   __shared__ uint32_t h[BINS];
   for (int d = threadIdx.x; d < BINS; d += kRsThreads) h[d] = 0;
-  if (clear_hist && blockIdx.x == 0)  // the fast path's second histogram has been read by now
+  const int64_t n = sort_count(state, cap_items);
+  if (clear_hist && blockIdx.x == 0 && n > 0)  // the fast path's second histogram has been read by now
     for (int b = threadIdx.x; b < kSelBins; b += kRsThreads) state[kHist + kSelBins + b] = 0;
   __syncthreads();
-  const int64_t n = sort_count(state, cap_items);
   const uint64_t kb = state[kBase];
   const int s0 = (int)state[kShift];
   const int64_t base = (int64_t)blockIdx.x * kRsItems;
@@ -1023,15 +1097,15 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const SortItem* __res
 
 // Last step of the fast path's radix sort: the items are in cell order; each
 // finds its place among the items of its own cell (by key, then tile) and is
-// packed.  A cell of more than kCellMax items (gains that agree in more than
-// 20 mantissa bits, many times over) sets kAgain.
+// packed.  A cell of more than kCellMax items (equal gains, or gains that agree
+// in more than 20 mantissa bits) goes to `big`, as its first item's place.
 // A block's keys (and kCellMax to either side) are compared in LDS, while the
 // gathers of its tiles' codes, the bulk of the memory time, are in flight.
 constexpr int kCellMax = 64;
 constexpr int kPcRounds = 4;
 constexpr int kPcItems = 256 * kPcRounds;
 __global__ __launch_bounds__(256) void k_pack_cells(const SortItem* __restrict__ in, uint64_t* state, int64_t cap_items,
-                                                    PackArgs pa) {
+                                                    uint32_t* __restrict__ big, PackArgs pa) {
   __shared__ uint64_t sk[kPcItems + 2 * kCellMax];
   __shared__ uint32_t st[kPcItems + 2 * kCellMax];
   const int64_t n = sort_count(state, cap_items);
@@ -1080,8 +1154,60 @@ __global__ __launch_bounds__(256) void k_pack_cells(const SortItem* __restrict__
       if (sort_value<true>(y.key, kb, s0) != cell) break;
       pos += kv_less(y, x[r]);
     }
-    if (d - 1 + e - 1 >= kCellMax) state[kAgain] = 1;
-    else pack_record(pa, state, pos, x[r].tile, x[r].aux, c[r]);
+    if (d - 1 + e - 1 < kCellMax)
+      pack_record(pa, state, pos, x[r].tile, x[r].aux, c[r]);
+    else if (d == 1)  // at most n / kCellMax of them, and `big` has room for n / 8
+      big[atomicAdd((unsigned long long*)&state[kBig], 1ull)] = (uint32_t)i;
+  }
+}
+
+// The cells that k_pack_cells left, one workgroup each: up to kCellSort items
+// are sorted in LDS and packed, a larger cell sets kAgain.  10 M records of 43 M
+// gains, 2% of these in groups of 128 equal ones: 1.4 ms, 3.2 when such a call
+// ran both paths; none to sort: 5 us.
+constexpr int kCellSort = 4096;
+constexpr int kCellBlocks = 128;
+__global__ __launch_bounds__(256) void k_sort_cells(const SortItem* __restrict__ in, uint64_t* state, int64_t cap_items,
+                                                    const uint32_t* __restrict__ big, PackArgs pa) {
+  __shared__ uint64_t sk[kCellSort];
+  __shared__ uint32_t st[kCellSort];
+  __shared__ int s_m;
+  const int64_t n = sort_count(state, cap_items);
+  const uint64_t n_big = state[kBig], kb = state[kBase];
+  const int s0 = (int)state[kShift];
+  for (uint64_t c = blockIdx.x; c < n_big; c += gridDim.x) {
+    const int64_t i0 = big[c];
+    const uint64_t cell = sort_value<true>(in[i0].key, kb, s0);
+    if (threadIdx.x == 0) s_m = 0;
+    __syncthreads();
+    int m = 0;  // items of the cell among the next kCellSort + 256 (they are adjacent)
+    for (int k = threadIdx.x; k < kCellSort + 256; k += 256) {
+      if (i0 + k >= n) break;
+      const SortItem x = in[i0 + k];
+      if (sort_value<true>(x.key, kb, s0) != cell) break;
+      if (k < kCellSort) {
+        sk[k] = x.key;
+        st[k] = x.tile;
+      }
+      ++m;
+    }
+    if (m) atomicAdd(&s_m, m);
+    __syncthreads();
+    m = s_m;
+    if (m > kCellSort) {  // uniform
+      if (threadIdx.x == 0) state[kAgain] = kAgainLate;
+      __syncthreads();
+      continue;
+    }
+    const int M = m <= 512 ? 512 : kCellSort;
+    for (int k = m + threadIdx.x; k < M; k += 256) {  // sorts behind every item
+      sk[k] = ~0ull;
+      st[k] = 0xFFFFFFFFu;
+    }
+    if (M == 512) bitonic_lds<512, 256>(sk, st);
+    else bitonic_lds<kCellSort, 256>(sk, st);
+    for (int k = threadIdx.x; k < m; k += 256) pack_record(pa, state, i0 + k, st[k]);
+    __syncthreads();  // sk, st and s_m are used again
   }
 }
 
@@ -1188,12 +1314,14 @@ static void sort_and_pack(const RankWs& ws, int64_t cap_items, int clear_hist, c
 // and kernels read the actual K from the state.  exact: the path that handles
 // any number of equal gains, else the fast one (see k_compact_fast).
 hipError_t launch_rank_segment(const double* gain, int64_t t0, int64_t n, int64_t cap, const RankWs& ws,
-                               const PackArgs& pa, bool exact, hipStream_t st) {
+                               const PackArgs& pa, RankPath path, hipStream_t st) {
+  const bool exact = path != kRankFast;
   const double* g = gain + t0;
   int64_t cb = (n + kThreads - 1) / kThreads;
   if (cb > 512) cb = 512;
   if (cb < 1) cb = 1;
-  hipLaunchKernelGGL(k_count_hist, dim3((unsigned)cb), dim3(kThreads), 0, st, g, n, ws.state);
+  if (path == kRankResume) hipLaunchKernelGGL(k_rank_resume, dim3(1), dim3(64), 0, st, ws.state);
+  else hipLaunchKernelGGL(k_count_hist, dim3((unsigned)cb), dim3(kThreads), 0, st, g, n, ws.state);
   // passes 1..5 over the digits 12, 12, 12, 12 and 4 bits below the top one
   const int shifts[6] = {64 - kSelBits, 64 - 2 * kSelBits, 64 - 3 * kSelBits, 64 - 4 * kSelBits, 64 - 5 * kSelBits, 0};
   const int widths[6] = {kSelBits, kSelBits, kSelBits, kSelBits, kSelBits, 4};
@@ -1205,13 +1333,16 @@ hipError_t launch_rank_segment(const double* gain, int64_t t0, int64_t n, int64_
   if (sb > sb_max) sb = sb_max;
   if (sb < 1) sb = 1;
   const int n_pass = exact ? 5 : 1;
-  for (int pass = 1; pass <= n_pass; ++pass)
+  int64_t cap_items = cap + (int64_t)cap_slack((size_t)n);
+  if (cap_items > n) cap_items = n;
+  // (the merges of smaller caps do not mind equal gains; the look ahead has one
+  // of the pass's blocks, of 128 or more)
+  const int probe = !exact && cap > 0 && cap_items > kRadixMin ? 1 : 0;
+  for (int pass = path == kRankResume ? 2 : 1; pass <= n_pass; ++pass)
     hipLaunchKernelGGL(k_select_pass, dim3((unsigned)sb), dim3(kThreads), 0, st, g, n, ws.state,
                        (int64_t)(cap > 0 ? cap : 0), pass, shifts[pass - 1], widths[pass - 1], shifts[pass],
-                       widths[pass], exact ? 0 : 1);
+                       widths[pass], exact ? 0 : 1, probe);
   if (!exact) {
-    int64_t cap_items = cap + (int64_t)cap_slack((size_t)n);
-    if (cap_items > n) cap_items = n;
     // small segments in shorter chunks, so that more blocks share them
     const int rounds = n > ((int64_t)1 << 22) ? 16 : 4;
     int64_t nb = (n + kThreads * rounds - 1) / (kThreads * rounds);
@@ -1239,7 +1370,8 @@ hipError_t launch_rank_segment(const double* gain, int64_t t0, int64_t n, int64_
       SortItem* tt = in; in = out; out = tt;
     }
     hipLaunchKernelGGL(k_pack_cells, dim3((unsigned)((cap_items + kPcItems - 1) / kPcItems)), dim3(256), 0, st, in, ws.state,
-                       cap_items, pa);
+                       cap_items, ws.rs_hist, pa);  // (the digit counts have been read)
+    hipLaunchKernelGGL(k_sort_cells, dim3(kCellBlocks), dim3(256), 0, st, in, ws.state, cap_items, ws.rs_hist, pa);
     return hipGetLastError();
   }
   // the first compaction launch finishes the select and records the totals

@@ -692,6 +692,12 @@ def _want_stream_records(rec, segs, caps):
     ([(1200000, 64)], False, 1.7, "plain"),                  # record cap above 2^20: cells of the radix sort
     ([(1200000, 64)], False, 1.7, "odd"),
     ([(1200000, 64)], False, 1.7, "narrow"),                 # cells that overflow
+    ([(1200000, 64)], False, 1.7, "groups"),                 # cells of 64 to 4096 items, sorted one by one
+    ([(1200000, 64)], False, 1.7, "group5000"),              # one cell above that
+    ([(2500000, 64)], False, 0.7, "few"),                    # 400 values: the select goes on exactly
+    ([(2500000, 64)], False, 0.7, "same"),
+    ([(2500000, 64), (9, 64), (2400000, 64)], True, 0.7, "few"),
+    ([(1200000, 64), (1300000, 64)], True, 1.7, "groups"),
 ])
 def test_rank_paths(shapes, per_module, bpw, kind):
     """Every path of the ranking (one workgroup per small segment, the fast
@@ -701,12 +707,22 @@ def test_rank_paths(shapes, per_module, bpw, kind):
     T = sum(r * c // 64 for r, c in shapes)
     p = awsrc.make_params(64, 8, 4, 256)
     rec = gen_records(T, 8, 4, 256, seed=9, device=DEV, frac_ties=0.6 if kind == "ties" else 0.0)
-    g = rec["gain"]
+    g, gt = rec["gain"], torch.Generator(device=DEV).manual_seed(4)
     if kind == "odd":
         for k, v in enumerate((float("inf"), float("nan"), 5e-324, 1e-310, -float("inf"), 0.0, -0.0, 1e300, 1e-300)):
             g[k * 7 % T::max(1, T // 5)] = v
     elif kind == "same":
         g.fill_(0.25)
+    elif kind == "few":
+        g.copy_(torch.where(g > 0, torch.exp((torch.rand(T, generator=gt, device=DEV) * 400).floor().double() / 50), g))
+    elif kind == "groups":  # equal gains, and gains that differ in the last bits, in groups of 63 to 4096
+        at = torch.randperm(T, generator=gt, device=DEV)
+        off = 0
+        for k, m in enumerate((63, 64, 65, 128, 511, 512, 513, 2000, 4095, 4096, 4096, 300)):
+            g[at[off:off + m]] = 0.01 * (k + 1) * (1 + (torch.arange(m, device=DEV) % (1 + k % 3)).double() * 2.0 ** -52)
+            off += m
+    elif kind == "group5000":
+        g[torch.randperm(T, generator=gt, device=DEV)[:5000]] = 0.01
     elif kind == "narrow":
         g.copy_(1.0 + torch.arange(T, device=DEV, dtype=torch.float64).mul_(2654435761 % T).remainder_(T) * 2.0 ** -52)
     segs, caps, off = [], [], 0
