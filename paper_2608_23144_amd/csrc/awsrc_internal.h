@@ -28,8 +28,9 @@ __host__ __device__ __forceinline__ uint64_t splitmix64(uint64_t key, uint64_t n
 //   sign[s][w]      sign words, bit j%64 of word j/64 set <=> sigma_j = -1
 //   mask[s][p][w]   bit j set <=> B_s[j, p] < 0, i.e. sigma_j xor parity(j & c_p)
 //   col[s][p]       the P selected Hadamard columns (draw order)
-//   tsign[s][j]     bit p set <=> B_s[j, p] < 0 (the mask transposed, one u16 per coordinate)
-//   sbytes(s)[c]    the same region before tsign is built, generator version 2, C <= 64, P <= 8:
+//   tsign[s][j]     bit p set <=> B_s[j, p] < 0 (the mask transposed, one u16 per coordinate);
+//                   the decoder's only table (launch_decode_setup)
+//   sbytes(s)[c]    the same region in the encoder, generator version 2, C <= 64, P <= 8:
 //                   byte p holds coordinates 8 c .. 8 c + 7 of the mask of column p (0 for p >= P)
 struct BasisTables {
   uint64_t* sign;

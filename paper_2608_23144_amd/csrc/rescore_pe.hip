@@ -312,7 +312,7 @@ __global__ __launch_bounds__(64, 2) void k_finalize_pe_modules(EncodeArgs a, con
 // gather rows take the staging blocks' place, so a second pass (a tile of the
 // wavefront needs its second seed, rare) stages them again.  Lists are in
 // tile order.  Attention projections of a 3B layer (147,456 tiles): 4 launches
-// of 47 us on the general re-score, one of 88 us here (same profiler).
+// of 47 us on the general re-score, one of 56 us here (same profiler).
 template <int PB>
 __global__ __launch_bounds__(64, 2) void k_finalize_perm_modules(EncodeArgs a, ModEntry one,
                                                                  const ModEntry* __restrict__ mods, int n_mods) {

@@ -11,6 +11,8 @@ Every test feeds both sides the same seeded synthetic tensors.  Bars:
 * repaired weights: fp32 targets within 2^-22 relative (one fp32 rounding of
   the add), bf16 targets within one bf16 half-ulp; untouched tiles bit-identical.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -63,6 +65,22 @@ def _check_encode_sample(wl, m, inp, W0_gpu, enc, tiles_idx, fmt=0, gen=1):
                             enc["alpha"].cpu().numpy()[tiles_idx] if enc.get("alpha") is not None else None)
     assert out["failures"] == 0, "\n".join(out["report"])
     return out["seed_diff"]
+
+
+def _check_screen_scores(wl, inp, W0, enc, g32, w32):
+    """The stored record is one of the two that the screen kept, best first, and
+    the screen's score of it lies within the re-score's window of its fp64 gain
+    (the wide one where either entry is flagged as a rounding knife edge)."""
+    assert bool((g32[:, 0, 0] >= g32[:, 0, 1]).all())
+    kept = (w32[:, 0] & 0xFFFF) == (enc["seed"].to(torch.int32) & 0xFFFF)[:, None]
+    assert bool(kept.any(1).all())
+    r = (inp["W"].float() - W0).double()
+    e = (inp["d"].double() * r * r).view(-1, wl.C).sum(1)
+    gain = enc["gain"]
+    edge = ((w32[:, 0] >> 16) & 1).any(1)
+    window = torch.where(edge, 3e-2 * gain.abs() + 3e-5 * e, 1e-4 * gain.abs() + 1e-7 * e)
+    score = torch.where(kept[:, 0], g32[:, 0, 0], g32[:, 0, 1]).double()
+    assert bool(((score - gain).abs() <= window).all()), float(((score - gain).abs() / window).max())
 
 
 # ------------------------------------------------------------------ backbone
@@ -178,6 +196,43 @@ def test_encode_whitened_matches_rows():
                                         bb[3][r0:r0 + 512].contiguous(), inp["d"])
         for k in ("seed", "codes", "scale", "gain"):
             assert torch.equal(part[k], enc[k][r0 * nb:(r0 + 512) * nb]), k
+
+
+def test_encode_whitened_workspace_sizes():
+    """Several C = 128 modules into workspaces from the least that is enough (the
+    former screen for all) to the queried size (the whitened one for the two that
+    it takes), some in between (whitened where a module's table fits): the same
+    records, and one byte below the least is refused."""
+    wl = workload("block3b", C=128, P=8, b=3, S=1024, d_mode="col")
+    mods = [Module("a", 1024, 4224, 0, 5, 5), Module("b", 40, 2048, 0, 6, 6), Module("c", 1100, 5632, 0, 7, 7)]
+    p = _params(wl)
+    inps = [gen_module_inputs(wl, m, DEV) for m in mods]
+    W0s = [awsrc.awsrc_backbone_rtn(i["W"])[3] for i in inps]
+    table = [m.cols // 128 * 2048 * 1024 for m in mods]  # 2 KB a (column block, seed)
+    shapes = [(m.rows, m.cols) for m in mods]
+    full = awsrc.encode_modules_workspace_bytes(p, shapes, awsrc.AWSRC_DTYPE_BF16, awsrc.AWSRC_D_PER_COL)
+    least = full - table[2]
+    ws = torch.empty(full, dtype=torch.uint8, device=DEV)
+    Ws, ds = [i["W"] for i in inps], [i["d"] for i in inps]
+    want = awsrc.awsrc_encode_modules(p, Ws, W0s, ds, workspace=ws)
+    got = {k: torch.empty_like(want[k]) for k in ("seed", "codes", "scale", "gain")}
+
+    def call(n_bytes):  # the wrapper would allocate a larger workspace itself
+        ptrs = [(ctypes.c_void_p * 3)(*[t.data_ptr() for t in ts]) for ts in (Ws, W0s, ds)]
+        dims = [(ctypes.c_int64 * 3)(*[sh[k] for sh in shapes]) for k in (0, 1)]
+        outs = [ctypes.c_void_p(got[k].data_ptr()) for k in ("seed", "codes", "scale", "gain")]
+        return awsrc.LIB.awsrc_encode_modules(ctypes.byref(p), 3, ptrs[0], awsrc.AWSRC_DTYPE_BF16, ptrs[1], ptrs[2],
+                                              awsrc.AWSRC_D_PER_COL, dims[0], dims[1], *outs, None,
+                                              ctypes.c_void_p(ws.data_ptr()), ctypes.byref(ctypes.c_size_t(n_bytes)),
+                                              ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+
+    for n in (least, least + (table[2] - table[0]) // 2, full - 256, full):
+        for t in (ws, *got.values()):
+            t.fill_(-1 if t is not ws else 0xFF)
+        assert call(n) == awsrc.AWSRC_OK
+        for k in got:
+            assert torch.equal(got[k], want[k]), (n, k)
+    assert call(least - 1) == awsrc.AWSRC_ENOSPC
 
 
 def test_encode_whitened_outlier_and_dead_blocks():
@@ -345,9 +400,7 @@ def test_encode_c16(P, b, S, d_mode, gen, fmt, name):
             assert torch.equal(got[k][off:off + T], ref[k]), (m.name, k)
         g32, w32 = awsrc.awsrc_encode_screen_lists(p, [(m.rows, m.cols)], dm, ref["workspace"])
         assert g32.shape == (T, 1, 2) and bool(((w32 & 0xFFFF) < S).all())
-        # the stored record is one of the two kept, and the screen's score of it is near its gain
-        kept = (w32[:, 0] & 0xFFFF) == (ref["seed"].to(torch.int32) & 0xFFFF)[:, None]
-        assert bool(kept.any(1).all())
+        _check_screen_scores(wl, inp, W0, ref, g32, w32)
         assert _check_encode_sample(wl, m, inp, W0, ref, np.arange(T), fmt, gen) <= max(1, T // 50)
         off += T
 
@@ -503,8 +556,7 @@ def test_encode_perm_modules(P, b, S, fmt, name):
             assert torch.equal(got[k][off:off + T], ref[k]), (m.name, k)
         g32, w32 = awsrc.awsrc_encode_screen_lists(p, [(m.rows, m.cols)], awsrc.AWSRC_D_PER_ELEM, ref["workspace"])
         assert g32.shape == (T, 1, 2) and bool(((w32 & 0xFFFF) < S).all())
-        kept = (w32[:, 0] & 0xFFFF) == (ref["seed"].to(torch.int32) & 0xFFFF)[:, None]
-        assert bool(kept.any(1).all())
+        _check_screen_scores(wl, inp, W0, ref, g32, w32)
         assert _check_encode_sample(wl, m, inp, W0, ref, np.arange(T), fmt, 2) <= max(1, T // 50)
         off += T
 
