@@ -24,18 +24,22 @@
  *  - The library never allocates device memory.  Calls that need scratch
  *    space take (workspace, ws_bytes): with workspace == NULL the call only
  *    stores the required byte count in *ws_bytes and returns AWSRC_OK;
- *    otherwise *ws_bytes must be at least that count.  The workspace must stay
- *    valid until the enqueued work has finished.
+ *    otherwise *ws_bytes must be at least that count (the encoder takes less
+ *    in one case, see awsrc_encode_tiles).  The workspace must stay valid until
+ *    the enqueued work has finished.
  *  - Every call returns an awsrc_status.  Nothing is launched when a call
  *    returns an error found during argument validation.  awsrc_last_error()
  *    returns a text description of the calling thread's last error.
- *  - The library keeps no mutable global state besides that per-thread error
- *    text and the scratch array of awsrc_encode_tiles_noalloc (with its
- *    per-device address, looked up once), so calls on different streams may
- *    run concurrently provided their buffers do not overlap (that entry point
- *    excepted, see there).  The small host copies of a call (a stream
- *    header, module tables, totals) go through host memory owned by that
- *    call, and a call that synchronizes waits on its own stream only.
+ *  - The library's mutable global state is that per-thread error text, the
+ *    scratch array of awsrc_encode_tiles_noalloc (with its per-device address,
+ *    looked up once), and one block of 256 KiB of pinned host memory, allocated
+ *    by the first call that synchronizes and kept until the process ends.
+ *    Calls on different streams and threads may run concurrently provided
+ *    their buffers do not overlap (awsrc_encode_tiles_noalloc excepted, see
+ *    there).  The small host copies of a call (a stream header, module tables,
+ *    totals) go through a 4 KiB slot of the pinned block that the call holds
+ *    while it runs, or through memory of its own when all 64 are held, and a
+ *    call that synchronizes waits on its own stream only.
  *
  * Conventions fixed where the paper leaves the choice open (the generator,
  * scale format, tie rules, backbone recipe and byte layouts) are documented
@@ -190,7 +194,11 @@ awsrc_status awsrc_backbone_sdq_dequant(const uint8_t* codes, const uint8_t* zer
  *  gain_out [T] f64 (weighted error reduction of the stored record; an
  *  all-zero record has gain 0), alpha_or_null [T, P] fp32 unquantized fit of
  *  the chosen seed, or NULL.
- *  Workspace: two-phase query as described above.
+ *  Workspace: two-phase query as described above.  With per-column weights at
+ *  C = 128, P <= 8, generator version 1, S >= 256, rows >= 1024 and T S >= 2^25
+ *  the queried size includes a table of 2 KB per (column block, seed), at most
+ *  128 MiB, for the screen that is then the faster one.  A workspace smaller by
+ *  that table is accepted too and takes the other screen, with the same records.
  */
 awsrc_status awsrc_encode_tiles(const awsrc_params* p, const void* W, int32_t w_dtype,
                                 const float* W0, int64_t rows, int64_t cols, const float* d,
@@ -236,9 +244,11 @@ awsrc_status awsrc_encode_modules(const awsrc_params* p, int32_t n_modules, cons
  * 1e-4 |g| + 1e-7 sum_j d_j r_j^2 of the first (3e-2 |g| + 3e-5 sum_j d_j
  * r_j^2 if either entry is flagged), so comparing the lists with gain_out of
  * the encode call measures the screen's error against that window.
- * Asynchronous on `stream`.  EINVAL where the call kept no
- * lists in the workspace: the per-column screen that runs the re-score
- * itself (C = 64, one seed range), or several modules encoded one by one.
+ * (Entries outside that window may differ between runs where the C = 128 table
+ * of awsrc_encode_tiles is used.)  Asynchronous on `stream`.  EINVAL where the
+ * call kept no lists in the workspace: the per-column screen that runs the
+ * re-score itself (C = 64, one seed range), or several modules, but for
+ * per-element weights at C = 64, P <= 8, generator version 1.
  */
 awsrc_status awsrc_encode_screen_lists(const awsrc_params* p, int32_t n_modules, const int64_t* rows,
                                        const int64_t* cols, int32_t d_mode, const void* workspace, float* gain_out,
@@ -248,13 +258,14 @@ awsrc_status awsrc_encode_screen_lists(const awsrc_params* p, int32_t n_modules,
  * awsrc_encode_tiles without a workspace, for callers that cannot allocate
  * device memory (code under stream capture, serving loops, harnesses that
  * forbid allocation).  Same arguments, outputs and kernels as
- * awsrc_encode_tiles; the scratch space (basis and factor tables, screened
+ * awsrc_encode_tiles (with the C = 128 table left out where it does not fit);
+ * the scratch space (basis and factor tables, screened
  * top lists) is one fixed device array per GPU inside the library, of
  * awsrc_encode_noalloc_max_bytes() bytes (64 MiB), held from the library's
  * load until the process ends; nothing is allocated or freed.  Its device
  * address is looked up on the first call on each device (the current device,
- * which `stream` must belong to).  A module whose scratch need (the size
- * awsrc_encode_tiles' query reports) exceeds the array returns AWSRC_ENOSPC
+ * which `stream` must belong to).  A module whose scratch need (the least size
+ * that awsrc_encode_tiles accepts) exceeds the array returns AWSRC_ENOSPC
  * before anything is launched.  Every call on a GPU uses the same array:
  * calls that overlap on one GPU (different streams, or threads) race and must
  * be serialized by the caller; calls ordered on one stream are safe.  Nothing
@@ -270,14 +281,17 @@ uint64_t awsrc_encode_noalloc_max_bytes(void);
 
 /*
  * Work statistic of the last awsrc_encode_tiles call that used `workspace`
- * (same pointer): the number of (tile, seed) candidates scored in full in
- * the fp32 screen, ordered on `stream` after that call.  The screen for
- * per-column weights at C = 64 first bounds every candidate by the score of
- * its unquantized fit (Eq. (3) without the rounding of Sec. 3.2's codes,
- * which no quantized fit can exceed) and scores in full only those whose
- * bound reaches the tile's current second-best score; the other screens
- * score all T * S.  The result is the same either way; the count measures
- * the work.  Reads 8 bytes of device memory and synchronizes the stream.
+ * (same pointer; of all its modules for awsrc_encode_modules): the number of
+ * (tile, seed) candidates scored in full in the fp32 screen, ordered on `stream`
+ * after that call.  The screens at C = 64 and C = 128 with P <= 8 (but C = 128
+ * with per-element weights) first bound every candidate by the score of its
+ * unquantized fit (Eq. (3) without the rounding of Sec. 3.2's codes, which no
+ * quantized fit can exceed) and score in full only those whose bound reaches
+ * the re-score's window below the tile's current best score (see
+ * awsrc_encode_screen_lists); the other screens score all T * S.  The result is
+ * the same either way; the count measures the work.  Where the C = 128 table is
+ * used (awsrc_encode_tiles) two wavefronts share a tile's best score as it
+ * comes, so that the count varies a little from run to run; the records do not.  Reads 8 bytes of device memory and synchronizes the stream.
  * EINVAL: NULL argument.
  */
 awsrc_status awsrc_encode_scored(const void* workspace, uint64_t* scored, void* stream);
