@@ -3,10 +3,11 @@
 // every module in one launch, for both weight modes and both generator
 // versions.
 //
-// What bounds it: the scoring chain of Eq. (3) and Sec. 3.2 on the vector
-// ALUs (about 130 instructions per candidate at P = 4, some 2.5 times the
-// time its memory traffic takes at S = 16); the projections and the Gram
-// entries are left to the matrix cores.
+// What bounds it: vector issue.  With per-element weights it counts 302 vector
+// instructions per 64 candidates, of them some 130 the scoring chain of Eq. (3)
+// and Sec. 3.2, the rest loads, knife edges and the re-score; at four cycles each
+// that is the launch's time.  The projections and the Gram entries are left to
+// the matrix cores (6 instructions per 64 candidates).
 //
 //   * Tiles are 16 consecutive weights, so a module is one linear array of
 //     them; a wavefront takes 64 consecutive tiles and reads them with

@@ -23,11 +23,12 @@
 //     its tile's best, the wavefront scores its candidates, the factors being
 //     in registers (a queue entry would have to carry all 44 of them).
 //
-// What bounds it: the vector ALUs (the factor and bound, about 200
-// instructions per candidate, and the scoring) beside 54 matrix instructions
-// per 64 candidates.  Attention projections of a 3B layer (9.4 M weights,
-// S = 256), whole encode: 12.19 ms on the general vector screen (a transform of
-// the permuted weights per candidate), 0.57 ms here.
+// What bounds it: the vector ALUs, 327 instructions per 64 candidates (the factor
+// and bound about 200 of them, the expansion and the scoring), beside 54 matrix
+// instructions; the two take turns more than they overlap (0.31 and 0.21 of
+// 0.52 ms).  Attention projections of a 3B layer (9.4 M weights, S = 256), whole
+// encode: 12.19 ms on the general vector screen (a transform of the permuted
+// weights per candidate), 0.57 ms here.
 #include <math.h>
 
 #include "awsrc_internal.h"

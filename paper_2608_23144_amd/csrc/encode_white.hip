@@ -35,11 +35,12 @@
 //
 // Measured, one decoder layer of a 32B model (seven modules, 3.8 M tiles, S =
 // 1024): screen 22.4 -> 11.8 ms, the whole encode 24.6 -> 14.1 ms.  Of the
-// 11.8 ms about 7 are the bound (some 500 cycles a step, of which the
-// sixteen matrix instructions take 256 and 65 vector instructions 260: with
-// the fragments in L1 it is 0.9 ms less, and neither interleaving the two kinds
-// nor reading further ahead gained) and 4.2 the rounds (2% of the candidates,
-// some 1,700 vector instructions for 64 of them).
+// 11.8 ms about 7 are the bound (some 500 cycles a step of 128 candidates, of
+// which the sixteen matrix instructions take 256 and 65 vector instructions 260:
+// with the fragments in L1 it is 0.9 ms less, and neither interleaving the two
+// kinds nor reading further ahead gained) and 4.2 the rounds (2% of the
+// candidates, some 1,700 vector instructions for 64 of them).  In all it counts
+// 144 vector instructions a step.
 #include <math.h>
 
 #include "awsrc_internal.h"
