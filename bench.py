@@ -49,40 +49,42 @@ MEASURED_TRAFFIC = {
     # 0.32 bpw stream, the reconstruction of its four nested prefixes (tile
     # ordering and the streaming pass), and the same on the SDQ backbone
     ("encode", "stack3b"): {
-        "files": ["awsrc_internal.h", "basis.hip", "encode.hip", "encode_mfma.hip", "encode_pe.hip",
+        "files": ["awsrc_internal.h", "basis.hip", "basis_gen.h", "encode.hip", "encode_mfma.hip",
+                  "mfma_bf16.h", "screen_halves.h", "screen_valu.h", "encode_white.hip", "encode_pe.hip",
                   "rescore_pe.hip", "rescore64.h"],
-        "sha256": "f5cd199c3a5245c6611d36b08ee9fe96bce500bab8f26b718433d744bcd47246",
-        "bytes": 59053364832},
+        "sha256": "cc10cf916e4511caf1962aad9abc37e037fee63c27acd97c2b86601d972754be",
+        "bytes": 59048321824},
     ("backbone", "stack3b"): {
         "files": ["awsrc_internal.h", "backbone.hip"],
-        "sha256": "dd09c1f2caf969e853367c60ca0066165bb345dae7435d5e68306dc76e166f06",
-        "bytes": 18135252320},
+        "sha256": "b27713a2dceaeaaba59b52643f2485b908123f139521693a01469a611388163a",
+        "bytes": 18135203840},
     ("decode_apply", "stack3b"): {
-        "files": ["awsrc_internal.h", "decode.hip"],
-        "sha256": "714d9fc777f576f347fc8ca0e18b6a2edc15cf7e84d2c2ff7b727c84c5f3c69c",
-        "bytes": 5032715136},
+        "files": ["awsrc_internal.h", "decode.hip", "basis_gen.h"],
+        "sha256": "ba5a84b51e62524cefae5ad44faf407d15c166be313af730ff847be100648d30",
+        "bytes": 5031884800},
     ("reconstruct_bf16", "stack3b"): {
-        "files": ["awsrc_internal.h", "decode.hip"],
-        "sha256": "714d9fc777f576f347fc8ca0e18b6a2edc15cf7e84d2c2ff7b727c84c5f3c69c",
-        "bytes": 26212606368},
+        "files": ["awsrc_internal.h", "decode.hip", "basis_gen.h"],
+        "sha256": "ba5a84b51e62524cefae5ad44faf407d15c166be313af730ff847be100648d30",
+        "bytes": 26217065224},
     ("reconstruct_bf16_sdq", "stack3b"): {
-        "files": ["awsrc_internal.h", "decode.hip"],
-        "sha256": "714d9fc777f576f347fc8ca0e18b6a2edc15cf7e84d2c2ff7b727c84c5f3c69c",
-        "bytes": 26142208960},
+        "files": ["awsrc_internal.h", "decode.hip", "basis_gen.h"],
+        "sha256": "ba5a84b51e62524cefae5ad44faf407d15c166be313af730ff847be100648d30",
+        "bytes": 26142074290},
     # one step of the 32B layer (profiles/counters_layer32b.md)
     ("encode", "layer32b"): {
-        "files": ["awsrc_internal.h", "basis.hip", "encode.hip", "encode_mfma.hip", "encode_white.hip", "encode_pe.hip",
+        "files": ["awsrc_internal.h", "basis.hip", "basis_gen.h", "encode.hip", "encode_mfma.hip",
+                  "mfma_bf16.h", "screen_halves.h", "screen_valu.h", "encode_white.hip", "encode_pe.hip",
                   "rescore_pe.hip", "rescore64.h"],
-        "sha256": "f5cd199c3a5245c6611d36b08ee9fe96bce500bab8f26b718433d744bcd47246",
-        "bytes": 8115737536},
+        "sha256": "cc10cf916e4511caf1962aad9abc37e037fee63c27acd97c2b86601d972754be",
+        "bytes": 9178695555},
     ("backbone", "layer32b"): {
         "files": ["awsrc_internal.h", "backbone.hip"],
-        "sha256": "dd09c1f2caf969e853367c60ca0066165bb345dae7435d5e68306dc76e166f06",
-        "bytes": 3185498720},
+        "sha256": "b27713a2dceaeaaba59b52643f2485b908123f139521693a01469a611388163a",
+        "bytes": 3185506304},
     ("decode_apply", "layer32b"): {
-        "files": ["awsrc_internal.h", "decode.hip"],
-        "sha256": "714d9fc777f576f347fc8ca0e18b6a2edc15cf7e84d2c2ff7b727c84c5f3c69c",
-        "bytes": 951661440},
+        "files": ["awsrc_internal.h", "decode.hip", "basis_gen.h"],
+        "sha256": "ba5a84b51e62524cefae5ad44faf407d15c166be313af730ff847be100648d30",
+        "bytes": 951625728},
 }
 
 
